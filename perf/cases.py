@@ -43,7 +43,7 @@ def listed():
         # An ordinary event of a ragged size in a ten-coordinate embedding (rows padded
         # to twelve floats and never 16-byte aligned).
         {"name": "ragged_47k_d10", "kind": "build", **_event(47_311, 10, 0.1, 256, 5, 18, 0.8, 0.15)},
-        # The benchmark's event: 120,000 hits in 8 coordinates, steps back to back.
+        # The benchmark's size: 120,000 hits in 8 coordinates, steps back to back.
         {"name": "single_120k", "kind": "step", **_event(120_000, 8, 0.1, 256, 5, 18, 0.8, 0.15), "events": 1},
         # The nearest 8 within the radius (a graph of bounded degree) on the same event.
         {"name": "nearest8_120k", "kind": "step", **_event(120_000, 8, 0.1, 8, 5, 18, 0.8, 0.15), "events": 1},
