@@ -46,8 +46,9 @@ constexpr int kKeysBlock = 1024;     // threads per workgroup of the key/histogr
 constexpr long long kKeysTwoFrom = 196608;  // events above this many rows: two points per thread in k_keys
 constexpr int kPlaceBlock = 256;     // threads per workgroup of the placement pass
 constexpr int kPlaceTile = 256;      // queries per workgroup of the placement pass (and kept tile)
-constexpr int kKeptGroup = 64;       // kept tiles per second-level total
-constexpr int kFlatTiles = 4096;     // up to this many kept tiles, placement sums the tile totals directly
+constexpr int kKeptGroup = 64;       // kept tiles per group (one workgroup of the kept-totals pass)
+constexpr int kSumsBlock = 1024;     // threads per workgroup of the kept-totals pass
+constexpr unsigned int kWaveKeys = 1024;  // hits of the longest list that one wave of the placement pass collects
 constexpr int kOwnerWindow = 4096;   // output positions formed in LDS at a time in placement
 constexpr int kPlaceMinBlocks = 512; // placement workgroups at least (all of them collect long lists)
 constexpr int kMaxEvents = 65535;  // events per call (the second grid dimension)
@@ -95,10 +96,10 @@ __host__ __device__ constexpr int cell_bits(int axes) { return axes == 4 ? 8 : 1
 // Single-address atomics serialise across the chip (about 11 ns each), so these
 // are touched only by rare events (long lists, bad input).
 struct Counters {
-    unsigned int heavy_count;      // queries whose list is long (entries of the long-list queue)
+    unsigned int heavy_count;      // queries whose list is long, of at most kWaveKeys hits (queued from the front)
     unsigned int abort;            // some event had a non-finite coordinate
     unsigned int capped;           // queries with more than K neighbours (summed after the search)
-    unsigned int pad;
+    unsigned int huge_count;       // queries with more hits (queued from the back)
     unsigned long long tested;     // pairs examined, summed over the search workgroups
     unsigned long long survived;   // pairs that reached the second stage, likewise
 };
@@ -129,12 +130,13 @@ struct Workspace {
     unsigned int *cell_count;   // [cells] histogram
     unsigned int *cell_start;   // [cells + 1] exclusive scan of the histogram
     unsigned long long *sums_cells;  // [tiles of cells + 1] per-tile histogram totals
-    unsigned long long *sums_kept;   // [tiles of kPlaceTile rows] per-tile kept totals
-    unsigned long long *sums_kept2;  // [groups of kKeptGroup tiles] per-group kept totals (more than kFlatTiles tiles)
+    unsigned long long *sums_kept;   // [tiles of kPlaceTile rows] kept neighbours before the tile in its group
+    unsigned long long *sums_kept2;  // [groups of kKeptGroup tiles] per-group kept totals
     float *sorted;              // [rows, dpad] points in cell order, zero-padded rows
     unsigned int *sorted_id;    // [2 rows] per sorted row: its original row, then its packed cell
     unsigned int *kept;         // [rows] neighbours kept per original row (| kKeptLong for a long list)
-    unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists, in queue order
+    unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists: those a wave collects from
+                                // the front in queue order, the others from the back
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries
     unsigned long long *tested; // [2 kMaxSearchBlocks] pairs examined, then pairs fully tested, per search workgroup
     unsigned int *capped_blk;   // [kMaxSearchBlocks] capped queries per search workgroup

@@ -21,8 +21,9 @@
 //                 sorted by its query's thread and the block's output formed in LDS,
 //                 then written to its (i asc, j asc) positions with coalesced
 //                 stores; then the queued lists longer than the search keeps, or
-//                 longer than K, collected again, one per workgroup at a time (the K
-//                 smallest by (D, j) from an MSB-first radix select)
+//                 longer than K, collected again, one per wave at a time (the K smallest
+//                 by (D, j) found bit by bit with ballots), those of more than kWaveKeys
+//                 hits one per workgroup (MSB-first radix select)
 //
 // Distances follow one fixed order with every product and sum rounded on its
 // own: this file is compiled with -ffp-contract=off and the pragma below.
@@ -275,7 +276,6 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
                                                    int ev_from_arg, BoundsPartial *__restrict__ part,
                                                    unsigned int *__restrict__ cell_count, long long cells,
                                                    unsigned long long *__restrict__ sums_cells, int tiles_cells,
-                                                   unsigned long long *__restrict__ sums_kept2, int groups_kept,
                                                    Counters *__restrict__ ctr) {
     const long long nblk = static_cast<long long>(gridDim.x) * gridDim.y;
     const long long bid = static_cast<long long>(blockIdx.y) * gridDim.x + blockIdx.x;
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
     const long long gstride = nblk * kBlock;
     for (long long c = gtid; c < cells; c += gstride) cell_count[c] = 0u;
     for (long long c = gtid; c < tiles_cells; c += gstride) sums_cells[c] = 0ull;
-    for (long long c = gtid; c < groups_kept; c += gstride) sums_kept2[c] = 0ull;
     if (gtid == 0) {
         Counters z = {};
         *ctr = z;
@@ -842,7 +841,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                                                    const Plan *__restrict__ plans, float r2, int K,
                                                    unsigned int *__restrict__ kept,
                                                    unsigned int *__restrict__ temp,
-                                                   unsigned int *__restrict__ long_slots,
+                                                   unsigned int *__restrict__ long_slots, long long rows,
                                                    Counters *__restrict__ ctr,
                                                    unsigned long long *__restrict__ tested_out,
                                                    unsigned int *__restrict__ capped_out, int prio) {
@@ -995,7 +994,10 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         if (mine) {
             kept[iq] = min(cnt, Ku) | (fits ? 0u : kKeptLong);
             if (cnt > Ku) ++capped;
-            if (!fits) long_slots[atomicAdd(&ctr->heavy_count, 1u)] = qrow_s[sl];
+            // Lists that a wave can collect are queued from the front, larger ones from
+            // the back (together at most one entry per row).
+            if (!fits && cnt <= kWaveKeys) long_slots[atomicAdd(&ctr->heavy_count, 1u)] = qrow_s[sl];
+            if (!fits && cnt > kWaveKeys) long_slots[rows - 1 - atomicAdd(&ctr->huge_count, 1u)] = qrow_s[sl];
         }
         if (fits && !(SEL && cnt > Ku)) {
             const uint4 *from = reinterpret_cast<const uint4 *>(lst + sl * kListCap);
@@ -1215,21 +1217,27 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
 
 // --------------------------------------------------------------- kept totals
 
-// Totals of the kept counts per placement tile, one wave per tile, and per group
-// of kKeptGroup tiles (spread-address atomics into totals cleared by the bounds
-// pass).  The last workgroup, which has no tiles, sums the search's per-workgroup
-// counts for the report, beside the others and off the placement pass's path.
-__global__ __launch_bounds__(kBlock) void k_kept_sums(int n, const unsigned int *__restrict__ kept,
-                                                      unsigned long long *__restrict__ sums_kept,
-                                                      unsigned long long *__restrict__ sums_kept2, int tiles_kept,
-                                                      const unsigned long long *__restrict__ tested,
-                                                      const unsigned int *__restrict__ capped_blk,
-                                                      int search_blocks, Counters *__restrict__ ctr) {
+// Kept counts summed per placement tile and per group of kKeptGroup tiles: block g
+// reads group g's counts, four per lane and load and all of a lane's loads issued
+// together, and writes each tile's prefix inside the group and the group's total, so
+// that a row's output position is the totals of the groups before it (a few loads for
+// a whole wave), its tile's prefix and the counts before it in its tile.  The last
+// workgroup, which has no group, sums the search's per-workgroup counts for the
+// report, beside the others and off the placement pass's path.
+__global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const unsigned int *__restrict__ kept,
+                                                          unsigned long long *__restrict__ tile_pre,
+                                                          unsigned long long *__restrict__ group_sum, int tiles_kept,
+                                                          const unsigned long long *__restrict__ tested,
+                                                          const unsigned int *__restrict__ capped_blk,
+                                                          int search_blocks, Counters *__restrict__ ctr) {
+    constexpr int kSumsWaves = kSumsBlock / 64;
+    constexpr int kTilesPerWave = kKeptGroup / kSumsWaves;
+    static_assert(kTilesPerWave * kSumsWaves == kKeptGroup && kPlaceTile == 256, "four counts per lane and tile");
     if (ctr->abort) return;
     if (blockIdx.x == gridDim.x - 1) {
-        __shared__ unsigned long long red[3][kWaves];
+        __shared__ unsigned long long red[3][kSumsWaves];
         unsigned long long t = 0, sv = 0, cp = 0;
-        for (int k = threadIdx.x; k < search_blocks; k += kBlock) {
+        for (int k = threadIdx.x; k < search_blocks; k += kSumsBlock) {
             t += tested[k];
             sv += tested[kMaxSearchBlocks + k];
             cp += capped_blk[k];
@@ -1245,7 +1253,7 @@ __global__ __launch_bounds__(kBlock) void k_kept_sums(int n, const unsigned int 
         __syncthreads();
         if (threadIdx.x == 0) {
             t = sv = cp = 0;
-            for (int w = 0; w < kWaves; ++w) {
+            for (int w = 0; w < kSumsWaves; ++w) {
                 t += red[0][w];
                 sv += red[1][w];
                 cp += red[2][w];
@@ -1256,20 +1264,36 @@ __global__ __launch_bounds__(kBlock) void k_kept_sums(int n, const unsigned int 
         }
         return;
     }
-    const int nw = static_cast<int>(gridDim.x - 1) * kWaves;
-    for (int t = static_cast<int>(blockIdx.x) * kWaves + wave_id(); t < tiles_kept; t += nw) {
-        const long long b = static_cast<long long>(t) * kPlaceTile;
-        unsigned long long s = 0;
+    __shared__ unsigned int tile_sum[kKeptGroup];
+    const int t0 = static_cast<int>(blockIdx.x) * kKeptGroup + wave_id() * kTilesPerWave;
+    uint4 c[kTilesPerWave];
 #pragma unroll
-        for (int k = 0; k < kPlaceTile / 64; ++k) {
-            const long long idx = b + k * 64 + lane_id();
-            if (idx < n) s += kept[idx] & ~kKeptLong;
+    for (int k = 0; k < kTilesPerWave; ++k) {
+        const long long i = static_cast<long long>(t0 + k) * kPlaceTile + 4 * lane_id();
+        if (i + 4 <= n) {
+            c[k] = *reinterpret_cast<const uint4 *>(kept + i);
+        } else {
+            c[k].x = i < n ? kept[i] : 0u;
+            c[k].y = i + 1 < n ? kept[i + 1] : 0u;
+            c[k].z = i + 2 < n ? kept[i + 2] : 0u;
+            c[k].w = 0u;
         }
-        s = wave_sum(s);
-        if (lane_id() == 0) {
-            sums_kept[t] = s;
-            if (s && tiles_kept > kFlatTiles) atomicAdd(&sums_kept2[t / kKeptGroup], s);
-        }
+    }
+    // A tile holds at most 256 x 4096 edges and a group 64 times that: 32 bits do.
+#pragma unroll
+    for (int k = 0; k < kTilesPerWave; ++k) {
+        const unsigned int v = (c[k].x & ~kKeptLong) + (c[k].y & ~kKeptLong) + (c[k].z & ~kKeptLong) +
+                               (c[k].w & ~kKeptLong);
+        const unsigned int t = wave_sum(v);
+        if (lane_id() == 0) tile_sum[wave_id() * kTilesPerWave + k] = t;
+    }
+    __syncthreads();
+    if (wave_id() == 0) {
+        const unsigned int v = tile_sum[lane_id()];
+        const unsigned int inc = wave_inclusive_scan(v);
+        const int t = static_cast<int>(blockIdx.x) * kKeptGroup + lane_id();
+        if (t < tiles_kept) tile_pre[t] = inc - v;
+        if (lane_id() == 63) group_sum[blockIdx.x] = inc;
     }
 }
 
@@ -1292,8 +1316,8 @@ struct LongLds {
 // a list with more hits is selected by enumerating its candidates again per pass.
 constexpr unsigned int kKeyCap = kOwnerWindow;
 
-// One long list, collected again by the whole workgroup (every thread calls this
-// with the same arguments): the query's candidates are enumerated over the same
+// One list of more than kWaveKeys hits, collected again by the whole workgroup (every
+// thread calls this with the same arguments): the query's candidates are enumerated over the same
 // runs of cells as in the search and its hits keyed (bits(D) << 32 | j), which
 // orders them by (D, j) since D is never negative.  With more hits than n_out
 // (the cap binds) the n_out-th smallest key is found by an MSB-first radix select
@@ -1460,11 +1484,191 @@ __device__ void long_list(const float *__restrict__ sorted, const unsigned int *
     __syncthreads();
 }
 
+// The lists a single wave collects: at most kWaveKeys hits.
+
+// Sorts R values per lane ascending, element r of lane l at position 64 r + l, by a
+// bitonic network: exchanges at distances of 64 and more stay inside a lane.
+template <int R>
+__device__ __forceinline__ void wave_sort(unsigned int (&v)[R]) {
+    const unsigned int lane = static_cast<unsigned int>(lane_id());
+#pragma unroll
+    for (unsigned int k = 2; k <= 64u * R; k <<= 1) {
+#pragma unroll
+        for (unsigned int j = k >> 1; j > 0; j >>= 1) {
+            if (j >= 64u) {
+#pragma unroll
+                for (unsigned int r = 0; r < R; ++r) {
+                    const unsigned int o = r ^ (j / 64u);
+                    if (o > r) {
+                        const unsigned int lo = min(v[r], v[o]), hi = max(v[r], v[o]);
+                        const bool up = ((r * 64u) & k) == 0u;  // k >= 128 here
+                        v[r] = up ? lo : hi;
+                        v[o] = up ? hi : lo;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (unsigned int r = 0; r < R; ++r) {
+                    const unsigned int p = static_cast<unsigned int>(__shfl_xor(static_cast<int>(v[r]), j));
+                    const bool up = (((r * 64u) | lane) & k) == 0u;
+                    const bool low = (lane & j) == 0u;
+                    v[r] = up == low ? min(v[r], p) : max(v[r], p);
+                }
+            }
+        }
+    }
+}
+
+// Loads h ids from LDS, sorts them and writes them local to their event.
+template <int R>
+__device__ __forceinline__ void wave_emit(const unsigned int *ids, unsigned int h, long long row0,
+                                          long long *__restrict__ out) {
+    unsigned int v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
+        v[r] = e < h ? ids[e] : 0xffffffffu;
+    }
+    wave_sort<R>(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
+        if (e < h) out[e] = static_cast<long long>(v[r]) - row0;
+    }
+}
+
+// Keeps the `want` smallest of h hits by (D, id), want < h, and compacts their ids to
+// the front of ids.  The want-th smallest D is found bit by bit from the top (D >= 0,
+// so its bits order like the value), counting with ballots; a step that leaves exactly
+// `want` hits below ends the search, and only hits tied at that D are then told apart
+// by id, in the same way.
+template <int R>
+__device__ __forceinline__ void wave_select(const unsigned int *dist, unsigned int *ids, unsigned int h,
+                                            unsigned int want) {
+    unsigned int d[R], v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
+        d[r] = e < h ? dist[e] : 0xffffffffu;
+        v[r] = e < h ? ids[e] : 0xffffffffu;
+    }
+    unsigned int T = 0u;  // the largest value with fewer than `want` D bits below it
+    bool split = false;
+    for (int b = 30; b >= 0; --b) {
+        const unsigned int c = T | (1u << b);
+        unsigned int n = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) n += __popcll(__builtin_amdgcn_ballot_w64(d[r] < c));
+        if (n == want) {
+            T = c;
+            split = true;
+            break;
+        }
+        if (n < want) T = c;
+    }
+    unsigned int U = 0u;  // ties at T are kept below this id
+    if (!split) {
+        unsigned int below = 0, at = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            below += __popcll(__builtin_amdgcn_ballot_w64(d[r] < T));
+            at += __popcll(__builtin_amdgcn_ballot_w64(d[r] == T));
+        }
+        const unsigned int need = want - below;
+        U = 0xffffffffu;
+        if (at > need) {
+            U = 0u;
+            for (int b = 30; b >= 0; --b) {  // ids are below 2^31
+                const unsigned int c = U | (1u << b);
+                unsigned int n = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) n += __popcll(__builtin_amdgcn_ballot_w64(d[r] == T && v[r] < c));
+                if (n < need) U = c;
+            }
+            ++U;  // U was the need-th smallest id
+        }
+    }
+    wave_lds_sync();
+    unsigned int at = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const bool keep = d[r] < T || (d[r] == T && v[r] < U);
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+        if (keep) ids[at + prefix_count(m)] = v[r];
+        at += static_cast<unsigned int>(__popcll(m));
+    }
+    wave_lds_sync();
+}
+
+// One long list, collected again by one wave: the query's candidates are enumerated
+// over the same runs of cells as in the search, 64 at a time, one per lane with its
+// whole row; hits go to LDS (dist and ids, kWaveKeys entries each).  With more hits
+// than n_out (the cap binds) the n_out nearest are selected; the kept ids are sorted in
+// registers and written, local to the query's event, to out[0, n_out).  A list takes a
+// wave a few hundred instructions and no barrier, and as many lists are in flight as
+// waves.  Collecting each with a whole workgroup, as the larger lists are (long_list,
+// a bitonic network with a barrier per step), the placement pass took 690 us for 51,000
+// lists of about 45 entries, against 111 us; 53 us against 17 on a 120k-point event
+// with some 2,000 lists of 17 and more, and 380 us against 57 with the nearest 32 of
+// about 95 kept for 17,000 queries.
+template <int DP>
+__device__ __forceinline__ void wave_list(const float *__restrict__ sorted, const unsigned int *__restrict__ sorted_id,
+                          const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
+                          unsigned int slot, unsigned int pc, float r2, unsigned int n_out, long long row0,
+                          long long *__restrict__ out, unsigned int *dist, unsigned int *ids, unsigned int *mark) {
+    const int lane = lane_id();
+    int u[kMaxAxes];
+    unpack_cell(pc, P.axes, u);
+    unsigned int start, pre, end;
+    const unsigned int M = wave_runs(u, cell0, P, run_lane(P), cell_start, start, pre, end);
+    const float *qrow = sorted + static_cast<size_t>(slot) * DP;
+    unsigned int h = 0;
+    for (unsigned int b = 0; b < M; b += 64u) {
+        wave_lds_sync();
+        mark[lane] = 0u;
+        wave_lds_sync();
+        if (end > pre && pre < b + 64u && end > b) mark[pre > b ? pre - b : 0u] = lane + 1u;
+        wave_lds_sync();
+        const int r = static_cast<int>(wave_scan_max(mark[lane])) - 1;
+        const unsigned int mm = b + lane;
+        const unsigned int srow = static_cast<unsigned int>(__shfl(start, r)) +
+                                  (mm - static_cast<unsigned int>(__shfl(pre, r)));
+        const unsigned int s = mm < M ? srow : slot;
+        const unsigned int j = sorted_id[2u * static_cast<size_t>(s)];
+        float c[DP];
+        load_row<DP>(sorted, s, c);
+        const float D = sq_dist<DP>(c, qrow);
+        const bool hit = D < r2 && s != slot;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+        const unsigned int pos = h + prefix_count(m);
+        if (hit && pos < kWaveKeys) {  // the search counted no more hits than fit
+            dist[pos] = __float_as_uint(D);
+            ids[pos] = j;
+        }
+        h += static_cast<unsigned int>(__popcll(m));
+    }
+    wave_lds_sync();
+    h = min(h, kWaveKeys);
+    if (h > n_out) {
+        if (h <= 64u) wave_select<1>(dist, ids, h, n_out);
+        else if (h <= 128u) wave_select<2>(dist, ids, h, n_out);
+        else if (h <= 256u) wave_select<4>(dist, ids, h, n_out);
+        else wave_select<kWaveKeys / 64>(dist, ids, h, n_out);
+        h = n_out;
+    }
+    if (h <= 64u) wave_emit<1>(ids, h, row0, out);
+    else if (h <= 128u) wave_emit<2>(ids, h, row0, out);
+    else if (h <= 256u) wave_emit<4>(ids, h, row0, out);
+    else if (h <= 512u) wave_emit<8>(ids, h, row0, out);
+    else wave_emit<kWaveKeys / 64>(ids, h, row0, out);
+    wave_lds_sync();
+}
+
 // ------------------------------------------------------------------- place
 
 // Block b < tiles_kept owns queries [kPlaceTile b, kPlaceTile (b + 1)), one per
-// thread.  Its first output position is the sum of the kept totals before it
-// (whole groups of kKeptGroup tiles, then the tiles of its own group); a block
+// thread.  Its first output position is the sum of the totals of the groups of
+// kKeptGroup tiles before its own and its prefix inside its group; a block
 // scan of its kept counts gives each query's offset.  Lists in the fixed
 // kListCap-slot places come from the search in the order their hits were found:
 // each query's thread sorts its list in registers.  The block's output is then
@@ -1474,14 +1678,15 @@ __device__ void long_list(const float *__restrict__ sorted, const unsigned int *
 // collector.  Indices are made local to each query's event.  Block 0 writes the
 // report and the status; the block holding an event's first row writes its edge
 // offset.  Then every block, including those past the tiles (the grid has at least
-// kPlaceMinBlocks), collects the long lists of the search's queue in turn: the
-// list's output position is the sum of the tile totals before its query's tile and
-// of the kept counts before it in that tile.
+// kPlaceMinBlocks), collects the long lists of the search's queue in turn, one per
+// wave, then the larger ones, one per workgroup: the list's output position is the
+// totals of the groups before its query's tile, the tile's prefix in its group and the
+// kept counts before the query in its tile.
 template <int DP>
 __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const EventDesc *__restrict__ ev,
                                                        int n_events, const unsigned int *__restrict__ kept,
-                                                       const unsigned long long *__restrict__ sums_kept,
-                                                       const unsigned long long *__restrict__ sums_kept2,
+                                                       const unsigned long long *__restrict__ tile_pre,
+                                                       const unsigned long long *__restrict__ group_sum,
                                                        int groups_kept, int tiles_kept,
                                                        const unsigned int *__restrict__ long_slots,
                                                        const unsigned int *__restrict__ temp,
@@ -1504,6 +1709,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     unsigned int *wdst = wbuf + kOwnerWindow;
     __shared__ unsigned long long scratch[kWaves];
     __shared__ LongLds<DP> L;
+    __shared__ unsigned int mark[kWaves][64];
     const bool abort = ctr->abort != 0;
     const int b = static_cast<int>(blockIdx.x);
     const bool tile_block = b < tiles_kept;
@@ -1530,26 +1736,15 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
             v[4 * c + 3] = w.w;
         }
     }
-    // Sum of the tile totals before tile t (and of all of them), one part per thread.
+    // Kept neighbours before tile t (and all of them), one part per thread.
     auto tile_prefix = [&](int t, unsigned long long &before, unsigned long long &all) {
-        before = 0;
+        const int gt = t / kKeptGroup;
+        before = threadIdx.x == 0 ? tile_pre[t] : 0ull;
         all = 0;
-        if (tiles_kept <= kFlatTiles) {
-            // Few tiles: the tile totals are summed directly.
-            for (int x = threadIdx.x; x < tiles_kept; x += kPlaceBlock) {
-                const unsigned long long y = sums_kept[x];
-                all += y;
-                if (x < t) before += y;
-            }
-        } else {
-            const int gt = t / kKeptGroup;
-            for (int x = threadIdx.x; x < groups_kept; x += kPlaceBlock) {
-                const unsigned long long y = sums_kept2[x];
-                all += y;
-                if (x < gt) before += y;
-            }
-            const int x = gt * kKeptGroup + static_cast<int>(threadIdx.x);
-            if (threadIdx.x < kKeptGroup && x < t) before += sums_kept[x];
+        for (int x = threadIdx.x; x < groups_kept; x += kPlaceBlock) {
+            const unsigned long long y = group_sum[x];
+            all += y;
+            if (x < gt) before += y;
         }
     };
     __shared__ unsigned long long red[3 * kWaves];
@@ -1568,7 +1763,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         rep.survived = abort ? 0ull : ctr->survived;
         rep.abort = abort ? 1 : 0;
         rep.capped = abort ? 0u : ctr->capped;
-        rep.heavy = ctr->heavy_count;
+        rep.heavy = ctr->heavy_count + ctr->huge_count;
         rep.n_cells = P.n_cells;
         for (int p = 0; p < kMaxAxes; ++p) {
             rep.G[p] = P.G[p];
@@ -1659,10 +1854,49 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         }
     }
     if (abort || overflow) return;
-    // Long lists of the search's queue, every gridDim-th one.
-    const unsigned int n_long = ctr->heavy_count;
-    for (unsigned int h = blockIdx.x; h < n_long; h += gridDim.x) {
-        const unsigned int slot = long_slots[h];
+    // Long lists that a wave collects.  The queue is in the search's order, so
+    // neighbouring entries share candidates: each XCD takes a contiguous share, its
+    // waves in turn.
+    __syncthreads();
+    {
+        const unsigned int xcd = blockIdx.x % 8u;
+        const unsigned int xnb = gridDim.x / 8u + (xcd < gridDim.x % 8u ? 1u : 0u);
+        const unsigned long long n_long = ctr->heavy_count;
+        const unsigned int lo = static_cast<unsigned int>(n_long * xcd / 8u);
+        const unsigned int hi = static_cast<unsigned int>(n_long * (xcd + 1u) / 8u);
+        unsigned int *lds = wbuf + wave_id() * (2 * kWaveKeys);
+        for (unsigned int h = lo + blockIdx.x / 8u * kWaves + wave_id(); h < hi; h += xnb * kWaves) {
+            const unsigned int slot = uniform(long_slots[h]);
+            if (static_cast<long long>(slot) >= rows) continue;  // only a corrupted queue
+            const uint2 id = reinterpret_cast<const uint2 *>(sorted_id)[slot];
+            const long long gi = uniform(id.x);  // the query's original row
+            const int t = static_cast<int>(gi / kPlaceTile);
+            if (gi >= rows || t >= tiles_kept) continue;  // likewise
+            // Output position: one 16-byte load per lane covers the tile's counts.
+            unsigned long long at = lane_id() == 0 ? tile_pre[t] : 0ull;
+            for (int x = lane_id(); x < t / kKeptGroup; x += 64) at += group_sum[x];
+            const long long x0 = static_cast<long long>(t) * kPlaceTile + 4 * lane_id();
+            if (x0 < gi) {  // then x0 .. x0 + 3 lie in the array (256-byte aligned, padded)
+                const uint4 c = *reinterpret_cast<const uint4 *>(kept + x0);
+                at += c.x & ~kKeptLong;
+                if (x0 + 1 < gi) at += c.y & ~kKeptLong;
+                if (x0 + 2 < gi) at += c.z & ~kKeptLong;
+                if (x0 + 3 < gi) at += c.w & ~kKeptLong;
+            }
+            const unsigned int nq = uniform(kept[gi]) & ~kKeptLong;
+            const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
+            const Plan P = plans[e];
+            at = wave_sum(at);
+            if (at + nq > cap) continue;  // cannot happen when E <= cap
+            wave_list<DP>(sorted, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot,
+                          uniform(id.y), r2, nq, ev[e].row0, dst + at, lds, lds + kWaveKeys, mark[wave_id()]);
+        }
+    }
+    __syncthreads();
+    // Larger ones, collected by the whole workgroup, every gridDim-th one.
+    const unsigned int n_huge = ctr->huge_count;
+    for (unsigned int h = blockIdx.x; h < n_huge; h += gridDim.x) {
+        const unsigned int slot = long_slots[rows - 1 - h];
         if (static_cast<long long>(slot) >= rows) continue;  // only a corrupted queue
         const long long gi = sorted_id[2u * slot];  // the query's original row
         const int t = static_cast<int>(gi / kPlaceTile);
@@ -1697,17 +1931,16 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     if (a.K < kListCap)
         hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, rows, ws.ctr, ws.tested, ws.capped_blk,
                            a.search_prio);
     else
         hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, rows, ws.ctr, ws.tested, ws.capped_blk,
                            a.search_prio);
     mark(5);
-    const long long kb = (static_cast<long long>(ws.tiles_kept_n) + kWaves - 1) / kWaves;
-    const int kblocks = static_cast<int>(kb > 2048 ? 2048 : kb) + 1;  // and one for the search's counts
-    hipLaunchKernelGGL(k_kept_sums, dim3(kblocks), dim3(kBlock), 0, a.stream, static_cast<int>(rows), ws.kept,
+    // One block per group of tiles, and one for the search's counts.
+    hipLaunchKernelGGL(k_kept_sums, dim3(ws.groups_kept_n + 1), dim3(kSumsBlock), 0, a.stream, rows, ws.kept,
                        ws.sums_kept, ws.sums_kept2, ws.tiles_kept_n, ws.tested, ws.capped_blk, a.search_blocks,
                        ws.ctr);
     mark(6);
@@ -1761,7 +1994,7 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
     mark(0);
     hipLaunchKernelGGL(k_bounds, dim3(a.bounds_blocks, a.n_events), dim3(kBlock), 0, a.stream, a.d, dd, vec4,
                        ws.ev, a.ev0, a.ev_from_arg, ws.part, ws.cell_count, ws.cells, ws.sums_cells,
-                       ws.tiles_cells_n, ws.sums_kept2, ws.groups_kept_n, ws.ctr);
+                       ws.tiles_cells_n, ws.ctr);
     mark(1);
     if (keys_per == 2)
         hipLaunchKernelGGL(k_keys<2>, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
