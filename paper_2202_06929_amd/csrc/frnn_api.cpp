@@ -275,7 +275,10 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
         long long m = per_wave < 128 ? 1 : per_wave / 128 + 1;
         m = m > 4 ? 4 : m;
         if (config && config->grid_mult > 0) m = config->grid_mult;
-        const long long b = resident * m;
+        // Small calls: at least kMinWaveRows rows per wave, and one workgroup per XCD.
+        const long long most = (rows + kWaves * kMinWaveRows - 1) / (kWaves * kMinWaveRows);
+        long long b = resident * m;
+        if (b > most) b = most < 8 ? 8 : most;
         a.search_blocks = static_cast<int>(b > kMaxSearchBlocks ? kMaxSearchBlocks : b);
         a.search_prio = a.search_blocks <= resident ? 1 : 0;
     }

@@ -28,6 +28,11 @@ constexpr int kMaxSearchBlocks = 8192;
 // A cell's fixed cost in the search (its runs' bounds, its candidates' first
 // loads), in queries, when the queries are divided among the waves by work.
 constexpr unsigned int kTileWeight = 4;
+// Fewest rows per wave of the search.  Below it more waves only repeat the fixed costs
+// (the cells they cut, partly filled list write-outs): a 20,000-point event of crowded
+// cells took 164, 164, 144, 132 and 145 us with at least 1, 2, 4, 8 and 16 rows, and a
+// 2,000-point event 53.1, 52.6, 52.6, 54.1 and 58.0 us.
+constexpr long long kMinWaveRows = 4;
 // The search's queries are cut into search_pieces(DP) pieces of equal work per
 // wave: each wave takes one piece of its XCD's share, then claims the share's
 // other pieces one at a time from kPools counters per XCD, so that waves that

@@ -577,13 +577,19 @@ __device__ __forceinline__ unsigned long long floor_div(unsigned long long a, un
 // starts there at the query that many weight units past the cell's fixed cost
 // (at its first query if it falls within the cost), so a dense cell can still be
 // split among waves.  wave_start[k] is that sorted row; wave_start[n_waves] =
-// rows.
+// rows.  The pieces that start in a tile are taken one per thread, each finding its
+// cell by bisection over the tile's weights in LDS.  (Walked cell by cell in the thread
+// that holds the cells, every lane waits for the fullest cell of its wave, 16 times
+// over: 51 us against 4.6 for 2,000 points, 23 against 6.8 for 20,000 in crowded cells,
+// 5.5 against 5.2 for 120,000 in sparse ones.)
 __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__restrict__ in, long long len,
                                                        const unsigned long long *__restrict__ sums, int tiles,
                                                        unsigned int *__restrict__ out,
                                                        unsigned int *__restrict__ wave_start, int n_waves,
                                                        long long rows, unsigned int *__restrict__ claims) {
     __shared__ unsigned long long red[4 * kWaves];
+    __shared__ __align__(16) unsigned int cell_w[kScanTile], cell_c[kScanTile];
+    __shared__ unsigned int tile_w;
     const long long base = static_cast<long long>(blockIdx.x) * kScanTile;
     if (base > len) return;
     constexpr int kPer = kScanTile / kBlock;
@@ -644,40 +650,16 @@ __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__res
         pre += w < wave_id() ? red[3 * kWaves + w] : 0ull;
     }
     pre += inc - mine;
-    unsigned long long run_c = cb + (pre & 0xffffffffull), run_w = wb + (pre >> 32);
-    const unsigned long long nw = static_cast<unsigned long long>(n_waves);
-    // Wave k starts at weight B_k = floor(k W / nw).  The thread's first wave is the
-    // smallest k with k W >= run_w nw (then B_k >= run_w); later ones follow by
-    // B_{k+1} = B_k + q + carry, with W = q nw + m and the remainder of k W / nw
-    // carried, so no division runs per wave.
-    unsigned int starts[kPer];
-    unsigned long long k = nw, B = 0, rem = 0, q = 0, m = 0;
-    if (W) {
-        q = floor_div(W, nw);
-        m = W - q * nw;
-        const unsigned long long target = run_w * nw;
-        k = floor_div(target + W - 1, W);
-        if (k == 0) k = 1;  // wave 0 starts at row 0
-        B = floor_div(k * W, nw);
-        rem = k * W - B * nw;
-    }
+    // The tile's counts and weights before each cell (relative to the tile's first).
+    unsigned int run_c = static_cast<unsigned int>(pre), run_w = static_cast<unsigned int>(pre >> 32);
+    const unsigned int first_row = static_cast<unsigned int>(cb);  // rows stay below 2^31
+    unsigned int starts[kPer], weights[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-        starts[j] = static_cast<unsigned int>(run_c);
-        const unsigned long long w = v[j] + (v[j] ? kTileWeight : 0u);
-        for (; k < nw && B < run_w + w; ++k) {
-            // B lies in this cell: past its fixed cost, one weight unit per query.
-            const unsigned long long past = B - run_w;
-            wave_start[k] = static_cast<unsigned int>(run_c + (past > kTileWeight ? past - kTileWeight : 0ull));
-            B += q;
-            rem += m;
-            if (rem >= nw) {
-                rem -= nw;
-                ++B;
-            }
-        }
+        starts[j] = first_row + run_c;
+        weights[j] = run_w;
         run_c += v[j];
-        run_w += w;
+        run_w += v[j] + (v[j] ? kTileWeight : 0u);
     }
     // cell_start has len + 1 entries: whole groups as uint4, the rest one by one.
     if (first + kPer <= len + 1) {
@@ -689,6 +671,36 @@ __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__res
 #pragma unroll
         for (int j = 0; j < kPer; ++j)
             if (first + j <= len) out[first + j] = starts[j];
+    }
+    {
+        uint4 *ws = reinterpret_cast<uint4 *>(cell_w + threadIdx.x * kPer);
+        uint4 *cs = reinterpret_cast<uint4 *>(cell_c + threadIdx.x * kPer);
+#pragma unroll
+        for (int j = 0; j < kPer / 4; ++j) {
+            ws[j] = make_uint4(weights[4 * j], weights[4 * j + 1], weights[4 * j + 2], weights[4 * j + 3]);
+            cs[j] = make_uint4(starts[4 * j], starts[4 * j + 1], starts[4 * j + 2], starts[4 * j + 3]);
+        }
+        if (threadIdx.x == kBlock - 1) tile_w = run_w;
+    }
+    __syncthreads();
+    // Pieces k with B_k = floor(k W / n) in the tile's weights [wb, wb + tile_w): those
+    // with k W >= wb n and k W < (wb + tile_w) n.
+    if (W && tile_w) {
+        const unsigned long long nw = static_cast<unsigned long long>(n_waves);
+        unsigned long long k0 = floor_div(wb * nw + W - 1, W);
+        const unsigned long long k1 = floor_div((wb + tile_w) * nw + W - 1, W);
+        if (k0 == 0) k0 = 1;  // wave 0 starts at row 0
+        for (unsigned long long k = k0 + threadIdx.x; k < k1 && k < nw; k += kBlock) {
+            const unsigned int at = static_cast<unsigned int>(floor_div(k * W, nw) - wb);
+            int lo = 0, hi = kScanTile - 1;  // the last cell that starts at or before it
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (cell_w[mid] <= at) lo = mid;
+                else hi = mid - 1;
+            }
+            const unsigned int past = at - cell_w[lo];
+            wave_start[k] = cell_c[lo] + (past > kTileWeight ? past - kTileWeight : 0u);
+        }
     }
     if (blockIdx.x == 0) {
         if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
