@@ -29,9 +29,9 @@ constexpr int kMaxSearchBlocks = 8192;
 // loads), in queries, when the queries are divided among the waves by work.
 constexpr unsigned int kTileWeight = 4;
 // Fewest rows per wave of the search.  Below it more waves only repeat the fixed costs
-// (the cells they cut, partly filled list write-outs): a 20,000-point event of crowded
-// cells took 164, 164, 144, 132 and 145 us with at least 1, 2, 4, 8 and 16 rows, and a
-// 2,000-point event 53.1, 52.6, 52.6, 54.1 and 58.0 us.
+// (the cells they cut, partly filled list write-outs), above it too few run at once: a
+// 20,000-point event of crowded cells took 121, 120, 119, 124 and 140 us with at least
+// 1, 2, 4, 8 and 16 rows, and a 2,000-point event 55.5, 54.8, 55.0, 57.0 and 60.6 us.
 constexpr long long kMinWaveRows = 4;
 // The search's queries are cut into search_pieces(DP) pieces of equal work per
 // wave: each wave takes one piece of its XCD's share, then claims the share's
@@ -99,12 +99,12 @@ struct Plan {
 __host__ __device__ constexpr int cell_bits(int axes) { return axes == 4 ? 8 : 10; }
 
 // Single-address atomics serialise across the chip (about 11 ns each), so these
-// are touched only by rare events (long lists, bad input).
+// are touched only by rare events (bad input) or once.
 struct Counters {
-    unsigned int heavy_count;      // queries whose list is long, of at most kWaveKeys hits (queued from the front)
+    unsigned int pad0;
     unsigned int abort;            // some event had a non-finite coordinate
     unsigned int capped;           // queries with more than K neighbours (summed after the search)
-    unsigned int huge_count;       // queries with more hits (queued from the back)
+    unsigned int pad1;
     unsigned long long tested;     // pairs examined, summed over the search workgroups
     unsigned long long survived;   // pairs that reached the second stage, likewise
 };
@@ -140,13 +140,14 @@ struct Workspace {
     float *sorted;              // [rows, dpad] points in cell order, zero-padded rows
     unsigned int *sorted_id;    // [2 rows] per sorted row: its original row, then its packed cell
     unsigned int *kept;         // [rows] neighbours kept per original row (| kKeptLong for a long list)
-    unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists: those a wave collects from
-                                // the front in queue order, the others from the back
+    unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists, queued per XCD in the part
+                                // of the XCD's rows
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries
     unsigned long long *tested; // [2 kMaxSearchBlocks] pairs examined, then pairs fully tested, per search workgroup
     unsigned int *capped_blk;   // [kMaxSearchBlocks] capped queries per search workgroup
     unsigned int *wave_start;   // [kMaxSearchBlocks kWaves kMaxPieces + 1] first sorted row of each search piece
-    unsigned int *claims;       // [8 kPools kPoolStride] the search's piece counters, cleared by the cell scan
+    unsigned int *claims;       // [8 kPools kPoolStride] the search's piece counters and, beside each XCD's first,
+                                // its long-list counts; cleared by the cell scan
     long long rows;
     long long cells;
     int tiles_cells_n;

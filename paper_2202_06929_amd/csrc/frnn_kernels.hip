@@ -556,6 +556,24 @@ __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
 
 // ------------------------------------------------------------------- scans
 
+// Workgroups of the search before those of XCD x (0..8): workgroups are dealt to the 8
+// XCDs round-robin, and each XCD works on a contiguous share of the pieces.
+__device__ __forceinline__ unsigned int xcd_first_block(unsigned int x, unsigned int blocks) {
+    return x * (blocks / 8u) + min(x, blocks % 8u);
+}
+
+// The queries with long lists are queued per XCD, in the part of long_slots that
+// belongs to the XCD's rows: lists that a wave of the placement pass can collect from
+// the front, larger ones from the back.  With one counter for all of them the search of
+// an event with many long lists waited for its atomics, one per wave that writes lists
+// out: 87 us against 30 for 60,000 points with some 45 neighbours each, 45 against 22
+// for 20,000 in denser ones, 32.4 against 27.5 for a 120k-point event where 2% of the
+// lists are long.
+constexpr int kLongCount = 1, kHugeCount = 2;  // words of an XCD's first claim line
+__device__ __forceinline__ unsigned int *long_counter(unsigned int *claims, unsigned int xcd, int which) {
+    return claims + xcd * kPools * kPoolStride + which;
+}
+
 // floor(a / b) for a < 2^52, b > 0: the quotient rounded in double is within one
 // of the exact, and integer products settle it.
 __device__ __forceinline__ unsigned long long floor_div(unsigned long long a, unsigned long long b) {
@@ -703,7 +721,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__res
         }
     }
     if (blockIdx.x == 0) {
+        static_assert(8 * kPools <= kBlock && kHugeCount < kPoolStride, "one claim line per thread");
         if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
+        if (threadIdx.x < 8) {
+            *long_counter(claims, threadIdx.x, kLongCount) = 0u;
+            *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
+        }
         if (W == 0) {  // no rows: every share is empty
             for (int t = threadIdx.x; t <= n_waves; t += kBlock) wave_start[t] = 0u;
         } else if (threadIdx.x == 0) {
@@ -789,9 +812,11 @@ __device__ __forceinline__ int run_count(const Plan &P) {
     return P.axes == 4 ? side * side * side : side * side;
 }
 
-// Offsets along axes 1..3 of the run a lane builds (lanes below run_count).
+// Offsets along axes 1..3 of the run a lane builds (lanes below run_count), and what
+// they add to the key of a cell.
 struct RunLane {
     int a[3];
+    int key;
     bool live;
 };
 
@@ -802,6 +827,7 @@ __device__ __forceinline__ RunLane run_lane(const Plan &P) {
     rl.a[0] = t % side - R;
     rl.a[1] = (t / side) % side - R;
     rl.a[2] = P.axes == 4 ? t / (side * side) - R : 0;
+    rl.key = ((rl.a[2] * P.G[2] + rl.a[1]) * P.G[1] + rl.a[0]) * P.G[0];
     return rl;
 }
 
@@ -815,14 +841,15 @@ __device__ __forceinline__ unsigned int wave_runs(const int (&u)[kMaxAxes], unsi
     const int R = P.reach;
     // Branch-free: every lane loads (a lane without a run reads the event's first
     // row of cells, a valid address) and keeps its run only if it is inside the grid
-    // (the unsigned comparisons also reject negative coordinates).
+    // (the unsigned comparisons also reject negative coordinates).  The key of the
+    // cell's row is wave-uniform; a lane adds its run's offset.
     const int y = u[1] + rl.a[0], z = u[2] + rl.a[1], w = u[3] + rl.a[2];
     const bool ok = rl.live & (static_cast<unsigned int>(y) < static_cast<unsigned int>(P.G[1])) &
                     (static_cast<unsigned int>(z) < static_cast<unsigned int>(P.G[2])) &
                     (static_cast<unsigned int>(w) < static_cast<unsigned int>(P.G[3]));
     const int xlo = max(u[0] - R, 0), xhi = min(u[0] + R, P.G[0] - 1);
-    const unsigned int row =
-        cell0 + (ok ? static_cast<unsigned int>(((w * P.G[2] + z) * P.G[1] + y) * P.G[0]) : 0u);
+    const int crow = ((u[3] * P.G[2] + u[2]) * P.G[1] + u[1]) * P.G[0];
+    const unsigned int row = cell0 + static_cast<unsigned int>(ok ? crow + rl.key : 0);
     const unsigned int s0 = cell_start[row + xlo];
     const unsigned int s1 = cell_start[row + xhi + 1];
     start = ok ? s0 : 0u;
@@ -831,6 +858,47 @@ __device__ __forceinline__ unsigned int wave_runs(const int (&u)[kMaxAxes], unsi
     pre = end - len;
     return __builtin_amdgcn_readlane(end, 63);
 }
+
+// Numbers a tile's candidates: lane l of chunk b gets the sorted row of candidate
+// b + l.  The runs that hold candidates are kept in order in LDS, each as (first row -
+// first candidate); a run that starts inside a chunk marks its lane there with the
+// chunk's own tag (so that nothing is cleared), and a ballot of the marks counts the
+// runs up to each lane.  (Against marks spread by a prefix maximum over the wave and two
+// cross-lane reads per chunk, with a tile's candidate rows masked where they arrive: the
+// 300k-point 12-D search took 89 us, now 83.)
+struct RunMap {
+    unsigned int *off;   // [64] per wave: the runs with candidates
+    unsigned int *mark;  // [64] per wave, cleared once before the first chunk
+    unsigned int tag = 0;
+    unsigned int before = 0;  // runs that start before the next chunk
+    __device__ __forceinline__ void clear() {
+        mark[lane_id()] = 0u;
+        wave_lds_sync();
+    }
+    // A new tile, from wave_runs.
+    __device__ __forceinline__ void begin(unsigned int start, unsigned int pre, unsigned int end) {
+        const unsigned long long some = __builtin_amdgcn_ballot_w64(end > pre);
+        wave_lds_sync();
+        if (end > pre) off[prefix_count(some)] = start - pre;
+        before = 0u;
+    }
+    // The row of candidate b + lane (of no meaning past the tile's last candidate).
+    // Chunks are asked for in order.
+    __device__ __forceinline__ unsigned int row(unsigned int b, unsigned int pre, unsigned int end) {
+        ++tag;
+        if (end > pre && pre - b < 64u) mark[pre - b] = tag;
+        wave_lds_sync();
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(mark[lane_id()] == tag);
+        // Runs that start at or before the lane's candidate: the marks up to its own.
+        const unsigned long long above = m >> 1;
+        const unsigned int base = before + static_cast<unsigned int>(m & 1ull) - 1u;
+        const unsigned int k = __builtin_amdgcn_mbcnt_hi(
+            static_cast<unsigned int>(above >> 32),
+            __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(above), base));
+        before += static_cast<unsigned int>(__popcll(m));
+        return off[k & 63u] + b + static_cast<unsigned int>(lane_id());
+    }
+};
 
 // ------------------------------------------------------------------ search
 
@@ -853,7 +921,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                                                    const Plan *__restrict__ plans, float r2, int K,
                                                    unsigned int *__restrict__ kept,
                                                    unsigned int *__restrict__ temp,
-                                                   unsigned int *__restrict__ long_slots, long long rows,
+                                                   unsigned int *__restrict__ long_slots,
                                                    Counters *__restrict__ ctr,
                                                    unsigned long long *__restrict__ tested_out,
                                                    unsigned int *__restrict__ capped_out, int prio) {
@@ -874,7 +942,8 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // the partial sum in racc.
     __shared__ unsigned long long ring_all[kWaves][kRing];
     __shared__ float racc_all[kWaves][kRing];
-    __shared__ unsigned int mark_all[kWaves][64];  // run starting at each lane of a chunk, plus one
+    __shared__ unsigned int off_all[kWaves][64];   // RunMap of each wave
+    __shared__ unsigned int mark_all[kWaves][64];
     __shared__ unsigned long long tested_w[kWaves];
     __shared__ unsigned long long survived_w[kWaves];
     __shared__ unsigned int capped_w[kWaves];
@@ -889,7 +958,10 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     unsigned int *qcnt = qcnt_all[wave_id()];
     unsigned long long *ring = ring_all[wave_id()];
     float *racc = racc_all[wave_id()];
-    unsigned int *mark = mark_all[wave_id()];
+    RunMap map;
+    map.off = off_all[wave_id()];
+    map.mark = mark_all[wave_id()];
+    map.clear();
     const int lane = lane_id();
     // Terms before the first exact rejection test: two for rows of up to 12 floats
     // (a three-term test rejects few more pairs than two terms do, and the first
@@ -898,12 +970,11 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // terms took whole 120k-point builds with 32-, 48- and 64-float rows from
     // 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
     constexpr int kLead = DP <= 12 ? 2 : 3;
-    // Pairs examined (lane q counts those of query q of each group) and pairs that
-    // reached the second stage (each lane counts those it queued).  Per-lane counts
-    // in vector registers, summed once at the end: scalar registers are the scarce
-    // ones in this kernel.
+    // Pairs examined (lane q counts those of query q of each group), in vector
+    // registers and summed once at the end: scalar registers are the scarce ones in
+    // this kernel.
     unsigned long long tested = 0;
-    unsigned long long survived = 0;
+    unsigned long long survived = 0;  // pairs that reached the second stage (wave-uniform)
 
     // The cell scan cuts the queries, in cell order, into kPieces pieces per wave
     // (one for rows of up to 24 floats, two for wider ones) of equal work (its
@@ -919,9 +990,9 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // the claims compile out.
     constexpr int kPieces = search_pieces(DP);
     const unsigned int nb = gridDim.x;
-    const unsigned int xcd = blockIdx.x % 8u, per = nb / 8u, rest = nb % 8u;
-    const unsigned int xnb = per + (xcd < rest ? 1u : 0u);  // workgroups on this XCD
-    const unsigned int xb0 = xcd < rest ? xcd * (per + 1u) : rest * (per + 1u) + (xcd - rest) * per;
+    const unsigned int xcd = blockIdx.x % 8u;
+    const unsigned int xb0 = xcd_first_block(xcd, nb);
+    const unsigned int xnb = xcd_first_block(xcd + 1u, nb) - xb0;  // workgroups on this XCD
     const unsigned int xblk = blockIdx.x / 8u;              // this workgroup's number on its XCD
     const unsigned int x_first = kPieces * kWaves * xb0;    // the XCD's first piece
     const unsigned int x_dyn = x_first + kWaves * xnb;      // its first claimed piece
@@ -958,6 +1029,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // row; the remaining coordinates are loaded here (the chunk holds only the
     // first four), so entries outlive their chunk and tile.
     auto finish_rows = [&](unsigned int h, unsigned int nb) {
+        survived += nb;
         wave_lds_sync();
         const bool act = static_cast<unsigned int>(lane) < nb;
         const unsigned int e = (h + lane) & (kRing - 1);
@@ -1006,10 +1078,10 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         if (mine) {
             kept[iq] = min(cnt, Ku) | (fits ? 0u : kKeptLong);
             if (cnt > Ku) ++capped;
-            // Lists that a wave can collect are queued from the front, larger ones from
-            // the back (together at most one entry per row).
-            if (!fits && cnt <= kWaveKeys) long_slots[atomicAdd(&ctr->heavy_count, 1u)] = qrow_s[sl];
-            if (!fits && cnt > kWaveKeys) long_slots[rows - 1 - atomicAdd(&ctr->huge_count, 1u)] = qrow_s[sl];
+            if (!fits && cnt <= kWaveKeys)
+                long_slots[wave_start[x_first] + atomicAdd(long_counter(claims, xcd, kLongCount), 1u)] = qrow_s[sl];
+            if (!fits && cnt > kWaveKeys)
+                long_slots[wave_start[x_end] - 1u - atomicAdd(long_counter(claims, xcd, kHugeCount), 1u)] = qrow_s[sl];
         }
         if (fits && !(SEL && cnt > Ku)) {
             const uint4 *from = reinterpret_cast<const uint4 *>(lst + sl * kListCap);
@@ -1128,39 +1200,30 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                     // the tests of the current chunk: each lane holds its candidate's first
                     // four coordinates (one 16-byte load).  Idle lanes read row 0 (any row
                     // is a valid address) and are masked out of every ballot.
+                    // The values are masked where they are used, not here, so that nothing
+                    // waits for the load before the tests of the current chunk.
                     constexpr int kHeld = 4;  // candidate coordinates held per lane
                     static_assert(kLead <= kHeld, "the first stage uses the held coordinates");
                     float cn[kHeld];
                     unsigned int sn;
-                    // Candidate b + lane lies in the last run that starts at or before it:
-                    // each run that starts inside the chunk marks its first lane (the run
-                    // holding candidate b marks lane 0) and a prefix maximum spreads the
-                    // marks over the lanes after them.
                     auto fetch = [&](unsigned int b) {
-                        wave_lds_sync();
-                        mark[lane] = 0u;
-                        wave_lds_sync();
-                        if (end > pre && pre < b + 64u && end > b) mark[pre > b ? pre - b : 0u] = lane + 1u;
-                        wave_lds_sync();
-                        const int r = static_cast<int>(wave_scan_max(mark[lane])) - 1;
-                        const unsigned int mm = b + lane;
-                        const unsigned int srow = static_cast<unsigned int>(__shfl(start, r)) +
-                                                  (mm - static_cast<unsigned int>(__shfl(pre, r)));
-                        sn = mm < M ? srow : 0u;
+                        const unsigned int srow = map.row(b, pre, end);
+                        sn = b + lane < M ? srow : 0u;
                         const float4 v = *reinterpret_cast<const float4 *>(sorted + static_cast<size_t>(sn) * DP);
                         cn[0] = v.x;
                         cn[1] = v.y;
                         cn[2] = v.z;
                         cn[3] = v.w;
-                        // Lanes past the last candidate fail every first-stage test.
-                        if (mm >= M) cn[0] = INFINITY;
                     };
+                    map.begin(start, pre, end);
                     fetch(0u);
                     for (unsigned int base = 0; base < M; base += 64) {
                         float c[kHeld];
 #pragma unroll
                         for (int k = 0; k < kHeld; ++k) c[k] = cn[k];
                         const unsigned int s = sn;
+                        // Lanes past the last candidate fail every first-stage test.
+                        if (base + lane >= M) c[0] = INFINITY;
                         if (base + 64 < M) fetch(base + 64);
                         // Query rows are wave-uniform (scalar loads); the next one is
                         // requested before the current one is tested (the sorted rows end with
@@ -1181,7 +1244,6 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                             const unsigned long long m1 = __builtin_amdgcn_ballot_w64(acc < r2);
                             if (m1 == 0ull) continue;
                             if (acc < r2) {
-                                ++survived;
                                 const unsigned int e = (tail + prefix_count(m1)) & (kRing - 1);
                                 const unsigned int slot = uniform((gs + static_cast<unsigned int>(q)) & (kQT - 1));
                                 ring[e] = (static_cast<unsigned long long>(slot) << 32) | s;
@@ -1206,7 +1268,6 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     if (pend_n) flush(pend0, pend_n);
     capped = wave_sum(capped);
     tested = wave_sum(tested);
-    survived = wave_sum(survived);
     if (lane == 0) {
         tested_w[wave_id()] = tested;
         survived_w[wave_id()] = survived;
@@ -1627,7 +1688,7 @@ template <int DP>
 __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, const unsigned int *__restrict__ sorted_id,
                           const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
                           unsigned int slot, unsigned int pc, float r2, unsigned int n_out, long long row0,
-                          long long *__restrict__ out, unsigned int *dist, unsigned int *ids, unsigned int *mark) {
+                          long long *__restrict__ out, unsigned int *dist, unsigned int *ids, RunMap &map) {
     const int lane = lane_id();
     int u[kMaxAxes];
     unpack_cell(pc, P.axes, u);
@@ -1635,16 +1696,10 @@ __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, cons
     const unsigned int M = wave_runs(u, cell0, P, run_lane(P), cell_start, start, pre, end);
     const float *qrow = sorted + static_cast<size_t>(slot) * DP;
     unsigned int h = 0;
+    map.begin(start, pre, end);
     for (unsigned int b = 0; b < M; b += 64u) {
-        wave_lds_sync();
-        mark[lane] = 0u;
-        wave_lds_sync();
-        if (end > pre && pre < b + 64u && end > b) mark[pre > b ? pre - b : 0u] = lane + 1u;
-        wave_lds_sync();
-        const int r = static_cast<int>(wave_scan_max(mark[lane])) - 1;
         const unsigned int mm = b + lane;
-        const unsigned int srow = static_cast<unsigned int>(__shfl(start, r)) +
-                                  (mm - static_cast<unsigned int>(__shfl(pre, r)));
+        const unsigned int srow = map.row(b, pre, end);
         const unsigned int s = mm < M ? srow : slot;
         const unsigned int j = sorted_id[2u * static_cast<size_t>(s)];
         float c[DP];
@@ -1701,6 +1756,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                                                        const unsigned long long *__restrict__ group_sum,
                                                        int groups_kept, int tiles_kept,
                                                        const unsigned int *__restrict__ long_slots,
+                                                       const unsigned int *__restrict__ long_counts,
+                                                       const unsigned int *__restrict__ wave_start,
+                                                       unsigned int search_blocks,
                                                        const unsigned int *__restrict__ temp,
                                                        const float *__restrict__ sorted,
                                                        const unsigned int *__restrict__ sorted_id,
@@ -1721,7 +1779,8 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     unsigned int *wdst = wbuf + kOwnerWindow;
     __shared__ unsigned long long scratch[kWaves];
     __shared__ LongLds<DP> L;
-    __shared__ unsigned int mark[kWaves][64];
+    __shared__ unsigned int map_all[kWaves][128];  // RunMap of each wave
+    __shared__ unsigned int q_first[8], q_last[8], q_wave[9], q_huge[9];
     const bool abort = ctr->abort != 0;
     const int b = static_cast<int>(blockIdx.x);
     const bool tile_block = b < tiles_kept;
@@ -1775,7 +1834,10 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         rep.survived = abort ? 0ull : ctr->survived;
         rep.abort = abort ? 1 : 0;
         rep.capped = abort ? 0u : ctr->capped;
-        rep.heavy = ctr->heavy_count + ctr->huge_count;
+        rep.heavy = 0u;
+        for (unsigned int x = 0; x < 8u && !abort; ++x)
+            rep.heavy += long_counts[x * kPools * kPoolStride + kLongCount] +
+                         long_counts[x * kPools * kPoolStride + kHugeCount];
         rep.n_cells = P.n_cells;
         for (int p = 0; p < kMaxAxes; ++p) {
             rep.G[p] = P.G[p];
@@ -1866,19 +1928,43 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         }
     }
     if (abort || overflow) return;
-    // Long lists that a wave collects.  The queue is in the search's order, so
-    // neighbouring entries share candidates: each XCD takes a contiguous share, its
-    // waves in turn.
+    // The search's queues, one per XCD: where each starts and ends in long_slots, and
+    // the lists of each kind before it.
+    if (threadIdx.x < 64) {
+        const unsigned int x = min(threadIdx.x, 7u);
+        const unsigned int *c = long_counts + x * kPools * kPoolStride;
+        const unsigned int n_wave = threadIdx.x < 8 ? c[kLongCount] : 0u;
+        const unsigned int n_huge = threadIdx.x < 8 ? c[kHugeCount] : 0u;
+        const unsigned int first = wave_start[search_pieces(DP) * kWaves * xcd_first_block(x, search_blocks)];
+        const unsigned int last = wave_start[search_pieces(DP) * kWaves * xcd_first_block(x + 1u, search_blocks)];
+        const unsigned int wave_inc = wave_scan_add(n_wave), huge_inc = wave_scan_add(n_huge);
+        if (threadIdx.x < 8) {
+            q_first[x] = first;
+            q_last[x] = last;
+            q_wave[x + 1] = wave_inc;
+            q_huge[x + 1] = huge_inc;
+            if (x == 0) q_wave[0] = q_huge[0] = 0u;
+        }
+    }
     __syncthreads();
+    // Long lists that a wave collects.  A queue is about in the search's order, so
+    // neighbouring entries share candidates: each XCD takes a contiguous share of them
+    // all, its waves in turn.
     {
         const unsigned int xcd = blockIdx.x % 8u;
         const unsigned int xnb = gridDim.x / 8u + (xcd < gridDim.x % 8u ? 1u : 0u);
-        const unsigned long long n_long = ctr->heavy_count;
+        const unsigned long long n_long = q_wave[8];
         const unsigned int lo = static_cast<unsigned int>(n_long * xcd / 8u);
         const unsigned int hi = static_cast<unsigned int>(n_long * (xcd + 1u) / 8u);
+        unsigned int queue = 0;
         unsigned int *lds = wbuf + wave_id() * (2 * kWaveKeys);
+        RunMap map;
+        map.off = map_all[wave_id()];
+        map.mark = map.off + 64;
+        map.clear();
         for (unsigned int h = lo + blockIdx.x / 8u * kWaves + wave_id(); h < hi; h += xnb * kWaves) {
-            const unsigned int slot = uniform(long_slots[h]);
+            while (h >= q_wave[queue + 1u]) ++queue;
+            const unsigned int slot = uniform(long_slots[q_first[queue] + (h - q_wave[queue])]);
             if (static_cast<long long>(slot) >= rows) continue;  // only a corrupted queue
             const uint2 id = reinterpret_cast<const uint2 *>(sorted_id)[slot];
             const long long gi = uniform(id.x);  // the query's original row
@@ -1901,14 +1987,16 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
             at = wave_sum(at);
             if (at + nq > cap) continue;  // cannot happen when E <= cap
             wave_list<DP>(sorted, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot,
-                          uniform(id.y), r2, nq, ev[e].row0, dst + at, lds, lds + kWaveKeys, mark[wave_id()]);
+                          uniform(id.y), r2, nq, ev[e].row0, dst + at, lds, lds + kWaveKeys, map);
         }
     }
     __syncthreads();
     // Larger ones, collected by the whole workgroup, every gridDim-th one.
-    const unsigned int n_huge = ctr->huge_count;
+    const unsigned int n_huge = q_huge[8];
+    unsigned int huge_queue = 0;
     for (unsigned int h = blockIdx.x; h < n_huge; h += gridDim.x) {
-        const unsigned int slot = long_slots[rows - 1 - h];
+        while (h >= q_huge[huge_queue + 1u]) ++huge_queue;
+        const unsigned int slot = long_slots[q_last[huge_queue] - 1u - (h - q_huge[huge_queue])];
         if (static_cast<long long>(slot) >= rows) continue;  // only a corrupted queue
         const long long gi = sorted_id[2u * slot];  // the query's original row
         const int t = static_cast<int>(gi / kPlaceTile);
@@ -1943,12 +2031,12 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     if (a.K < kListCap)
         hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, rows, ws.ctr, ws.tested, ws.capped_blk,
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
                            a.search_prio);
     else
         hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, rows, ws.ctr, ws.tested, ws.capped_blk,
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
                            a.search_prio);
     mark(5);
     // One block per group of tiles, and one for the search's counts.
@@ -1959,7 +2047,8 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const int place_blocks = ws.tiles_kept_n > kPlaceMinBlocks ? ws.tiles_kept_n : kPlaceMinBlocks;
     hipLaunchKernelGGL(k_place<DP>, dim3(static_cast<unsigned int>(place_blocks)), dim3(kPlaceBlock), 0, a.stream,
                        rows, ws.ev, a.n_events, ws.kept, ws.sums_kept, ws.sums_kept2, ws.groups_kept_n,
-                       ws.tiles_kept_n, ws.long_slots, ws.temp, ws.sorted, ws.sorted_id, ws.cell_start, a.r2, a.K,
+                       ws.tiles_kept_n, ws.long_slots, ws.claims, ws.wave_start,
+                       static_cast<unsigned int>(a.search_blocks), ws.temp, ws.sorted, ws.sorted_id, ws.cell_start, a.r2, a.K,
                        a.src, a.dst, a.edge_capacity, ws.plans, ws.ctr, a.edge_off_out ? a.edge_off_out : ws.edge_off,
                        a.report_out ? a.report_out : ws.report);
 }
