@@ -93,7 +93,6 @@ int search_blocks_cached(int dpad, bool sel) {
     auto it = g_blocks.find({dev, key});
     if (it != g_blocks.end()) return it->second;
     int b = search_blocks_for(dpad, sel);
-    if (b > kMaxSearchBlocks) b = kMaxSearchBlocks;
     g_blocks[{dev, key}] = b;
     return b;
 }
@@ -194,9 +193,7 @@ Workspace layout(void *base, long long rows, long long cells, int n_events, int 
     ws.kept = cv.take<unsigned int>(rows);
     ws.long_slots = cv.take<unsigned int>(rows);
     ws.temp = cv.take<unsigned int>(static_cast<size_t>(rows) * kListCap);
-    ws.tested = cv.take<unsigned long long>(2 * kMaxSearchBlocks);
-    ws.capped_blk = cv.take<unsigned int>(kMaxSearchBlocks);
-    ws.wave_start = cv.take<unsigned int>(static_cast<size_t>(kMaxSearchBlocks) * kWaves * kMaxPieces + 1);
+    ws.wave_start = cv.take<unsigned int>(static_cast<size_t>(kMaxPieceCount) + 1);
     ws.claims = cv.take<unsigned int>(8 * kPools * kPoolStride);
     ws.rows = rows;
     ws.cells = cells;
@@ -265,21 +262,22 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
     a.src = reinterpret_cast<long long *>(src);
     a.dst = reinterpret_cast<long long *>(dst);
     a.stream = stream;
-    // One round of resident workgroups (whose waves then order their issue by
-    // progress) unless each resident wave would get more than 128 rows; then up to
-    // four times as many workgroups as fit at once, so that the hardware hands the
-    // remaining shares to whichever workgroups finish first.
+    // One round of resident workgroups (whose waves then order their issue by progress)
+    // up to kRowsPerPiece rows per piece, then as many rounds as keep a piece at that: the
+    // hardware hands the remaining shares to whichever workgroups finish first, and the
+    // rows that an XCD's resident waves work on at a time fit its L2.
     {
         const int resident = search_blocks_cached(a.dpad, K < kListCap);
-        const long long per_wave = rows / (static_cast<long long>(resident) * kWaves);
-        long long m = per_wave < 128 ? 1 : per_wave / 128 + 1;
-        m = m > 4 ? 4 : m;
+        const int pieces = search_pieces(a.dpad);
+        const long long per_piece = rows / (static_cast<long long>(resident) * kWaves * pieces);
+        long long m = per_piece / kRowsPerPiece + 1;
         if (config && config->grid_mult > 0) m = config->grid_mult;
+        long long b = resident * m;
         // Small calls: at least kMinWaveRows rows per wave, and one workgroup per XCD.
         const long long most = (rows + kWaves * kMinWaveRows - 1) / (kWaves * kMinWaveRows);
-        long long b = resident * m;
         if (b > most) b = most < 8 ? 8 : most;
-        a.search_blocks = static_cast<int>(b > kMaxSearchBlocks ? kMaxSearchBlocks : b);
+        const long long room = kMaxPieceCount / (kWaves * pieces);
+        a.search_blocks = static_cast<int>(b > room ? room : b);
         a.search_prio = a.search_blocks <= resident ? 1 : 0;
     }
     // About 16 coordinates per thread of the bounds pass, at most kBoundsBlocks blocks per event.

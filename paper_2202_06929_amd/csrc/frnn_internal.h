@@ -24,7 +24,8 @@ constexpr int kMaxAxes = 4;          // binned coordinates: 3, or 4 with cell_di
 constexpr int kGridAxisMax3 = 1024;
 constexpr int kGridAxisMax4 = 256;
 constexpr int kMaxK = 4096;
-constexpr int kMaxSearchBlocks = 8192;
+// Most pieces of the search (wave_start has an entry per piece).
+constexpr int kMaxPieceCount = 98304;
 // A cell's fixed cost in the search (its runs' bounds, its candidates' first
 // loads), in queries, when the queries are divided among the waves by work.
 constexpr unsigned int kTileWeight = 4;
@@ -33,6 +34,13 @@ constexpr unsigned int kTileWeight = 4;
 // 20,000-point event of crowded cells took 121, 120, 119, 124 and 140 us with at least
 // 1, 2, 4, 8 and 16 rows, and a 2,000-point event 55.5, 54.8, 55.0, 57.0 and 60.6 us.
 constexpr long long kMinWaveRows = 4;
+// Rows per piece from which the search takes more rounds of workgroups.  Pieces of this
+// size keep the rows, cell starts and ids that an XCD's resident waves read (about a
+// thousand pieces) near its 4 MB of L2: a batch of 5.6M 8-D points took 2,561, 2,286,
+// 2,096, 1,975 and 1,955 us with 1, 2, 4, 8 and 16 rounds (683 to 43 rows per piece), six
+// events of 610k points in all 251, 246 and 249 us with pieces of up to 128, 32 and 16
+// rows, a 300k-point 12-D event 156.5 and 154.7 us with up to 128 and 32.
+constexpr long long kRowsPerPiece = 32;
 // The search's queries are cut into search_pieces(DP) pieces of equal work per
 // wave: each wave takes one piece of its XCD's share, then claims the share's
 // other pieces one at a time from kPools counters per XCD, so that waves that
@@ -43,7 +51,6 @@ constexpr long long kMinWaveRows = 4;
 // rows 0.089 and 0.120 ms against 0.085 and 0.117).  Wider rows, whose queries
 // cost more and which run fewer waves per SIMD, take two (32-, 48- and 64-float
 // rows: 0.173, 0.292 and 0.558 ms against 0.181, 0.340 and 0.713 with one).
-constexpr int kMaxPieces = 2;
 constexpr int search_pieces(int dpad) { return dpad <= 24 ? 1 : 2; }
 constexpr int kPools = 8;
 constexpr int kPoolStride = 32;  // counters 128 bytes apart
@@ -109,6 +116,15 @@ struct Counters {
     unsigned long long survived;   // pairs that reached the second stage, likewise
 };
 
+// Counts of one search workgroup.  They lie where the ranks were: a workgroup has at
+// least 16 rows beyond the first eight (kMinWaveRows), so the ranks are the larger.
+struct SearchCounts {
+    unsigned long long tested;    // pairs examined
+    unsigned long long survived;  // pairs that reached the second stage
+    unsigned int capped;          // queries with more than K neighbours
+    unsigned int pad;
+};
+
 // Result summary copied to the host at the end of a call (event 0's grid).
 struct Report {
     long long n_edges;
@@ -131,7 +147,7 @@ struct Workspace {
     Report *report;
     long long *edge_off;        // [n_events + 2] first edge of each event, then E, then a status
     unsigned int *pcell;        // [rows] packed cell coordinates of each point
-    unsigned int *rank;         // [rows] arrival rank inside its cell
+    unsigned int *rank;         // [rows] arrival rank inside its cell; after the scatter, the search's SearchCounts
     unsigned int *cell_count;   // [cells] histogram
     unsigned int *cell_start;   // [cells + 1] exclusive scan of the histogram
     unsigned long long *sums_cells;  // [tiles of cells + 1] per-tile histogram totals
@@ -143,9 +159,7 @@ struct Workspace {
     unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists, queued per XCD in the part
                                 // of the XCD's rows
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries
-    unsigned long long *tested; // [2 kMaxSearchBlocks] pairs examined, then pairs fully tested, per search workgroup
-    unsigned int *capped_blk;   // [kMaxSearchBlocks] capped queries per search workgroup
-    unsigned int *wave_start;   // [kMaxSearchBlocks kWaves kMaxPieces + 1] first sorted row of each search piece
+    unsigned int *wave_start;   // [kMaxPieceCount + 1] first sorted row of each search piece
     unsigned int *claims;       // [8 kPools kPoolStride] the search's piece counters and, beside each XCD's first,
                                 // its long-list counts; cleared by the cell scan
     long long rows;

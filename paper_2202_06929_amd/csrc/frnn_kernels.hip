@@ -128,6 +128,7 @@ __device__ __forceinline__ float dpp_keep(float v) {
 }
 constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
 constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+constexpr int kWaveShr1 = 0x138;  // lane i - 1 of the whole wave (0 in lane 0)
 
 // Inclusive prefix sum across the 64 lanes (a scan within each row of 16 lanes,
 // then the row totals carried into the rows after them), for 32- or 64-bit
@@ -812,54 +813,72 @@ __device__ __forceinline__ int run_count(const Plan &P) {
     return P.axes == 4 ? side * side * side : side * side;
 }
 
-// Offsets along axes 1..3 of the run a lane builds (lanes below run_count), and what
-// they add to the key of a cell.
+// Offsets along axes 1..3 of the run a lane builds (lanes below run_count, of each half
+// of the wave when the halves build the runs of two cells), and what they add to the
+// key of a cell.
 struct RunLane {
     int a[3];
     int key;
     bool live;
+    unsigned int stride[3];  // keys between neighbours along axes 1..3 (24 bits: see wave_runs)
 };
 
-__device__ __forceinline__ RunLane run_lane(const Plan &P) {
-    const int R = P.reach, side = 2 * R + 1, t = lane_id();
+__device__ __forceinline__ RunLane run_lane(const Plan &P, bool halves) {
+    const int R = P.reach, side = 2 * R + 1, t = halves ? lane_id() & 31 : lane_id();
     RunLane rl;
     rl.live = t < run_count(P);
     rl.a[0] = t % side - R;
     rl.a[1] = (t / side) % side - R;
     rl.a[2] = P.axes == 4 ? t / (side * side) - R : 0;
     rl.key = ((rl.a[2] * P.G[2] + rl.a[1]) * P.G[1] + rl.a[0]) * P.G[0];
+    rl.stride[0] = static_cast<unsigned int>(P.G[0]);
+    rl.stride[1] = static_cast<unsigned int>(P.G[0] * P.G[1]) & 0xffffffu;
+    rl.stride[2] = static_cast<unsigned int>(P.G[0] * P.G[1] * P.G[2]) & 0xffffffu;
     return rl;
 }
 
-// Lane t < run_count builds run t around the cell with coordinates u (global keys
-// start at cell0): its first sorted row (start) and its candidates [pre, end) in
-// the tile's candidate numbering (other lanes: an empty run at the end).  Returns
-// the candidate count, the same in every lane.  Call with the whole wave active.
-__device__ __forceinline__ unsigned int wave_runs(const int (&u)[kMaxAxes], unsigned int cell0, const Plan &P,
-                                                  const RunLane &rl, const unsigned int *__restrict__ cell_start,
-                                                  unsigned int &start, unsigned int &pre, unsigned int &end) {
+// Lane t < run_count builds run t around the cell whose packed coordinates are pc
+// (global keys start at cell0): its first sorted row (start) and its candidates
+// [pre, end) in the cell's candidate numbering (other lanes: an empty run at the end).
+// With `halves`, lanes 32.. do the same for a second cell (their pc), numbered by
+// itself.  Call with the whole wave active; a cell's candidate count is `end` in the
+// last lane of its half (or of the wave).
+__device__ __forceinline__ void wave_runs(unsigned int pc, unsigned int cell0, const Plan &P, const RunLane &rl,
+                                          bool live, bool halves, const unsigned int *__restrict__ cell_start,
+                                          unsigned int &start, unsigned int &pre, unsigned int &end) {
     const int R = P.reach;
+    int u[kMaxAxes];
+    unpack_cell(pc, P.axes, u);
     // Branch-free: every lane loads (a lane without a run reads the event's first
     // row of cells, a valid address) and keeps its run only if it is inside the grid
-    // (the unsigned comparisons also reject negative coordinates).  The key of the
-    // cell's row is wave-uniform; a lane adds its run's offset.
+    // (the unsigned comparisons also reject negative coordinates).  An event has at most
+    // 2^24 cells, so the products are full-rate 24-bit ones (a stride of 2^24 means that
+    // the axis has one cell, and its coordinate is 0).
     const int y = u[1] + rl.a[0], z = u[2] + rl.a[1], w = u[3] + rl.a[2];
-    const bool ok = rl.live & (static_cast<unsigned int>(y) < static_cast<unsigned int>(P.G[1])) &
+    const bool ok = live & (static_cast<unsigned int>(y) < static_cast<unsigned int>(P.G[1])) &
                     (static_cast<unsigned int>(z) < static_cast<unsigned int>(P.G[2])) &
                     (static_cast<unsigned int>(w) < static_cast<unsigned int>(P.G[3]));
     const int xlo = max(u[0] - R, 0), xhi = min(u[0] + R, P.G[0] - 1);
-    const int crow = ((u[3] * P.G[2] + u[2]) * P.G[1] + u[1]) * P.G[0];
-    const unsigned int row = cell0 + static_cast<unsigned int>(ok ? crow + rl.key : 0);
+    const unsigned int crow = __umul24(u[1], rl.stride[0]) +
+                              __umul24(u[2], rl.stride[1]) +
+                              __umul24(u[3], rl.stride[2]);
+    const unsigned int row = cell0 + (ok ? crow + static_cast<unsigned int>(rl.key) : 0u);
     const unsigned int s0 = cell_start[row + xlo];
     const unsigned int s1 = cell_start[row + xhi + 1];
     start = ok ? s0 : 0u;
     const unsigned int len = ok ? s1 - s0 : 0u;
-    end = wave_scan_add(len);
+    unsigned int x = len;
+    x += dpp_move<kRowShr1>(x);
+    x += dpp_move<kRowShr2>(x);
+    x += dpp_move<kRowShr4>(x);
+    x += dpp_move<kRowShr8>(x);
+    x += dpp_move<kRowBcast15, 0xa>(x);
+    if (!halves) x += dpp_move<kRowBcast31, 0xc>(x);
+    end = x;
     pre = end - len;
-    return __builtin_amdgcn_readlane(end, 63);
 }
 
-// Numbers a tile's candidates: lane l of chunk b gets the sorted row of candidate
+// Numbers a cell's candidates: lane l of chunk b gets the sorted row of candidate
 // b + l.  The runs that hold candidates are kept in order in LDS, each as (first row -
 // first candidate); a run that starts inside a chunk marks its lane there with the
 // chunk's own tag (so that nothing is cleared), and a ballot of the marks counts the
@@ -870,23 +889,30 @@ struct RunMap {
     unsigned int *off;   // [64] per wave: the runs with candidates
     unsigned int *mark;  // [64] per wave, cleared once before the first chunk
     unsigned int tag = 0;
-    unsigned int before = 0;  // runs that start before the next chunk
+    unsigned int first;   // first candidate of the lane's run, or kNone
+    unsigned int before;  // runs kept in off that start before the next chunk
+    static constexpr unsigned int kNone = 0x80000000u;  // candidates are fewer
     __device__ __forceinline__ void clear() {
         mark[lane_id()] = 0u;
         wave_lds_sync();
     }
-    // A new tile, from wave_runs.
-    __device__ __forceinline__ void begin(unsigned int start, unsigned int pre, unsigned int end) {
+    // The runs of wave_runs (of both halves): the ballot of those with candidates.
+    __device__ __forceinline__ unsigned long long keep(unsigned int start, unsigned int pre, unsigned int end) {
         const unsigned long long some = __builtin_amdgcn_ballot_w64(end > pre);
         wave_lds_sync();
         if (end > pre) off[prefix_count(some)] = start - pre;
-        before = 0u;
+        return some;
     }
-    // The row of candidate b + lane (of no meaning past the tile's last candidate).
+    // A new cell: the lanes that hold its runs, and the runs kept before them.
+    __device__ __forceinline__ void begin(bool mine, unsigned int pre, unsigned int end, unsigned int runs_before) {
+        first = mine && end > pre ? pre : kNone;
+        before = runs_before;
+    }
+    // The row of candidate b + lane (of no meaning past the cell's last candidate).
     // Chunks are asked for in order.
-    __device__ __forceinline__ unsigned int row(unsigned int b, unsigned int pre, unsigned int end) {
+    __device__ __forceinline__ unsigned int row(unsigned int b) {
         ++tag;
-        if (end > pre && pre - b < 64u) mark[pre - b] = tag;
+        if (first - b < 64u) mark[first - b] = tag;
         wave_lds_sync();
         const unsigned long long m = __builtin_amdgcn_ballot_w64(mark[lane_id()] == tag);
         // Runs that start at or before the lane's candidate: the marks up to its own.
@@ -900,14 +926,21 @@ struct RunMap {
     }
 };
 
-// ------------------------------------------------------------------ search
-
 // Waves per SIMD the search asks the register allocator for: a lane holds only a
 // candidate's first four coordinates, so rows of up to 16 floats fit in 64
 // registers (8 waves, some scalar registers spilled to vector lanes); wider rows,
-// whose second stage holds the rest of a row, keep the compiler's choice.
+// whose second stage holds the rest of a row, keep the compiler's choice (48 floats:
+// held just below the 128 registers of 4 waves).
 template <int DP>
-constexpr int kSearchWaves = DP <= 16 ? 8 : 1;
+constexpr int kSearchWaves = DP <= 16 ? 8 : (DP == 48 ? 4 : 1);
+
+// Terms before the first exact rejection test: two for rows of up to 12 floats
+// (a three-term test rejects few more pairs than two terms do, and the first
+// stage runs for every query and candidate; on the 300k-point 12-D event two,
+// three and four terms took 87.5, 88.7 and 89.6 us), three for wider rows (two
+// terms took whole 120k-point builds with 32-, 48- and 64-float rows from
+// 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
+constexpr int search_lead(int dpad) { return dpad <= 12 ? 2 : 3; }
 
 // SEL: the cap K is below kListCap, so a list that fits may still need the K
 // nearest of its hits: the lists then also hold each hit's distance.
@@ -923,23 +956,26 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                                                    unsigned int *__restrict__ temp,
                                                    unsigned int *__restrict__ long_slots,
                                                    Counters *__restrict__ ctr,
-                                                   unsigned long long *__restrict__ tested_out,
-                                                   unsigned int *__restrict__ capped_out, int prio) {
-    // Queries per tile: 16 when the lists also hold distances (their LDS would
+                                                   SearchCounts *__restrict__ counts, int prio) {
+    // Queries per batch: 16 when the lists also hold distances (their LDS would
     // otherwise cost occupancy), else kQTile.
     constexpr int kQT = SEL ? 16 : kQTile;
-    static_assert((kQT & (kQT - 1)) == 0 && kQT <= 64, "list slots are numbered modulo kQT");
+    static_assert(kQT < 64, "a batch and the start of the next fit in a wave's lanes");
     __shared__ __align__(16) unsigned int lst_all[kWaves][kQT * kListCap];
     __shared__ unsigned int lstd_all[SEL ? kWaves : 1][SEL ? kQT * kListCap : 1];  // D bits of each hit
-    // Per list slot (kQT per wave, taken by the queries in turn): the query's sorted
-    // and original rows.
-    __shared__ unsigned int qrow_all[kWaves][kQT];
-    __shared__ unsigned int qid_all[kWaves][kQT];
-    __shared__ unsigned int pre_all[kWaves][kQT + 1];
-    __shared__ unsigned int cnt_all[kWaves][kQT];
-    __shared__ unsigned int qcnt_all[kWaves][kQT];
-    // Queued first-stage survivors: query slot << 32 | candidate's sorted row, with
-    // the partial sum in racc.
+    __shared__ unsigned int pre_all[SEL ? kWaves : 1][SEL ? kQT : 1];
+    __shared__ unsigned int cnt_all[SEL ? kWaves : 1][SEL ? kQT : 1];
+    __shared__ unsigned int qcnt_all[kWaves][kQT];  // hits of each query of the batch
+    constexpr int kLead = search_lead(DP);
+    // Coordinates kLead.. of the batch's queries, read by the second stage, for rows
+    // wide enough that registers, not LDS, bound the waves per SIMD (32-float rows:
+    // 29.1 us against 31.6 with the query rows loaded per entry; for 12-float rows the
+    // LDS would cost a wave per SIMD: 106 us against 82 on the 300k-point event).
+    constexpr bool kTailLds = DP >= 24 && !SEL;
+    constexpr int kTail = DP - kLead;
+    __shared__ float tail_all[kTailLds ? kWaves : 1][kTailLds ? kQT * kTail : 1];
+    // Queued first-stage survivors: number in the batch << 32 | candidate's sorted row,
+    // with the partial sum in racc.
     __shared__ unsigned long long ring_all[kWaves][kRing];
     __shared__ float racc_all[kWaves][kRing];
     __shared__ unsigned int off_all[kWaves][64];   // RunMap of each wave
@@ -950,12 +986,11 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     if (ctr->abort) return;
     unsigned int *lst = lst_all[wave_id()];
     unsigned int *lstd = lstd_all[SEL ? wave_id() : 0];
-    unsigned int *qrow_s = qrow_all[wave_id()];
-    unsigned int *qid = qid_all[wave_id()];
     unsigned int capped = 0;
-    unsigned int *tpre = pre_all[wave_id()];
-    unsigned int *tcnt = cnt_all[wave_id()];
+    unsigned int *tpre = pre_all[SEL ? wave_id() : 0];
+    unsigned int *tcnt = cnt_all[SEL ? wave_id() : 0];
     unsigned int *qcnt = qcnt_all[wave_id()];
+    float *qtail = tail_all[kTailLds ? wave_id() : 0];
     unsigned long long *ring = ring_all[wave_id()];
     float *racc = racc_all[wave_id()];
     RunMap map;
@@ -963,18 +998,8 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     map.mark = mark_all[wave_id()];
     map.clear();
     const int lane = lane_id();
-    // Terms before the first exact rejection test: two for rows of up to 12 floats
-    // (a three-term test rejects few more pairs than two terms do, and the first
-    // stage runs for every query and candidate; on the 300k-point 12-D event two,
-    // three and four terms took 87.5, 88.7 and 89.6 us), three for wider rows (two
-    // terms took whole 120k-point builds with 32-, 48- and 64-float rows from
-    // 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
-    constexpr int kLead = DP <= 12 ? 2 : 3;
-    // Pairs examined (lane q counts those of query q of each group), in vector
-    // registers and summed once at the end: scalar registers are the scarce ones in
-    // this kernel.
-    unsigned long long tested = 0;
-    unsigned long long survived = 0;  // pairs that reached the second stage (wave-uniform)
+    unsigned long long tested = 0;    // pairs examined (wave-uniform, as the next)
+    unsigned long long survived = 0;  // pairs that reached the second stage
 
     // The cell scan cuts the queries, in cell order, into kPieces pieces per wave
     // (one for rows of up to 24 floats, two for wider ones) of equal work (its
@@ -1002,18 +1027,18 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     unsigned int *claim = claims + (xcd * kPools + pool) * kPoolStride;
     Plan P;
     RunLane rl;
+    bool halves = false;  // a cell's runs fit half a wave: the runs of two cells are built at once
     unsigned int cell0 = 0;
     unsigned int ev_end = 0;  // first row after the current event
     const uint2 *__restrict__ sid = reinterpret_cast<const uint2 *>(sorted_id);
-    // Queries take the wave's kQT list slots in turn (query number k of the wave
-    // uses slot k mod kQT).  First-stage survivors stay queued across tiles, and
-    // the lists of the pending queries are written out together: when the next
-    // group of queries would not find free slots (the queue is emptied first) and
-    // at the end of the share.  A tile of a sparse cell holds a few queries, so
-    // the queue's partial drain and the list stores are shared by many tiles.
-    unsigned int head = 0, tail = 0;     // queued survivors [head, tail)
-    unsigned int pend0 = 0, pend_n = 0;  // pending queries: numbers [pend0, pend0 + pend_n)
-    // A pair that passes the full test joins the list of the query in slot q.
+    // The queries are taken in batches of at most kQT, which end between cells unless a
+    // single cell has more: lane l holds query win + l (its original row and packed
+    // cell), and list slot l is its own.  First-stage survivors stay queued across the
+    // batch's cells (a sparse cell holds a few queries), and the batch's lists are
+    // written out together.
+    unsigned int win = 0;             // sorted row of the batch's first query
+    unsigned int head = 0, tail = 0;  // queued survivors [head, tail)
+    // A pair that passes the full test joins the list of query q of the batch.
     auto keep = [&](bool pass, unsigned int q, unsigned int j, float D) {
         if (pass) {
             const unsigned int pos = atomicAdd(&qcnt[q], 1u);
@@ -1025,66 +1050,66 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     };
     // Second stage for ring entries [h, h + nb): lane l takes entry h + l and
     // adds terms kLead.. of the definition to the first stage's partial sum, in
-    // the same order.  An entry names its query's slot and the candidate's sorted
-    // row; the remaining coordinates are loaded here (the chunk holds only the
-    // first four), so entries outlive their chunk and tile.
+    // the same order.  An entry names its query and the candidate's sorted row; the
+    // remaining coordinates are loaded here (the chunk holds only the first four), so
+    // entries outlive their chunk and cell.
     auto finish_rows = [&](unsigned int h, unsigned int nb) {
         survived += nb;
         wave_lds_sync();
         const bool act = static_cast<unsigned int>(lane) < nb;
         const unsigned int e = (h + lane) & (kRing - 1);
-        const unsigned long long ent = act ? ring[e] : 0ull;
+        const unsigned long long ent = act ? ring[e] : static_cast<unsigned long long>(win);
         const float a3 = act ? racc[e] : 0.0f;
         const unsigned int q = static_cast<unsigned int>(ent >> 32);
         const unsigned int s2 = static_cast<unsigned int>(ent);
-        const unsigned int qr = qrow_s[q];
         const float *crow = sorted + static_cast<size_t>(s2) * DP;
-        float cc[DP];
+        float cc[DP], qq[DP];
 #pragma unroll
         for (int k = kLead; k < DP; ++k) cc[k] = crow[k];
-        const unsigned int j2 = sorted_id[2u * s2];
-        const float D = add_terms<kLead, DP, DP>(a3, cc, sorted + static_cast<size_t>(qr) * DP);
-        keep(act && D < r2 && s2 != qr, q, j2, D);
-        wave_lds_sync();
-    };
-    // Empties the queue.
-    auto drain_all = [&]() {
-        if (tail != head) {
-            finish_rows(head, tail - head);
-            head = tail;
+        if (kTailLds) {
+#pragma unroll
+            for (int k = kLead; k < DP; ++k) qq[k] = qtail[q * kTail + (k - kLead)];
+        } else {
+            const float *qrow = sorted + static_cast<size_t>(win + q) * DP;
+#pragma unroll
+            for (int k = kLead; k < DP; ++k) qq[k] = qrow[k];
         }
-    };
-    // Writes out the lists of pending queries [f0, f0 + nf), nf <= kQT, whose
-    // survivors are all finished; lane l takes query f0 + l.  Kept counts for every
-    // query; lists that fit go to their fixed place (kListCap slots per original
-    // row) as found, in 16-byte pieces, and the placement pass orders every such
-    // list by neighbour id; the sorted rows of longer ones are queued (one atomic
-    // each) for the placement pass to collect again.  With the cap binding (SEL and
-    // more than K hits), the entries of those lists are numbered through a prefix
-    // over their lengths; each lane takes one entry, finds its query by binary
-    // search, ranks it by its (D, j) key within its list (D >= 0, so its bits order
-    // like the value; keys are distinct) and, if the rank is below K, writes it at
-    // that rank: the list's first K slots then hold its K nearest.  The stores are
-    // scattered, but everything about query i lands at places indexed by i, which
-    // the placement pass then reads in order.
-    auto flush = [&](unsigned int f0, unsigned int nf) {
+        unsigned int j2 = sorted_id[2u * static_cast<size_t>(s2)];
+        const float D = add_terms_r<kLead, DP, DP, DP>(a3, cc, qq);
+        // The id is requested with the rows, not (as the compiler would have it) in a
+        // round trip of its own once a pair has passed.
+        asm volatile("" : "+v"(j2));
+        keep(act && D < r2 && s2 != win + q, q, j2, D);
         wave_lds_sync();
-        const bool mine = static_cast<unsigned int>(lane) < nf;
-        const unsigned int sl = (f0 + static_cast<unsigned int>(lane)) & (kQT - 1);
-        const unsigned int cnt = mine ? qcnt[sl] : 0u;
-        const unsigned int iq = qid[sl];
+    };
+    // Writes out the batch's nq lists, whose survivors are all finished; lane l takes
+    // query l, whose original row is iq.  Kept counts for every query; lists that fit go
+    // to their fixed place (kListCap slots per original row) as found, in 16-byte pieces,
+    // and the placement pass orders every such list by neighbour id; the sorted rows of
+    // longer ones are queued for the placement pass to collect again.  With the cap
+    // binding (SEL and more than K hits), the entries of those lists are numbered through
+    // a prefix over their lengths; each lane takes one entry, finds its query by binary
+    // search, ranks it by its (D, j) key within its list (D >= 0, so its bits order like
+    // the value; keys are distinct) and, if the rank is below K, writes it at that rank:
+    // the list's first K slots then hold its K nearest.  The stores are scattered, but
+    // everything about query i lands at places indexed by i, which the placement pass
+    // then reads in order.
+    auto flush = [&](unsigned int nq, unsigned int iq) {
+        wave_lds_sync();
+        const bool mine = static_cast<unsigned int>(lane) < nq;
+        const unsigned int cnt = mine ? qcnt[lane] : 0u;
         const unsigned int Ku = static_cast<unsigned int>(K);
         const bool fits = mine && cnt <= static_cast<unsigned int>(kListCap) && (SEL || cnt <= Ku);
         if (mine) {
             kept[iq] = min(cnt, Ku) | (fits ? 0u : kKeptLong);
             if (cnt > Ku) ++capped;
             if (!fits && cnt <= kWaveKeys)
-                long_slots[wave_start[x_first] + atomicAdd(long_counter(claims, xcd, kLongCount), 1u)] = qrow_s[sl];
+                long_slots[wave_start[x_first] + atomicAdd(long_counter(claims, xcd, kLongCount), 1u)] = win + lane;
             if (!fits && cnt > kWaveKeys)
-                long_slots[wave_start[x_end] - 1u - atomicAdd(long_counter(claims, xcd, kHugeCount), 1u)] = qrow_s[sl];
+                long_slots[wave_start[x_end] - 1u - atomicAdd(long_counter(claims, xcd, kHugeCount), 1u)] = win + lane;
         }
         if (fits && !(SEL && cnt > Ku)) {
-            const uint4 *from = reinterpret_cast<const uint4 *>(lst + sl * kListCap);
+            const uint4 *from = reinterpret_cast<const uint4 *>(lst + lane * kListCap);
             uint4 *to = reinterpret_cast<uint4 *>(temp + static_cast<size_t>(iq) * kListCap);
             for (unsigned int k = 0; 4u * k < cnt; ++k) to[k] = from[k];
         }
@@ -1097,37 +1122,89 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                 tcnt[lane] = take;
             }
             wave_lds_sync();
-            auto entry_query = [&](unsigned int t) {
-                int lo = 0, hi = static_cast<int>(nf) - 1;  // last query whose list starts at or before t
+            for (unsigned int t0 = 0; t0 < T; t0 += 64) {
+                const unsigned int t = t0 + lane;
+                int lo = 0, hi = static_cast<int>(nq) - 1;  // last query whose list starts at or before t
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
                     if (tpre[mid] <= t) lo = mid;
                     else hi = mid - 1;
                 }
-                return lo;
-            };
-            for (unsigned int t0 = 0; t0 < T; t0 += 64) {
-                const unsigned int t = t0 + lane;
+                const unsigned int row = static_cast<unsigned int>(__shfl(static_cast<int>(iq), lo));
                 if (t < T) {
-                    const int lo = entry_query(t);
-                    const unsigned int ls = (f0 + static_cast<unsigned int>(lo)) & (kQT - 1);
                     const unsigned int cq = tcnt[lo];
-                    const unsigned int *l = lst + ls * kListCap;
-                    const unsigned int *ld = lstd + ls * kListCap;
+                    const unsigned int *l = lst + lo * kListCap;
+                    const unsigned int *ld = lstd + lo * kListCap;
                     const unsigned int x = t - tpre[lo];
                     const unsigned long long key = (static_cast<unsigned long long>(ld[x]) << 32) | l[x];
                     unsigned int sr = 0;  // the entry's rank by (D, j) in its list
                     for (unsigned int u = 0; u < cq; ++u)
                         sr += ((static_cast<unsigned long long>(ld[u]) << 32) | l[u]) < key ? 1u : 0u;
-                    if (sr < Ku) temp[static_cast<size_t>(qid[ls]) * kListCap + sr] = l[x];
+                    if (sr < Ku) temp[static_cast<size_t>(row) * kListCap + sr] = l[x];
                 }
             }
         }
         wave_lds_sync();
     };
-    // The share is read in windows of 64 queries: lane l holds query win + l (its
-    // original row and packed cell), and a tile is a run of consecutive lanes with the
-    // same cell, found by a ballot (no per-tile lookup of where the cell ends).
+    float lead[kLead] = {};  // leading coordinates of the lane's query
+    // The queries [q0, q1) of the batch, which share a cell, against the cell's M
+    // candidates.
+    auto search_cell = [&](unsigned int q0, unsigned int q1, unsigned int M) {
+        // Candidates are fetched one chunk ahead so that their latency overlaps
+        // the tests of the current chunk: each lane holds its candidate's first
+        // four coordinates (one 16-byte load).  Idle lanes read row 0 (any row
+        // is a valid address) and are masked out of every ballot.
+        // The values are masked where they are used, not here, so that nothing
+        // waits for the load before the tests of the current chunk.
+        constexpr int kHeld = 4;  // candidate coordinates held per lane
+        static_assert(kLead <= kHeld, "the first stage uses the held coordinates");
+        float cn[kHeld];
+        unsigned int sn;
+        auto fetch = [&](unsigned int b) {
+            const unsigned int srow = map.row(b);
+            sn = b + lane < M ? srow : 0u;
+            const float4 v = *reinterpret_cast<const float4 *>(sorted + static_cast<size_t>(sn) * DP);
+            cn[0] = v.x;
+            cn[1] = v.y;
+            cn[2] = v.z;
+            cn[3] = v.w;
+        };
+        fetch(0u);
+        for (unsigned int base = 0; base < M; base += 64) {
+            float c[kHeld];
+#pragma unroll
+            for (int k = 0; k < kHeld; ++k) c[k] = cn[k];
+            const unsigned int s = sn;
+            // Lanes past the last candidate fail every first-stage test.
+            if (base + lane >= M) c[0] = INFINITY;
+            if (base + 64 < M) fetch(base + 64);
+            for (unsigned int q = q0; q < q1; ++q) {
+                // The query's leading coordinates, from the lane that holds them: scalar
+                // loads would make every step wait for the ring's LDS writes too (one
+                // counter covers both).
+                float qc[kLead];
+#pragma unroll
+                for (int k = 0; k < kLead; ++k)
+                    qc[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lead[k]), q));
+                // First stage: kLead terms for all 64 candidates; pairs that are not
+                // yet at r2 are queued (exact: the remaining terms only add).
+                const float acc = add_terms_r<0, kLead, kHeld, kLead>(0.0f, c, qc);
+                const unsigned long long m1 = __builtin_amdgcn_ballot_w64(acc < r2);
+                if (m1 == 0ull) continue;
+                if (acc < r2) {
+                    const unsigned int e = (tail + prefix_count(m1)) & (kRing - 1);
+                    ring[e] = (static_cast<unsigned long long>(uniform(q)) << 32) | s;
+                    racc[e] = acc;
+                }
+                tail += static_cast<unsigned int>(__popcll(m1));
+                if (tail - head >= 64u) {
+                    finish_rows(head, 64u);
+                    head += 64u;
+                }
+            }
+        }
+        tested += static_cast<unsigned long long>(M) * (q1 - q0);
+    };
     for (unsigned int piece = x_first + xblk * kWaves + wave_id(); piece < x_end;) {
         // The next piece is claimed before this one is worked off, so that the claim's
         // round trip overlaps the first loads.
@@ -1135,139 +1212,111 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         if (kPieces > 1 && lane == 0) claimed = atomicAdd(claim, 1u);
         const unsigned int q_lo = wave_start[piece];
         const unsigned int q_hi = wave_start[piece + 1u];
-        for (unsigned int win = q_lo; win < q_hi;) {
-            const unsigned int nwin = min(64u, q_hi - win);
-            uint2 me = make_uint2(0u, 0u);
-            if (static_cast<unsigned int>(lane) < nwin) me = sid[win + lane];
-            const unsigned int v_orig = me.x, v_pc = me.y;
-            for (unsigned int t0 = 0; t0 < nwin;) {
-                const unsigned int qs = win + t0;
-                if (qs >= ev_end) {
-                    const int e = n_events == 1 ? 0 : find_event(ev, n_events, qs);
-                    P = plans[e];
-                    const EventDesc E = ev[e];
-                    cell0 = static_cast<unsigned int>(E.cell0);
-                    ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
-                    rl = run_lane(P);
+        // The lane's query of a batch: its original row and packed cell, and the leading
+        // coordinates of its row.
+        // (16-float rows have no registers left to hold the latter ahead.)
+        constexpr bool kLeadAhead = DP != 16;
+        uint2 next = make_uint2(0u, 0u);
+        float next_lead[kLead] = {};
+        auto fetch_query = [&](unsigned int row) {
+            if (row < q_hi) {
+                next = sid[row];
+                if (kLeadAhead) {
+#pragma unroll
+                    for (int k = 0; k < kLead; ++k) next_lead[k] = sorted[static_cast<size_t>(row) * DP + k];
                 }
-                const unsigned int pc = __builtin_amdgcn_readlane(v_pc, t0);
-                const unsigned long long other =
-                    __builtin_amdgcn_ballot_w64(static_cast<unsigned int>(lane) >= nwin || v_pc != pc) &
-                    (~0ull << t0);
-                unsigned int t1 = other ? static_cast<unsigned int>(__builtin_ctzll(other)) : 64u;
-                t1 = min(t1, ev_end - win);  // a tile never crosses into the next event
-                const unsigned int qe = win + t1;
-                int u[kMaxAxes];
-                unpack_cell(pc, P.axes, u);
-                unsigned int start, pre, end;
-                const unsigned int M = wave_runs(u, cell0, P, rl, cell_start, start, pre, end);
-                for (unsigned int q0 = qs; q0 < qe; q0 += kQT) {
-                    const int Qn = static_cast<int>(uniform(min(static_cast<unsigned int>(kQT), qe - q0)));
-                    if (prio) {
-                        // A SIMD issues the oldest ready wave first, so with every workgroup
-                        // resident from the start the waves dispatched last finish last and
-                        // the SIMD runs its final stretch with few waves.  Issue priority
-                        // falls as a wave works off its share (3 in the first quarter, 0 in
-                        // the last), so that waves behind are issued first and the waves of
-                        // a SIMD finish closer together.
-                        const unsigned int left = q_hi - q0;
-                        const unsigned int share = q_hi - q_lo;
-                        if (4u * left > 3u * share) __builtin_amdgcn_s_setprio(3);
-                        else if (4u * left > 2u * share) __builtin_amdgcn_s_setprio(2);
-                        else if (4u * left > share) __builtin_amdgcn_s_setprio(1);
-                        else __builtin_amdgcn_s_setprio(0);
-                    }
-                    // Slots for the group's queries; when they do not fit, the queue is
-                    // emptied and the pending lists written out first.
-                    if (pend_n + static_cast<unsigned int>(Qn) > static_cast<unsigned int>(kQT)) {
-                        drain_all();
-                        flush(pend0, pend_n);
-                        pend0 += pend_n;
-                        pend_n = 0;
-                    }
-                    const unsigned int gs = pend0 + pend_n;  // number of the group's first query
-                    // Original row of query q0 + lane, held by lane q0 + lane - win.
-                    const unsigned int iq = static_cast<unsigned int>(
-                        __shfl(static_cast<int>(v_orig), static_cast<int>((q0 - win + lane) & 63u)));
-                    if (lane < Qn) {
-                        const unsigned int sl = (gs + static_cast<unsigned int>(lane)) & (kQT - 1);
-                        qcnt[sl] = 0u;
-                        qrow_s[sl] = q0 + lane;
-                        qid[sl] = iq;
-                    }
-                    pend_n += static_cast<unsigned int>(Qn);
-                    // Candidates are fetched one chunk ahead so that their latency overlaps
-                    // the tests of the current chunk: each lane holds its candidate's first
-                    // four coordinates (one 16-byte load).  Idle lanes read row 0 (any row
-                    // is a valid address) and are masked out of every ballot.
-                    // The values are masked where they are used, not here, so that nothing
-                    // waits for the load before the tests of the current chunk.
-                    constexpr int kHeld = 4;  // candidate coordinates held per lane
-                    static_assert(kLead <= kHeld, "the first stage uses the held coordinates");
-                    float cn[kHeld];
-                    unsigned int sn;
-                    auto fetch = [&](unsigned int b) {
-                        const unsigned int srow = map.row(b, pre, end);
-                        sn = b + lane < M ? srow : 0u;
-                        const float4 v = *reinterpret_cast<const float4 *>(sorted + static_cast<size_t>(sn) * DP);
-                        cn[0] = v.x;
-                        cn[1] = v.y;
-                        cn[2] = v.z;
-                        cn[3] = v.w;
-                    };
-                    map.begin(start, pre, end);
-                    fetch(0u);
-                    for (unsigned int base = 0; base < M; base += 64) {
-                        float c[kHeld];
-#pragma unroll
-                        for (int k = 0; k < kHeld; ++k) c[k] = cn[k];
-                        const unsigned int s = sn;
-                        // Lanes past the last candidate fail every first-stage test.
-                        if (base + lane >= M) c[0] = INFINITY;
-                        if (base + 64 < M) fetch(base + 64);
-                        // Query rows are wave-uniform (scalar loads); the next one is
-                        // requested before the current one is tested (the sorted rows end with
-                        // one padding row, so the request after the last query stays in bounds).
-                        float qn[kLead];
-#pragma unroll
-                        for (int k = 0; k < kLead; ++k) qn[k] = sorted[static_cast<size_t>(q0) * DP + k];
-                        const float *qrow = sorted + static_cast<size_t>(q0) * DP;
-                        for (int q = 0; q < Qn; ++q, qrow += DP) {
-                            float qc[kLead];
-#pragma unroll
-                            for (int k = 0; k < kLead; ++k) qc[k] = qn[k];
-#pragma unroll
-                            for (int k = 0; k < kLead; ++k) qn[k] = qrow[DP + k];
-                            // First stage: kLead terms for all 64 candidates; pairs that are not
-                            // yet at r2 are queued (exact: the remaining terms only add).
-                            const float acc = add_terms_r<0, kLead, kHeld, kLead>(0.0f, c, qc);
-                            const unsigned long long m1 = __builtin_amdgcn_ballot_w64(acc < r2);
-                            if (m1 == 0ull) continue;
-                            if (acc < r2) {
-                                const unsigned int e = (tail + prefix_count(m1)) & (kRing - 1);
-                                const unsigned int slot = uniform((gs + static_cast<unsigned int>(q)) & (kQT - 1));
-                                ring[e] = (static_cast<unsigned long long>(slot) << 32) | s;
-                                racc[e] = acc;
-                            }
-                            tail += static_cast<unsigned int>(__popcll(m1));
-                            if (tail - head >= 64u) {
-                                finish_rows(head, 64u);
-                                head += 64u;
-                            }
-                        }
-                    }
-                    if (lane < Qn) tested += M;
-                }
-                t0 = t1;
             }
-            win += nwin;
+        };
+        fetch_query(q_lo + lane);
+        for (win = q_lo; win < q_hi;) {
+            if (win >= ev_end) {
+                const int e = n_events == 1 ? 0 : find_event(ev, n_events, win);
+                P = plans[e];
+                const EventDesc E = ev[e];
+                cell0 = static_cast<unsigned int>(E.cell0);
+                ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
+                halves = run_count(P) <= 32;
+                rl = run_lane(P, halves);
+            }
+            const unsigned int v_orig = next.x, v_pc = next.y;
+#pragma unroll
+            for (int k = 0; k < kLead; ++k)
+                lead[k] = kLeadAhead ? next_lead[k]
+                                     : sorted[static_cast<size_t>(min(win + lane, q_hi - 1u)) * DP + k];
+            // The lanes that start a cell, and the batch's end: after its last whole cell
+            // (a batch never crosses into the next event).
+            const unsigned int n = min(min(64u, q_hi - win), ev_end - win);
+            const unsigned int pc_before = dpp_move<kWaveShr1>(v_pc);  // with every lane active
+            const unsigned long long starts = __builtin_amdgcn_ballot_w64((v_pc != pc_before) | (lane == 0)) &
+                                              (n < 64u ? (1ull << n) - 1ull : ~0ull);
+            unsigned int nq = n;
+            if (n > static_cast<unsigned int>(kQT)) {
+                const unsigned long long ends = (starts >> 1) & ((1ull << kQT) - 1ull);  // bit b: a batch of b + 1
+                nq = ends ? 64u - static_cast<unsigned int>(__builtin_clzll(ends)) : static_cast<unsigned int>(kQT);
+            }
+            // The next batch's queries are requested before this one is worked off.
+            const unsigned int after = win + nq;
+            fetch_query(after + lane);
+            if (prio) {
+                // A SIMD issues the oldest ready wave first, so with every workgroup
+                // resident from the start the waves dispatched last finish last and
+                // the SIMD runs its final stretch with few waves.  Issue priority
+                // falls as a wave works off its share (3 in the first quarter, 0 in
+                // the last), so that waves behind are issued first and the waves of
+                // a SIMD finish closer together.
+                const unsigned int left = q_hi - win;
+                const unsigned int share = q_hi - q_lo;
+                if (4u * left > 3u * share) __builtin_amdgcn_s_setprio(3);
+                else if (4u * left > 2u * share) __builtin_amdgcn_s_setprio(2);
+                else if (4u * left > share) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
+            }
+            if (lane < kQT) qcnt[lane] = 0u;
+            if (kTailLds)
+                for (unsigned int k = lane; k < nq * kTail; k += 64u)
+                    qtail[k] = sorted[static_cast<size_t>(win + k / kTail) * DP + kLead + k % kTail];
+            // End of the cell that query t of the batch lies in.
+            auto cell_end = [&](unsigned int t) {
+                const unsigned long long rest = t < 63u ? starts >> (t + 1u) : 0ull;
+                const unsigned int e = rest ? t + 1u + static_cast<unsigned int>(__builtin_ctzll(rest)) : 64u;
+                return min(e, nq);
+            };
+            for (unsigned int t0 = 0; t0 < nq;) {
+                // The runs of this cell and, in the other half of the wave, of the next.
+                const unsigned int t1 = cell_end(t0);
+                const bool two = halves && t1 < nq;
+                const unsigned int t2 = two ? cell_end(t1) : t1;
+                const unsigned int pc0 = __builtin_amdgcn_readlane(v_pc, t0);
+                const unsigned int pc1 = __builtin_amdgcn_readlane(v_pc, two ? t1 : t0);
+                const bool second = halves && lane >= 32;
+                unsigned int start, pre, end;
+                wave_runs(second ? pc1 : pc0, cell0, P, rl, rl.live && (!second || two), halves, cell_start, start,
+                          pre, end);
+                const unsigned long long some = map.keep(start, pre, end);
+                const unsigned int m_first = __builtin_amdgcn_readlane(end, halves ? 31 : 63);
+                const unsigned int m_second = lane63(end);
+                map.begin(!second, pre, end, 0u);
+#pragma clang loop unroll(disable)
+                for (unsigned int M = m_first, q = t0, qe = t1;;) {
+                    search_cell(q, qe, M);
+                    if (qe == t2) break;
+                    q = t1;
+                    qe = t2;
+                    M = m_second;
+                    map.begin(second, pre, end, static_cast<unsigned int>(__popcll(some & 0xffffffffull)));
+                }
+                t0 = t2;
+            }
+            if (tail != head) {
+                finish_rows(head, tail - head);
+                head = tail;
+            }
+            flush(nq, v_orig);
+            win = after;
         }
         piece = kPieces > 1 ? x_dyn + pool + __builtin_amdgcn_readfirstlane(claimed) * pools : x_end;
     }
-    drain_all();
-    if (pend_n) flush(pend0, pend_n);
     capped = wave_sum(capped);
-    tested = wave_sum(tested);
     if (lane == 0) {
         tested_w[wave_id()] = tested;
         survived_w[wave_id()] = survived;
@@ -1282,9 +1331,12 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
             sv += survived_w[w];
             c += capped_w[w];
         }
-        tested_out[blockIdx.x] = t;
-        tested_out[kMaxSearchBlocks + blockIdx.x] = sv;
-        capped_out[blockIdx.x] = c;
+        SearchCounts out;
+        out.tested = t;
+        out.survived = sv;
+        out.capped = c;
+        out.pad = 0u;
+        counts[blockIdx.x] = out;
     }
 }
 
@@ -1300,8 +1352,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
 __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const unsigned int *__restrict__ kept,
                                                           unsigned long long *__restrict__ tile_pre,
                                                           unsigned long long *__restrict__ group_sum, int tiles_kept,
-                                                          const unsigned long long *__restrict__ tested,
-                                                          const unsigned int *__restrict__ capped_blk,
+                                                          const SearchCounts *__restrict__ counts,
                                                           int search_blocks, Counters *__restrict__ ctr) {
     constexpr int kSumsWaves = kSumsBlock / 64;
     constexpr int kTilesPerWave = kKeptGroup / kSumsWaves;
@@ -1311,9 +1362,9 @@ __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const uns
         __shared__ unsigned long long red[3][kSumsWaves];
         unsigned long long t = 0, sv = 0, cp = 0;
         for (int k = threadIdx.x; k < search_blocks; k += kSumsBlock) {
-            t += tested[k];
-            sv += tested[kMaxSearchBlocks + k];
-            cp += capped_blk[k];
+            t += counts[k].tested;
+            sv += counts[k].survived;
+            cp += counts[k].capped;
         }
         t = wave_sum(t);
         sv = wave_sum(sv);
@@ -1409,10 +1460,10 @@ __device__ void long_list(const float *__restrict__ sorted, const unsigned int *
     const int nruns = run_count(P);
     for (int k = threadIdx.x; k < DP; k += kPlaceBlock) L.qv[k] = sorted[static_cast<size_t>(slot) * DP + k];
     if (wave_id() == 0) {
-        int u[kMaxAxes];
-        unpack_cell(sorted_id[2u * slot + 1u], P.axes, u);
         unsigned int start, pre, end;
-        const unsigned int M = wave_runs(u, cell0, P, run_lane(P), cell_start, start, pre, end);
+        const RunLane rl = run_lane(P, false);
+        wave_runs(sorted_id[2u * slot + 1u], cell0, P, rl, rl.live, false, cell_start, start, pre, end);
+        const unsigned int M = lane63(end);
         L.run_start[lane_id()] = start;
         L.run_pre[lane_id()] = pre;
         if (lane_id() == 0) {
@@ -1690,16 +1741,17 @@ __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, cons
                           unsigned int slot, unsigned int pc, float r2, unsigned int n_out, long long row0,
                           long long *__restrict__ out, unsigned int *dist, unsigned int *ids, RunMap &map) {
     const int lane = lane_id();
-    int u[kMaxAxes];
-    unpack_cell(pc, P.axes, u);
     unsigned int start, pre, end;
-    const unsigned int M = wave_runs(u, cell0, P, run_lane(P), cell_start, start, pre, end);
+    const RunLane rl = run_lane(P, false);
+    wave_runs(pc, cell0, P, rl, rl.live, false, cell_start, start, pre, end);
+    const unsigned int M = lane63(end);
     const float *qrow = sorted + static_cast<size_t>(slot) * DP;
     unsigned int h = 0;
-    map.begin(start, pre, end);
+    map.keep(start, pre, end);
+    map.begin(true, pre, end, 0u);
     for (unsigned int b = 0; b < M; b += 64u) {
         const unsigned int mm = b + lane;
-        const unsigned int srow = map.row(b, pre, end);
+        const unsigned int srow = map.row(b);
         const unsigned int s = mm < M ? srow : slot;
         const unsigned int j = sorted_id[2u * static_cast<size_t>(s)];
         float c[DP];
@@ -2028,21 +2080,19 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
                        a.ev_from_arg, ws.plans,
                        ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, ws.sorted_id);
     mark(4);
+    SearchCounts *counts = reinterpret_cast<SearchCounts *>(ws.rank);
     if (a.K < kListCap)
         hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
-                           a.search_prio);
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
     else
         hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, ws.tested, ws.capped_blk,
-                           a.search_prio);
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
     mark(5);
     // One block per group of tiles, and one for the search's counts.
     hipLaunchKernelGGL(k_kept_sums, dim3(ws.groups_kept_n + 1), dim3(kSumsBlock), 0, a.stream, rows, ws.kept,
-                       ws.sums_kept, ws.sums_kept2, ws.tiles_kept_n, ws.tested, ws.capped_blk, a.search_blocks,
-                       ws.ctr);
+                       ws.sums_kept, ws.sums_kept2, ws.tiles_kept_n, counts, a.search_blocks, ws.ctr);
     mark(6);
     const int place_blocks = ws.tiles_kept_n > kPlaceMinBlocks ? ws.tiles_kept_n : kPlaceMinBlocks;
     hipLaunchKernelGGL(k_place<DP>, dim3(static_cast<unsigned int>(place_blocks)), dim3(kPlaceBlock), 0, a.stream,
