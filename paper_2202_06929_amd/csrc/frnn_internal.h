@@ -60,9 +60,14 @@ constexpr int kPlaceBlock = 256;     // threads per workgroup of the placement p
 constexpr int kPlaceTile = 256;      // queries per workgroup of the placement pass (and kept tile)
 constexpr int kKeptGroup = 64;       // kept tiles per group (one workgroup of the kept-totals pass)
 constexpr int kSumsBlock = 1024;     // threads per workgroup of the kept-totals pass
-constexpr unsigned int kWaveKeys = 1024;  // hits of the longest list that one wave of the placement pass collects
-constexpr int kOwnerWindow = 4096;   // output positions formed in LDS at a time in placement
-constexpr int kPlaceMinBlocks = 512; // placement workgroups at least (all of them collect long lists)
+constexpr unsigned int kWaveKeys = 512;  // hits of the longest list that one wave of the placement pass collects
+constexpr int kOwnerWindow = 3072;   // output positions formed in LDS at a time in placement
+constexpr int kPlaceWords = 4096;    // LDS words of placement: an output window, four waves' or one workgroup's hits
+// Placement workgroups at least (all of them collect long lists): six per CU, so that
+// many small events with long lists keep as many lists in flight as the CUs hold (50,000
+// lists of a 60k-point event: whole build 175, 139, 127 and 129 us with 512, 1024, 1536
+// and 2048; 2,000 points without any 55.0, 55.2, 55.0 and 55.2).
+constexpr int kPlaceMinBlocks = 1536;
 constexpr int kMaxEvents = 65535;  // events per call (the second grid dimension)
 // A kept count with this bit set belongs to a long list (more than kListCap
 // neighbours, or more than K without the search's own selection), which the

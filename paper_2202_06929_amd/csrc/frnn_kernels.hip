@@ -1361,6 +1361,7 @@ __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const uns
     if (blockIdx.x == gridDim.x - 1) {
         __shared__ unsigned long long red[3][kSumsWaves];
         unsigned long long t = 0, sv = 0, cp = 0;
+#pragma unroll 8
         for (int k = threadIdx.x; k < search_blocks; k += kSumsBlock) {
             t += counts[k].tested;
             sv += counts[k].survived;
@@ -1438,7 +1439,7 @@ struct LongLds {
 
 // Hit keys a long list keeps in LDS (the two window arrays of the placement pass);
 // a list with more hits is selected by enumerating its candidates again per pass.
-constexpr unsigned int kKeyCap = kOwnerWindow;
+constexpr unsigned int kKeyCap = kPlaceWords / 2;
 
 // One list of more than kWaveKeys hits, collected again by the whole workgroup (every
 // thread calls this with the same arguments): the query's candidates are enumerated over the same
@@ -1732,9 +1733,13 @@ __device__ __forceinline__ void wave_select(const unsigned int *dist, unsigned i
 // wave a few hundred instructions and no barrier, and as many lists are in flight as
 // waves.  Collecting each with a whole workgroup, as the larger lists are (long_list,
 // a bitonic network with a barrier per step), the placement pass took 690 us for 51,000
-// lists of about 45 entries, against 111 us; 53 us against 17 on a 120k-point event
-// with some 2,000 lists of 17 and more, and 380 us against 57 with the nearest 32 of
-// about 95 kept for 17,000 queries.
+// lists of about 45 entries, against 53 us; 53 us against 14 on a 120k-point event
+// with 3,200 lists of 17 and more, and 380 us against 31 with the nearest 32 of
+// about 95 kept for 17,000 queries.  What bounds a list is its chain of round trips
+// (queue, ids, counts and cells, candidates), so the LDS of the pass is kept to what
+// leaves six workgroups per CU: lists of up to 512 hits and windows of 3,072 positions
+// against 1,024 and 4,096 (four workgroups) took the placement of a batch of 5.6M
+// points with 148,000 long lists from 560 to 458 us.
 template <int DP>
 __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, const unsigned int *__restrict__ sorted_id,
                           const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
@@ -1821,14 +1826,17 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                                                        long long *__restrict__ edge_off,
                                                        Report *__restrict__ report) {
     static_assert(kPlaceBlock == kPlaceTile, "one query per thread");
-    static_assert(kOwnerWindow >= kMaxK && kPlaceBlock == 256, "the window arrays hold a long list's keys");
-    // A window of the block's output (event-local rows, then neighbours); a
+    static_assert(kPlaceWords >= kMaxK && kPlaceBlock == 256, "a long list's ids fit");
+    static_assert(kPlaceWords >= 2 * static_cast<int>(kWaveKeys) * kWaves, "each wave has room for its hits");
+    static_assert(4 * kPlaceWords >= 5 * kOwnerWindow, "a window takes five bytes per position");
+    // A window of the block's output (neighbours, then queries as one byte each); a
     // neighbour entry of kSkip belongs to a long list, written by its collector.
     constexpr unsigned int kSkip = 0xffffffffu;
     __shared__ unsigned int o[kPlaceTile + 1];
-    __shared__ __align__(16) unsigned int wbuf[2 * kOwnerWindow];
-    unsigned int *wsrc = wbuf;
-    unsigned int *wdst = wbuf + kOwnerWindow;
+    __shared__ __align__(16) unsigned int wbuf[kPlaceWords];
+    unsigned int *wdst = wbuf;
+    unsigned char *wq = reinterpret_cast<unsigned char *>(wbuf + kOwnerWindow);  // the query, in the block
+    __shared__ unsigned int il_s[kPlaceTile];  // event-local row of each of the block's queries
     __shared__ unsigned long long scratch[kWaves];
     __shared__ LongLds<DP> L;
     __shared__ unsigned int map_all[kWaves][128];  // RunMap of each wave
@@ -1949,7 +1957,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                 }
             }
         }
-        const unsigned int il = static_cast<unsigned int>(i0 + q) - brow;  // the query's event-local row
+        il_s[q] = static_cast<unsigned int>(i0 + q) - brow;
         for (unsigned int w0 = 0; w0 < total; w0 += kOwnerWindow) {
             const unsigned int wend = total - w0 < kOwnerWindow ? total - w0 : kOwnerWindow;
             if (fixed) {
@@ -1957,7 +1965,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                 for (int u = 0; u < kListCap; ++u) {
                     const unsigned int pw = oq + static_cast<unsigned int>(u) - w0;  // wraps when before the window
                     if (static_cast<unsigned int>(u) < kq && oq + u >= w0 && pw < wend) {
-                        wsrc[pw] = il;
+                        wq[pw] = static_cast<unsigned char>(q);
                         wdst[pw] = v[u] - brow;
                     }
                 }
@@ -1965,14 +1973,14 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                 const unsigned int a0 = oq > w0 ? oq - w0 : 0u;
                 const unsigned int a1 = oq + kq > w0 ? min(oq + kq - w0, wend) : 0u;
                 for (unsigned int pw = a0; pw < a1; ++pw) {
-                    wsrc[pw] = il;
+                    wq[pw] = static_cast<unsigned char>(q);
                     wdst[pw] = kSkip;
                 }
             }
             __syncthreads();
             for (unsigned int pw = threadIdx.x; pw < wend; pw += kPlaceBlock) {
                 const long long at = static_cast<long long>(pre) + w0 + pw;
-                src[at] = wsrc[pw];
+                src[at] = il_s[wq[pw]];
                 const unsigned int dv = wdst[pw];
                 if (dv != kSkip) dst[at] = dv;
             }
@@ -2014,11 +2022,29 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         map.off = map_all[wave_id()];
         map.mark = map.off + 64;
         map.clear();
-        for (unsigned int h = lo + blockIdx.x / 8u * kWaves + wave_id(); h < hi; h += xnb * kWaves) {
+        // An entry's row, and then the row's ids, are requested while the entries before
+        // it are worked off.
+        const unsigned int step = xnb * kWaves;
+        auto entry = [&](unsigned int h) -> unsigned int {
+            if (h >= hi) return 0u;
             while (h >= q_wave[queue + 1u]) ++queue;
-            const unsigned int slot = uniform(long_slots[q_first[queue] + (h - q_wave[queue])]);
-            if (static_cast<long long>(slot) >= rows) continue;  // only a corrupted queue
-            const uint2 id = reinterpret_cast<const uint2 *>(sorted_id)[slot];
+            const unsigned int slot = long_slots[q_first[queue] + (h - q_wave[queue])];
+            return static_cast<long long>(slot) < rows ? slot : 0u;  // only a corrupted queue holds another
+        };
+        const uint2 *sid = reinterpret_cast<const uint2 *>(sorted_id);
+        unsigned int h = lo + blockIdx.x / 8u * kWaves + wave_id();
+        unsigned int slot1 = entry(h);
+        unsigned int slot2 = entry(h + step);
+        uint2 id1 = sid[slot1];
+        long long ev_lo = 0, ev_end = 0;  // rows of the event that P and cell0 are of
+        Plan P;
+        unsigned int cell0 = 0;
+        for (; h < hi; h += step) {
+            const unsigned int slot = uniform(slot1);
+            const uint2 id = id1;
+            slot1 = slot2;
+            slot2 = entry(h + 2u * step);
+            id1 = sid[slot1];
             const long long gi = uniform(id.x);  // the query's original row
             const int t = static_cast<int>(gi / kPlaceTile);
             if (gi >= rows || t >= tiles_kept) continue;  // likewise
@@ -2034,12 +2060,17 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                 if (x0 + 3 < gi) at += c.w & ~kKeptLong;
             }
             const unsigned int nq = uniform(kept[gi]) & ~kKeptLong;
-            const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
-            const Plan P = plans[e];
+            if (gi < ev_lo || gi >= ev_end) {
+                const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
+                P = plans[e];
+                cell0 = static_cast<unsigned int>(ev[e].cell0);
+                ev_lo = ev[e].row0;
+                ev_end = ev_lo + ev[e].n;
+            }
             at = wave_sum(at);
             if (at + nq > cap) continue;  // cannot happen when E <= cap
-            wave_list<DP>(sorted, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot,
-                          uniform(id.y), r2, nq, ev[e].row0, dst + at, lds, lds + kWaveKeys, map);
+            wave_list<DP>(sorted, sorted_id, cell_start, P, cell0, slot, uniform(id.y), r2, nq, ev_lo, dst + at, lds,
+                          lds + kWaveKeys, map);
         }
     }
     __syncthreads();
