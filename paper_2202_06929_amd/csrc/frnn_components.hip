@@ -33,6 +33,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <atomic>
+
 #include "frnn.h"
 
 namespace {
@@ -74,6 +76,13 @@ __device__ unsigned int cc_find(unsigned int *parent, unsigned int x) {
         st(parent + x, gp);
         x = gp;
     }
+}
+
+// Orders the LDS accesses of one wave.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Root of x by plain reads (no path halving).
@@ -130,6 +139,7 @@ __device__ void cc_union(unsigned int *parent, unsigned int u, unsigned int v, C
         if (__hip_atomic_compare_exchange_strong(parent + hi, &expected, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return;
+        if (expected == lo) return;  // joined meanwhile, as most failed swaps find
         u = cc_root(parent, expected);
         v = lo;
     }
@@ -149,9 +159,9 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_init(unsigned int *parent, long
 // cluster whose vertices all neighbour its smallest vertex (the FRNN graph of a
 // track: its points lie within r of one another) is a star before the union-find
 // pass, which then finds equal roots for its edges and swaps nothing.  Lanes of a
-// wave that share a source take the minimum of their targets below it by a
-// segmented reduction (edges come grouped by source), and one lane per source does
-// a device-scope atomicMin on the source's parent.  The parent array then still
+// wave that share a source (edges come grouped by source) take the minimum of their
+// targets, the first one where targets ascend and else by a segmented reduction, and
+// one lane per source does a device-scope atomicMin on the source's parent.  The parent array then still
 // points only to smaller ids and every entry to a neighbour or itself: each
 // vertex is hooked at most under one neighbour, a valid union of two trees, as
 // every vertex is still a root before this pass.  Whatever this pass leaves
@@ -164,45 +174,78 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_minhook(const long long *__rest
                                                          const long long *__restrict__ dst, long long n_edges,
                                                          long long n, const float *__restrict__ scores,
                                                          float threshold, unsigned int *parent) {
-    const long long stride = static_cast<long long>(gridDim.x) * kCcBlock;
     const int lane = static_cast<int>(threadIdx.x & 63u);
+    constexpr long long kWaveSpan = 64 * kPerLane;
+    const long long span = static_cast<long long>(kCcBlock) * kPerLane;
+    const long long stride = static_cast<long long>(gridDim.x) * span;
+    const unsigned long long below = (1ull << lane) - 1ull;
     // Wave-aligned bases, so that every lane of a wave takes the same trip count.
-    for (long long e0 = static_cast<long long>(blockIdx.x) * kCcBlock + (threadIdx.x & ~63u); e0 < n_edges;
+    for (long long e0 = static_cast<long long>(blockIdx.x) * span + (threadIdx.x >> 6) * kWaveSpan; e0 < n_edges;
          e0 += stride) {
-        const long long e = e0 + lane;
-        unsigned int a = 0xffffffffu, m = 0xffffffffu;
-        if (e < n_edges && !(scores && !(scores[e] > threshold))) {
-            const long long x = src[e], y = dst[e];
-            if (x >= 0 && x < n && y >= 0 && y < n) {  // out-of-range edges are reported by the hook pass
-                a = static_cast<unsigned int>(x);
-                m = static_cast<unsigned int>(y);
-            }
-        }
-        // Minimum over the lanes at or after this one with the same source.
+        constexpr unsigned int kNone = 0xffffffffu;  // past the end or out of range (reported by the hook pass)
+        unsigned int a[kPerLane], t[kPerLane];
+        bool kept[kPerLane];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned int a2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(a), o));
-            const unsigned int m2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(m), o));
-            if (lane + o < 64 && a2 == a && m2 < m) m = m2;
+        for (int j = 0; j < kPerLane; ++j) {
+            const long long e = e0 + 64 * j + lane;
+            const bool in = e < n_edges;
+            const long long x = in ? src[e] : -1, y = in ? dst[e] : -1;
+            const bool ok = x >= 0 && x < n && y >= 0 && y < n;
+            a[j] = ok ? static_cast<unsigned int>(x) : kNone;
+            t[j] = ok ? static_cast<unsigned int>(y) : kNone;
+            kept[j] = ok && !(scores && !(scores[e] > threshold));
         }
-        const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(a), 1));
-        const bool head = lane == 0 || a_prev != a;
-        if (head && a != 0xffffffffu && m < a) atomicMin(parent + a, m);
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(a[j]), 1));
+            const unsigned int t_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(t[j]), 1));
+            const bool head = lane == 0 || a_prev != a[j];
+            if (__builtin_amdgcn_ballot_w64(!head && t_prev > t[j]) == 0ull) {
+                // Targets ascend within every source, as in the graph builder's lists: a
+                // source's smallest kept target is its first.
+                const unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
+                const unsigned long long keeps = __builtin_amdgcn_ballot_w64(kept[j]);
+                const unsigned long long run = ~0ull << (63 - __builtin_clzll(heads & (below | (1ull << lane))));
+                if (kept[j] && (keeps & below & run) == 0ull && t[j] < a[j]) atomicMin(parent + a[j], t[j]);
+                continue;
+            }
+            // Minimum over the lanes at or after this one with the same source.
+            unsigned int m = kept[j] ? t[j] : kNone;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned int a2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(a[j]), o));
+                const unsigned int m2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(m), o));
+                if (lane + o < 64 && a2 == a[j] && m2 < m) m = m2;
+            }
+            if (head && a[j] != kNone && m < a[j]) atomicMin(parent + a[j], m);
+        }
     }
 }
 
+// Each wave takes 64 kPerLane edges at a time.  Most have endpoints with the same
+// parent (after the min-neighbour pass) and are done; the others are queued in LDS as
+// pairs of parents and joined 64 at a time, one per lane: what the pass waits for is its
+// compare-and-swaps (8.6 us without them, 15.6 with, on 1.06M edges), so only the first
+// of a run of equal pairs swaps (42,000 edges lead between 1,670 pairs of trees there),
+// and a failed swap that finds the wanted parent is done.  Walking and swapping edge by
+// edge, four per lane in turn, took 17 us, and 36 against 33 on 2.4M scored edges.
 __global__ __launch_bounds__(kCcBlock) void k_cc_hook(const long long *__restrict__ src,
                                                       const long long *__restrict__ dst, long long n_edges,
                                                       long long n, const float *__restrict__ scores,
                                                       float threshold, unsigned int *parent, CcState *state) {
+    __shared__ uint2 queue_all[kCcBlock / 64][64 * kPerLane];
+    const int lane = static_cast<int>(threadIdx.x & 63u);
+    uint2 *queue = queue_all[threadIdx.x >> 6];
+    constexpr long long kWaveSpan = 64 * kPerLane;
     const long long span = static_cast<long long>(kCcBlock) * kPerLane;
     const long long stride = static_cast<long long>(gridDim.x) * span;
-    for (long long e0 = static_cast<long long>(blockIdx.x) * span + threadIdx.x; e0 < n_edges; e0 += stride) {
+    for (long long e0 = static_cast<long long>(blockIdx.x) * span + (threadIdx.x >> 6) * kWaveSpan; e0 < n_edges;
+         e0 += stride) {
         unsigned int ra[kPerLane], rb[kPerLane];
         bool act[kPerLane];
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
-            const long long e = e0 + static_cast<long long>(kCcBlock) * j;
+            const long long e = e0 + 64 * j + lane;
             act[j] = e < n_edges && !(scores && !(scores[e] > threshold));
             const long long a = act[j] ? src[e] : 0, b = act[j] ? dst[e] : 0;
             if (act[j] && (a < 0 || a >= n || b < 0 || b >= n)) {
@@ -212,19 +255,36 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_hook(const long long *__restric
             ra[j] = static_cast<unsigned int>(a);
             rb[j] = static_cast<unsigned int>(b);
         }
-        // Endpoints with the same parent are in one tree already (the common case
-        // after the min-neighbour pass): no walk to the roots.
+        // Endpoints with the same parent are in one tree already: no walk to the roots.
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
             ra[j] = act[j] ? ld(parent + ra[j]) : 0u;
             rb[j] = act[j] ? ld(parent + rb[j]) : 0u;
         }
+        unsigned int queued = 0;
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
-            if (!act[j] || ra[j] == rb[j]) continue;
-            cc_find2(parent, ra[j], rb[j]);
-            if (ra[j] != rb[j]) cc_union(parent, ra[j], rb[j], state);
+            const bool join = act[j] && ra[j] != rb[j];
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(join);
+            if (join)
+                queue[queued + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned int>(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(m), 0u))] =
+                    make_uint2(ra[j], rb[j]);
+            queued += static_cast<unsigned int>(__popcll(m));
         }
+        wave_lds_sync();
+        for (unsigned int q0 = 0; q0 < queued; q0 += 64u) {
+            const unsigned int q = q0 + lane;
+            uint2 r = q < queued ? queue[q] : make_uint2(0u, 0u);
+            cc_find2(parent, r.x, r.y);
+            const unsigned int hi = max(r.x, r.y), lo = min(r.x, r.y);
+            // A source's edges are neighbours in the queue and mostly lead from one tree
+            // to one other: the first of each run joins them.
+            const unsigned int hi_before = static_cast<unsigned int>(__shfl_up(static_cast<int>(hi), 1));
+            const unsigned int lo_before = static_cast<unsigned int>(__shfl_up(static_cast<int>(lo), 1));
+            if (hi != lo && (lane == 0 || hi != hi_before || lo != lo_before)) cc_union(parent, hi, lo, state);
+        }
+        wave_lds_sync();
     }
 }
 
@@ -301,7 +361,7 @@ int enqueue(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_v
     const long long n = n_vertices;
     hipLaunchKernelGGL(k_cc_init, dim3(grid_for(n)), dim3(kCcBlock), 0, s, parent, n, state);
     if (n_edges > 0)
-        hipLaunchKernelGGL(k_cc_minhook, dim3(grid_for(n_edges)), dim3(kCcBlock), 0, s,
+        hipLaunchKernelGGL(k_cc_minhook, dim3(grid_for((n_edges + kPerLane - 1) / kPerLane)), dim3(kCcBlock), 0, s,
                            reinterpret_cast<const long long *>(src), reinterpret_cast<const long long *>(dst),
                            static_cast<long long>(n_edges), n, scores, threshold, parent);
     if (n_edges > 0)
@@ -316,7 +376,8 @@ int enqueue(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_v
     return hipGetLastError() == hipSuccess ? FRNN_OK : FRNN_ERR_HIP;
 }
 
-thread_local long long *t_result = nullptr;  // pinned host copy of [n_components, status]
+thread_local long long *t_result = nullptr;      // pinned host copy of [n_components, status]
+thread_local long long *t_result_dev = nullptr;  // its device-visible address (null: copy instead)
 
 }  // namespace
 
@@ -342,18 +403,31 @@ extern "C" int frnn_components(const int64_t *src, const int64_t *dst, int64_t n
     const int st = check(src, dst, n_edges, n_vertices, workspace, workspace_bytes, labels);
     if (st != FRNN_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    // The last kernel writes the result straight into pinned host memory when the runtime
+    // maps it for the device (a copy enqueued behind the kernels took several us);
+    // otherwise it is copied back.
     if (!t_result) {
         void *p = nullptr;
-        if (hipHostMalloc(&p, 2 * sizeof(long long), hipHostMallocDefault) != hipSuccess) return FRNN_ERR_HIP;
+        if (hipHostMalloc(&p, 2 * sizeof(long long), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+            if (hipHostMalloc(&p, 2 * sizeof(long long), hipHostMallocDefault) != hipSuccess) return FRNN_ERR_HIP;
+        } else {
+            void *dp = nullptr;
+            if (hipHostGetDevicePointer(&dp, p, 0) == hipSuccess) t_result_dev = static_cast<long long *>(dp);
+        }
         t_result = static_cast<long long *>(p);
     }
-    int64_t *result_device = reinterpret_cast<int64_t *>(
-        static_cast<char *>(workspace) + 256 + align256(sizeof(unsigned int) * static_cast<size_t>(n_vertices)));
+    int64_t *result_device =
+        t_result_dev ? reinterpret_cast<int64_t *>(t_result_dev)
+                     : reinterpret_cast<int64_t *>(static_cast<char *>(workspace) + 256 +
+                                                   align256(sizeof(unsigned int) * static_cast<size_t>(n_vertices)));
+    t_result[1] = FRNN_ERR_HIP;  // until the result arrives
     const int e = enqueue(src, dst, n_edges, n_vertices, scores, threshold, workspace, labels, result_device, s);
     if (e != FRNN_OK) return e;
-    if (hipMemcpyAsync(t_result, result_device, 2 * sizeof(long long), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    if (!t_result_dev &&
+        hipMemcpyAsync(t_result, result_device, 2 * sizeof(long long), hipMemcpyDeviceToHost, s) != hipSuccess)
         return FRNN_ERR_HIP;
+    if (hipStreamSynchronize(s) != hipSuccess) return FRNN_ERR_HIP;
+    std::atomic_thread_fence(std::memory_order_acquire);
     if (n_components) *n_components = t_result[0];
     return static_cast<int>(t_result[1]);
 }
