@@ -283,6 +283,8 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
     // About 16 coordinates per thread of the bounds pass, at most kBoundsBlocks blocks per event.
     const long long bb = (static_cast<long long>(max_n) * d + 16 * kBlock - 1) / (16 * kBlock);
     a.bounds_blocks = static_cast<int>(bb < 1 ? 1 : (bb > kBoundsBlocks ? kBoundsBlocks : bb));
+    a.bin_span = bin_span_for(max_n);
+    a.tile_points = rows > kTilePointsFrom ? kTilePointsLarge : kTilePointsMin;
     a.ev0 = descs ? descs[0] : EventDesc{};
     a.ev_from_arg = n_events == 1 ? 1 : 0;
     a.edge_off_out = edge_off_out;

@@ -55,7 +55,35 @@ constexpr int search_pieces(int dpad) { return dpad <= 24 ? 1 : 2; }
 constexpr int kPools = 8;
 constexpr int kPoolStride = 32;  // counters 128 bytes apart
 constexpr int kKeysBlock = 1024;     // threads per workgroup of the key/histogram pass
-constexpr long long kKeysTwoFrom = 196608;  // events above this many rows: two points per thread in k_keys
+constexpr int kKeysPer = 2;          // points per thread of the key/histogram pass
+constexpr int kKeysSpan = kKeysBlock * kKeysPer;
+// Binning through tiles (k_bin, k_tiles), for calls whose largest event has at most
+// kBinMaxRows rows: shares of kKeysBlock or twice as many rows, at most kBinMaxShares an
+// event; tiles of up to 2^kTileShiftMax cells and, on average, at most kTilePointsMin
+// points: fewer leave the shares' segments of a tile too short, more too few tiles for
+// the CUs (120k points: whole build 64.9, 65.3, 66.5 and 70.7 us with 256, 512, 1024 and
+// 2048; 300k points 138.8, 138.0, 141.8, 141.5).  Calls of more than kTilePointsFrom rows
+// have tiles enough for kTilePointsLarge (a batch of 5.6M rows 1754, 1651, 1639, 1660).
+constexpr int kTilesBlock = 512;
+constexpr int kBinMaxShares = 512;
+constexpr int kBinMaxRows = kBinMaxShares * kKeysBlock * 2;
+constexpr int kBinMaxTiles = 4096;
+constexpr int kTileShiftMax = 12;
+constexpr int kTilePointsMin = 512;
+constexpr int kTilePointsLarge = 1024;
+constexpr long long kTilePointsFrom = 1 << 19;
+// Rows per share of a call (0: binning by atomics).
+constexpr int bin_span_for(long long max_n) {
+    return max_n > kBinMaxRows ? 0 : (max_n > kBinMaxShares * kKeysBlock ? 2 * kKeysBlock : kKeysBlock);
+}
+// Most tiles an event of n rows can have: with the shift at its largest, cells_max /
+// 2^kTileShiftMax + 1; below it n 2^(shift + 1) > n_cells tile_points.
+constexpr int bin_tiles_bound(long long n, int tile_points) {
+    const long long by_points = 2 * n / tile_points + 1;
+    const long long by_cells = ((2 * n > 32768 ? 2 * n : 32768) >> kTileShiftMax) + 1;
+    return static_cast<int>(by_points > by_cells ? by_points : by_cells);
+}
+static_assert(bin_tiles_bound(kBinMaxRows, kTilePointsMin) <= kBinMaxTiles + 1, "the tiles of an event fit k_bin's LDS");
 constexpr int kPlaceBlock = 256;     // threads per workgroup of the placement pass
 constexpr int kPlaceTile = 256;      // queries per workgroup of the placement pass (and kept tile)
 constexpr int kKeptGroup = 64;       // kept tiles per group (one workgroup of the kept-totals pass)
@@ -105,6 +133,8 @@ struct Plan {
     int reach;              // neighbour cells searched on each side, per axis
     int abort;              // a coordinate was NaN or infinite
     int axes;               // binned coordinates (3 or 4)
+    int tile_shift;         // log2 of the cells per tile
+    int n_tiles;            // tiles of the event
 };
 
 // Bits per axis in a packed cell coordinate word (axis p at bits [p b, p b + b)).
@@ -204,6 +234,8 @@ struct LaunchArgs {
     int search_blocks;      // resident workgroups of the search kernel
     int search_prio;        // 1: the search grid is one round of resident workgroups
     int bounds_blocks;      // bounds partials per event (<= kBoundsBlocks)
+    int bin_span;           // rows per share of the binning through tiles, or 0 (by atomics)
+    int tile_points;        // points per tile aimed at
     EventDesc ev0;          // event 0, written to ws.ev by the first kernel when ev_from_arg
     int ev_from_arg;
     long long *edge_off_out;  // device [n_events + 2] for the edge ranges and status, or null (workspace)

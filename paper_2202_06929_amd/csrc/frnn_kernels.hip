@@ -4,10 +4,16 @@
 // coordinates into grid cells, then visit only the cells around each query):
 //   k_bounds      min/max of the binned coordinates and a non-finite check over
 //                 all coordinates; clears the histogram, tile totals, counters
-//   k_keys        grid plan (cell edge, cells per axis), cell key of every point,
-//                 histogram with in-cell arrival rank, per-tile histogram totals
+//   k_bin         grid plan (cell edge, cells per axis), cell of every point, each share
+//                 of points sorted by tile (a run of cells) in LDS
+//   k_tiles       each tile's points gathered from the shares, counted and ordered by
+//                 cell in LDS: first sorted row of each cell, the search's shares of equal
+//                 work (cells' fixed costs plus queries), rows copied into cell order
+//   or, for calls with an event of more than kBinMaxRows rows, in place of the two:
+//   k_keys        grid plan, cell key of every point, histogram with in-cell arrival
+//                 rank, per-tile histogram totals
 //   k_scan_cells  exclusive scan of the histogram -> first sorted row of each cell;
-//                 the search's shares of equal work (cells' fixed costs plus queries)
+//                 the search's shares of equal work
 //   k_scatter     counting-sort scatter: rows copied into cell order
 //   k_search      each wave takes a share of equal work in cell order: a
 //                 cell's queries against the (2R+1)^(axes-1) contiguous runs of
@@ -255,18 +261,29 @@ struct Dims {
     int c[kMaxAxes];
 };
 
+// Minimum and maximum of N columns that a thread sees, and whether a value was not a
+// number (infinite values show in the minimum or maximum).
+template <int N>
 struct BoundsAcc {
-    float mn[kMaxAxes] = {INFINITY, INFINITY, INFINITY, INFINITY};
-    float mx[kMaxAxes] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    int bad = 0;
-    __device__ __forceinline__ void add(float v, int col, const Dims &dd) {
-        bad |= !__builtin_isfinite(v);
+    float mn[N], mx[N];
+    bool nan = false;
+    __device__ __forceinline__ BoundsAcc() {
 #pragma unroll
-        for (int p = 0; p < kMaxAxes; ++p)
-            if (col == dd.c[p]) {
-                mn[p] = fminf(mn[p], v);
-                mx[p] = fmaxf(mx[p], v);
-            }
+        for (int k = 0; k < N; ++k) {
+            mn[k] = INFINITY;
+            mx[k] = -INFINITY;
+        }
+    }
+    __device__ __forceinline__ void add(int k, float v) {
+        nan |= v != v;
+        mn[k] = fminf(mn[k], v);
+        mx[k] = fmaxf(mx[k], v);
+    }
+    __device__ __forceinline__ bool bad() const {
+        bool b = nan;
+#pragma unroll
+        for (int k = 0; k < N; ++k) b |= mn[k] == -INFINITY || mx[k] == INFINITY;
+        return b;
     }
 };
 
@@ -292,63 +309,86 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
     const EventDesc E = ev_from_arg ? ev0 : ev[blockIdx.y];
     const int tid = blockIdx.x * kBlock + threadIdx.x;
     const int stride = gridDim.x * kBlock;
-    BoundsAcc acc;
     const long long total = static_cast<long long>(E.n) * d;
     const float *Xe = E.pts;
-    // The column of a thread's element advances by a fixed step per stride, so it
-    // is tracked incrementally instead of a 64-bit remainder per element.
-    auto next_col = [d](int col, int step) {
-        col += step;
-        return col >= d ? col - d : col;
-    };
+    float mn[kMaxAxes] = {INFINITY, INFINITY, INFINITY, INFINITY};
+    float mx[kMaxAxes] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    int bad = 0;
+    // A thread's elements (float4 groups, or single ones) are a whole number of rows
+    // apart, so that it sees the same columns every time and needs no look at them per
+    // element: a minimum, a maximum and a comparison each (with the column tracked and
+    // compared per element the pass was bound by its instructions: 67 us against 52 on a
+    // batch of 5.6M 8-D points, 8.9 against 5.5 on 300k 12-D and 8.2 against 4.3 on 47k
+    // 10-D ones, whose rows are read one float at a time).  Several loads are in flight per thread, issued together also for the
+    // last, partial round (the grid gives most threads exactly four).
     if (vec4) {
         const float4 *X4 = reinterpret_cast<const float4 *>(Xe);
         const long long nv = total / 4;
-        const int step = static_cast<int>((4ll * stride) % d);
-        int col = static_cast<int>((4ll * tid) % d);
-        // Four independent loads in flight per thread, issued together also for the
-        // last, partial round (the grid gives most threads exactly four), so that a
-        // thread waits for one round trip per four loads.
-        for (long long v = tid; v < nv; v += 4ll * stride) {
+        const int groups = d / 4;
+        const long long step = static_cast<long long>(stride / groups) * groups;
+        BoundsAcc<4> acc;
+        for (long long v = tid < step ? tid : nv; v < nv; v += 4 * step) {
             float4 x[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const long long w = v + u * static_cast<long long>(stride);
-                x[u] = w < nv ? X4[w] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                // Past the end the thread's own first group is read again.
+                const long long w = v + u * step;
+                x[u] = X4[w < nv ? w : v];
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                if (v + u * static_cast<long long>(stride) < nv) {
-                    acc.add(x[u].x, col, dd);
-                    acc.add(x[u].y, col + 1, dd);
-                    acc.add(x[u].z, col + 2, dd);
-                    acc.add(x[u].w, col + 3, dd);
-                }
-                col = next_col(col, step);
+                acc.add(0, x[u].x);
+                acc.add(1, x[u].y);
+                acc.add(2, x[u].z);
+                acc.add(3, x[u].w);
             }
         }
+        bad = acc.bad();
+        const int col = 4 * (tid % groups);
+#pragma unroll
+        for (int p = 0; p < kMaxAxes; ++p)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (col + k == dd.c[p]) {
+                    mn[p] = acc.mn[k];
+                    mx[p] = acc.mx[k];
+                }
     } else {
-        const int step = stride % d;
-        int col = tid % d;
-        for (long long e = tid; e < total; e += stride) {
-            acc.add(Xe[e], col, dd);
-            col = next_col(col, step);
+        const long long step = static_cast<long long>(stride / d) * d;
+        BoundsAcc<1> acc;
+        for (long long e = tid < step ? tid : total; e < total; e += 8 * step) {
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const long long w = e + u * step;
+                x[u] = Xe[w < total ? w : e];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc.add(0, x[u]);
         }
+        bad = acc.bad();
+        const int col = tid % d;
+#pragma unroll
+        for (int p = 0; p < kMaxAxes; ++p)
+            if (col == dd.c[p]) {
+                mn[p] = acc.mn[0];
+                mx[p] = acc.mx[0];
+            }
     }
 #pragma unroll
     for (int p = 0; p < kMaxAxes; ++p) {
-        acc.mn[p] = wave_min(acc.mn[p]);
-        acc.mx[p] = wave_max(acc.mx[p]);
+        mn[p] = wave_min(mn[p]);
+        mx[p] = wave_max(mx[p]);
     }
-    acc.bad = wave_any(acc.bad);
+    bad = wave_any(bad);
     __shared__ BoundsPartial sp[kWaves];
     if (lane_id() == 0) {
         BoundsPartial &p = sp[wave_id()];
         for (int q = 0; q < kMaxAxes; ++q) {
-            p.mn[q] = acc.mn[q];
-            p.mx[q] = acc.mx[q];
+            p.mn[q] = mn[q];
+            p.mx[q] = mx[q];
         }
-        p.nonfinite = acc.bad;
+        p.nonfinite = bad;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -371,7 +411,7 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
 // Every block derives the same plan from the same partials (min/max are exact).
 // Axes from `axes` on are not binned: one cell each.
 __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, float r,
-                            int cell_div, int axes, int cells_max, Plan *out) {
+                            int cell_div, int axes, int cells_max, int n, int tile_points, Plan *out) {
     float mn[kMaxAxes] = {INFINITY, INFINITY, INFINITY, INFINITY};
     float mx[kMaxAxes] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     int bad = 0;
@@ -449,6 +489,14 @@ __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, 
     out->reach = cell_div;
     out->abort = bad;
     out->axes = axes;
+    // Cells per tile of the tile pass: the power of two that gives a tile at most
+    // tile_points points on average.
+    int shift = 0;
+    while (shift < kTileShiftMax &&
+           static_cast<long long>(n) << (shift + 1) <= static_cast<long long>(out->n_cells) * tile_points)
+        ++shift;
+    out->tile_shift = shift;
+    out->n_tiles = (out->n_cells + (1 << shift) - 1) >> shift;
 }
 
 // Clamping is monotone and moves no coordinate by more than the clamp, so two
@@ -486,10 +534,9 @@ constexpr int kMaxCellTiles = ((1 << 24) + kScanTile - 1) / kScanTile + 2;
 // stores its plan; every block computes the cells of kKeysBlock x kKeysPer of the
 // event's rows.  Two points per thread halve the blocks, and with them the
 // blocks' atomic adds to each tile total, which pays for large events.
-template <int kKeysPer>
 __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
-                                                     float r, int cell_div, const EventDesc *__restrict__ ev,
-                                                     EventDesc ev0, int ev_from_arg,
+                                                     float r, int cell_div, int tile_points,
+                                                     const EventDesc *__restrict__ ev, EventDesc ev0, int ev_from_arg,
                                                      const BoundsPartial *__restrict__ part, int nparts,
                                                      Plan *__restrict__ plans, Counters *__restrict__ ctr,
                                                      unsigned int *__restrict__ pcell,
@@ -501,7 +548,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
     __shared__ unsigned long long tile_count[kMaxCellTiles];
     const int e = blockIdx.y;
     const EventDesc E = ev_from_arg ? ev0 : ev[e];  // one event: no load before the points'
-    constexpr int kSpan = kKeysBlock * kKeysPer;
+    constexpr int kSpan = kKeysSpan;
     if (blockIdx.x != 0 && static_cast<long long>(blockIdx.x) * kSpan >= E.n) return;
     // kKeysPer points per thread, kKeysBlock apart; their binned coordinates are
     // loaded before the plan is derived so that the two latencies overlap.
@@ -519,7 +566,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
         }
     }
     if (wave_id() == 0)
-        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, &P);
+        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points, &P);
     const int tile_end = static_cast<int>((E.cell0 + E.cells_max - 1) / kScanTile);
     const int ntiles = tile_end - E.tile0 + 1;
     for (int t = threadIdx.x; t < ntiles; t += kKeysBlock) tile_count[t] = 0ull;
@@ -788,6 +835,293 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int d, int vec4, const Event
         // The original row and the packed cell of a sorted row sit side by side, so
         // the scattered write is one 8-byte store instead of two 4-byte ones.
         reinterpret_cast<uint2 *>(sorted_id)[slot] = make_uint2(static_cast<unsigned int>(gi), pc);
+    }
+}
+
+// --------------------------------------------------- binning through tiles in LDS
+
+// Events of up to kBinMaxRows rows are sorted into cells without an atomic on global
+// memory per point: k_bin sorts each share of points by tile (a run of cells) in LDS, and
+// k_tiles gathers one tile's points from all shares, counts and orders them by cell in
+// LDS and writes rows, cell starts and search shares.  By atomics (k_keys, k_scan_cells,
+// k_scatter: larger events, whose shares would hold too few points of each of their many
+// tiles) every point takes a returning atomic beyond its XCD's L2 and its row is written
+// to a place that shares its lines with rows of other XCDs.  One 120k-point event: 13.7,
+// 5.1 and 6.9 us by atomics, 8.5 and 10.5 through tiles; 300k 12-D points: 22.0, 5.6 and
+// 14.7 against 10.1 and 19.3; a batch of 64 events (5.6M points): 240, 34 and 217 against
+// 92 and 198, where k_tiles is bound by memory (1.1 GB at 5.4 TB/s: a line of points holds
+// the rows of several tiles and is fetched for each; giving each event's tiles to one XCD
+// took 235 us, the XCDs' shares being uneven).
+
+// Exclusive prefixes over the block in thread order of two values, and the block's totals
+// of both, for a block of WAVES waves, with one barrier (scratch belongs to this call).
+template <int WAVES>
+__device__ __forceinline__ uint2 block_prefix2(uint2 v, uint2 *scratch, uint2 &total) {
+    const uint2 inc = make_uint2(wave_inclusive_scan(v.x), wave_inclusive_scan(v.y));
+    if (lane_id() == 63) scratch[wave_id()] = inc;
+    __syncthreads();
+    uint2 before = make_uint2(0u, 0u), all = make_uint2(0u, 0u);
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint2 x = scratch[w];
+        before.x += w < wave_id() ? x.x : 0u;
+        before.y += w < wave_id() ? x.y : 0u;
+        all.x += x.x;
+        all.y += x.y;
+    }
+    total = all;
+    return make_uint2(before.x + inc.x - v.x, before.y + inc.y - v.y);
+}
+
+__device__ __forceinline__ int bin_shares(int n, int span) { return (n + span - 1) / span; }
+
+// Grid (shares, n_events): block (b, e) takes rows [b span, (b + 1) span) of event e.  It
+// writes each row's number and packed cell in the order of the rows' tiles to the same
+// range of ents, and where each tile starts in the share to row b of the event's table
+// (n_tiles + 1 entries, in the event's part of the histogram's memory).
+template <int kPer>
+__global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, float r, int cell_div,
+                                                    int tile_points, const EventDesc *__restrict__ ev, EventDesc ev0, int ev_from_arg,
+                                                    const BoundsPartial *__restrict__ part, int nparts,
+                                                    Plan *__restrict__ plans, Counters *__restrict__ ctr,
+                                                    uint2 *__restrict__ ents, unsigned short *__restrict__ table) {
+    __shared__ Plan P;
+    __shared__ unsigned int start[kBinMaxTiles];  // rows per tile, then where the tile starts
+    __shared__ uint2 scratch[kKeysBlock / 64];
+    const int e = blockIdx.y;
+    const EventDesc E = ev_from_arg ? ev0 : ev[e];
+    constexpr int kSpan = kKeysBlock * kPer;
+    if (blockIdx.x != 0 && static_cast<long long>(blockIdx.x) * kSpan >= E.n) return;
+    // The binned coordinates are loaded before the plan is derived so that the two
+    // latencies overlap.
+    float x[kPer][kMaxAxes];
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+#pragma unroll
+        for (int p = 0; p < kMaxAxes; ++p) x[m][p] = 0.0f;
+        if (i < E.n) {
+            const float *row = E.pts + static_cast<size_t>(i) * d;
+#pragma unroll
+            for (int p = 0; p < kMaxAxes; ++p)
+                if (p < axes) x[m][p] = row[dd.c[p]];
+        }
+    }
+    if (wave_id() == 0)
+        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points, &P);
+    for (int t = threadIdx.x; t < kBinMaxTiles; t += kKeysBlock) start[t] = 0u;
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        plans[e] = P;
+        if (P.abort) atomicOr(&ctr->abort, 1u);
+    }
+    if (P.abort) return;
+    const int n_tiles = P.n_tiles;
+    unsigned int tile[kPer], rank[kPer], pc[kPer];
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+        if (i >= E.n) continue;
+        int u[kMaxAxes];
+#pragma unroll
+        for (int p = 0; p < kMaxAxes; ++p) u[p] = cell_coord(x[m][p], P.lo[p], P.inv_c[p], P.G[p]);
+        pc[m] = pack_cell(u, axes);
+        tile[m] = cell_key(u, P) >> P.tile_shift;
+        rank[m] = atomicAdd(&start[tile[m]], 1u);
+    }
+    __syncthreads();
+    // Four consecutive tiles per thread.
+    static_assert(kBinMaxTiles == 4 * kKeysBlock, "four tiles per thread");
+    uint4 c = *reinterpret_cast<const uint4 *>(start + 4 * threadIdx.x);
+    uint2 all;
+    const unsigned int pre = block_prefix2<kKeysBlock / 64>(make_uint2(c.x + c.y + c.z + c.w, 0u), scratch, all).x;
+    c = make_uint4(pre, pre + c.x, pre + c.x + c.y, pre + c.x + c.y + c.z);
+    *reinterpret_cast<uint4 *>(start + 4 * threadIdx.x) = c;
+    __syncthreads();
+    unsigned short *row = table + 2 * E.cell0 + static_cast<size_t>(blockIdx.x) * (n_tiles + 1);
+    for (int t = threadIdx.x; t <= n_tiles; t += kKeysBlock)
+        row[t] = static_cast<unsigned short>(t < n_tiles ? start[t] : all.x);
+#pragma unroll
+    for (int m = 0; m < kPer; ++m) {
+        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+        if (i >= E.n) continue;
+        ents[E.row0 + static_cast<long long>(blockIdx.x) * kSpan + start[tile[m]] + rank[m]] =
+            make_uint2(static_cast<unsigned int>(i), pc[m]);
+    }
+}
+
+// Grid (tiles, n_events): block (t, e) finishes tile t of event e: its points' cells
+// counted in LDS, the cells' first sorted rows, the search's pieces that start in the
+// tile, then the rows themselves, copied into cell order and zero-padded to DP.
+//
+// The pieces are dealt to the tiles by rows (a tile of some hundred points has about the
+// same mix of cells as the next) and cut inside a tile by work: a cell weighs its points
+// plus kTileWeight if it has any.  Piece k ideally starts at row k rows / n_pieces; in
+// its tile it starts at the same share of the tile's weight, at the query that many
+// weight units past its cell's fixed cost (at the cell's first query if it falls within
+// the cost).
+template <int DP>
+__global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span, const EventDesc *__restrict__ ev,
+                                                       EventDesc ev0, int ev_from_arg,
+                                                       const Plan *__restrict__ plans,
+                                                       const Counters *__restrict__ ctr,
+                                                       const uint2 *__restrict__ ents,
+                                                       const unsigned short *__restrict__ table,
+                                                       unsigned int *__restrict__ cell_start,
+                                                       float *__restrict__ sorted,
+                                                       unsigned int *__restrict__ sorted_id,
+                                                       unsigned int *__restrict__ wave_start, int n_pieces,
+                                                       long long rows, unsigned int *__restrict__ claims) {
+    constexpr int kTWaves = kTilesBlock / 64;
+    constexpr int kCells = 1 << kTileShiftMax;
+    __shared__ __align__(16) unsigned int cursor[kCells];  // points per cell, then where the cell starts in the tile
+    __shared__ __align__(16) unsigned int weight[kCells];  // weight before the cell in the tile
+    __shared__ unsigned int seg_pre[kBinMaxShares];   // points of the tile in the shares before
+    __shared__ unsigned int seg_from[kBinMaxShares];  // where the share's points of the tile lie in ents
+    __shared__ uint2 scratch[2][kTWaves];
+    if (ctr->abort) return;
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        static_assert(8 * kPools <= kTilesBlock && kHugeCount < kPoolStride, "one claim line per thread");
+        if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
+        if (threadIdx.x < 8) {
+            *long_counter(claims, threadIdx.x, kLongCount) = 0u;
+            *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
+        }
+        if (threadIdx.x == 0) wave_start[n_pieces] = static_cast<unsigned int>(rows);
+    }
+    const EventDesc E = ev_from_arg ? ev0 : ev[blockIdx.y];
+    const Plan P = plans[blockIdx.y];
+    const int t = static_cast<int>(blockIdx.x);
+    if (t >= P.n_tiles || E.n == 0) return;
+    // The tile's segment of every share (one share per thread).
+    static_assert(kBinMaxShares == kTilesBlock, "one share per thread");
+    const int shares = bin_shares(E.n, span);
+    unsigned int from = 0, len = 0;
+    if (static_cast<int>(threadIdx.x) < shares) {
+        const unsigned short *row = table + 2 * E.cell0 + static_cast<size_t>(threadIdx.x) * (P.n_tiles + 1) + t;
+        from = row[0];
+        len = row[1] - from;
+    }
+    const unsigned int key0 = static_cast<unsigned int>(t) << P.tile_shift;  // the tile's first cell
+    const int cells = min(1 << P.tile_shift, P.n_cells - static_cast<int>(key0));
+    for (int c = threadIdx.x; c < cells; c += kTilesBlock) cursor[c] = 0u;
+    uint2 sums;  // the tile's points, and the points of the event's tiles before it
+    seg_pre[threadIdx.x] = block_prefix2<kTWaves>(make_uint2(len, from), scratch[0], sums).x;
+    seg_from[threadIdx.x] = threadIdx.x * static_cast<unsigned int>(span) + from;
+    const unsigned int n_tile = sums.x;
+    const unsigned int first_row = static_cast<unsigned int>(E.row0) + sums.y;
+    __syncthreads();
+    const uint2 *__restrict__ mine = ents + E.row0;
+    // The tile's q-th point: its row in the event, and its cell in the tile.
+    auto point = [&](unsigned int q, unsigned int &cell) {
+        int lo = 0, hi = shares - 1;  // the last share that starts at or before it
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (seg_pre[mid] <= q) lo = mid;
+            else hi = mid - 1;
+        }
+        const uint2 x = mine[seg_from[lo] + (q - seg_pre[lo])];
+        int u[kMaxAxes];
+        unpack_cell(x.y, P.axes, u);
+        cell = cell_key(u, P) - key0;
+        return x;
+    };
+    // A thread's first kHeld points stay in registers between the two passes.
+    constexpr int kHeld = 2;
+    uint2 held[kHeld];
+    unsigned int held_cell[kHeld];
+#pragma unroll
+    for (int m = 0; m < kHeld; ++m) {
+        const unsigned int q = m * kTilesBlock + threadIdx.x;
+        if (q < n_tile) {
+            held[m] = point(q, held_cell[m]);
+            atomicAdd(&cursor[held_cell[m]], 1u);
+        }
+    }
+    for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
+        unsigned int cell;
+        point(q, cell);
+        atomicAdd(&cursor[cell], 1u);
+    }
+    __syncthreads();
+    // Points and weight before each cell: consecutive cells per thread.
+    const int per = (cells + kTilesBlock - 1) / kTilesBlock;
+    const int c0 = min(static_cast<int>(threadIdx.x) * per, cells), c1 = min(c0 + per, cells);
+    uint2 run = make_uint2(0u, 0u);
+    for (int c = c0; c < c1; ++c) {
+        const unsigned int v = cursor[c];
+        run.x += v;
+        run.y += v + (v ? kTileWeight : 0u);
+    }
+    uint2 all;
+    run = block_prefix2<kTWaves>(run, scratch[1], all);
+    for (int c = c0; c < c1; ++c) {
+        const unsigned int v = cursor[c];
+        cursor[c] = run.x;
+        weight[c] = run.y;
+        run.x += v;
+        run.y += v + (v ? kTileWeight : 0u);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < cells; c += kTilesBlock) cell_start[E.cell0 + key0 + c] = first_row + cursor[c];
+    if (t == P.n_tiles - 1 && threadIdx.x == 0)
+        cell_start[E.cell0 + P.n_cells] = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
+    if (n_tile) {
+        // Pieces k with first_row <= k rows / n_pieces < first_row + n_tile.
+        const unsigned long long np = static_cast<unsigned long long>(n_pieces);
+        const unsigned long long R = static_cast<unsigned long long>(rows);
+        const unsigned long long w_tile = all.y;
+        const unsigned long long k0 = floor_div(first_row * np + R - 1, R);
+        const unsigned long long k1 = floor_div((first_row + static_cast<unsigned long long>(n_tile)) * np + R - 1, R);
+        for (unsigned long long k = k0 + threadIdx.x; k < k1; k += kTilesBlock) {
+            // Share of the tile before the piece's ideal start, of its weight.
+            const unsigned long long past_rows = floor_div(k * R, np) - first_row;
+            const unsigned int at = static_cast<unsigned int>(floor_div(past_rows * w_tile, n_tile));
+            int lo = 0, hi = cells - 1;  // the last cell that starts at or before it
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (weight[mid] <= at) lo = mid;
+                else hi = mid - 1;
+            }
+            const unsigned int past = at - weight[lo];
+            wave_start[k] = first_row + cursor[lo] + (past > kTileWeight ? past - kTileWeight : 0u);
+        }
+    }
+    __syncthreads();
+    // The rows, each to the next place of its cell.
+    auto place = [&](uint2 x, unsigned int cell) {
+        float row[DP];
+        if (vec4) {
+            const float4 *src = reinterpret_cast<const float4 *>(E.pts + static_cast<size_t>(x.x) * d);
+#pragma unroll
+            for (int k = 0; k < DP / 4; ++k) {
+                float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (4 * k < d) w = src[k];
+                row[4 * k] = w.x;
+                row[4 * k + 1] = w.y;
+                row[4 * k + 2] = w.z;
+                row[4 * k + 3] = w.w;
+            }
+        } else {
+            const float *src = E.pts + static_cast<size_t>(x.x) * d;
+#pragma unroll
+            for (int k = 0; k < DP; ++k) row[k] = k < d ? src[k] : 0.0f;
+        }
+        const unsigned int slot = first_row + atomicAdd(&cursor[cell], 1u);
+        float4 *out = reinterpret_cast<float4 *>(sorted + static_cast<size_t>(slot) * DP);
+#pragma unroll
+        for (int k = 0; k < DP / 4; ++k)
+            out[k] = make_float4(row[4 * k], row[4 * k + 1], row[4 * k + 2], row[4 * k + 3]);
+        reinterpret_cast<uint2 *>(sorted_id)[slot] =
+            make_uint2(static_cast<unsigned int>(E.row0) + x.x, x.y);
+    };
+#pragma unroll
+    for (int m = 0; m < kHeld; ++m)
+        if (m * kTilesBlock + threadIdx.x < n_tile) place(held[m], held_cell[m]);
+    for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
+        unsigned int cell;
+        const uint2 x = point(q, cell);
+        place(x, cell);
     }
 }
 
@@ -2098,6 +2432,11 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     }
 }
 
+// The binning through tiles works in memory of the other one: the entries where packed
+// cells and ranks lie (next to each other), the tables in the histogram.
+uint2 *bin_ents(const Workspace &ws) { return reinterpret_cast<uint2 *>(ws.pcell); }
+unsigned short *bin_table(const Workspace &ws) { return reinterpret_cast<unsigned short *>(ws.cell_count); }
+
 // Launches the stages whose kernels depend on the padded row width.
 template <int DP>
 void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
@@ -2107,9 +2446,15 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const long long rows = ws.rows;
     const long long nb = (static_cast<long long>(a.max_n) + kBlock - 1) / kBlock;
     const int gs = static_cast<int>(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
-    hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
-                       a.ev_from_arg, ws.plans,
-                       ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, ws.sorted_id);
+    if (a.bin_span)
+        hipLaunchKernelGGL(k_tiles<DP>, dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events), dim3(kTilesBlock),
+                           0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0, a.ev_from_arg, ws.plans, ws.ctr,
+                           bin_ents(ws), bin_table(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
+                           a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
+    else
+        hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
+                           a.ev_from_arg, ws.plans,
+                           ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, ws.sorted_id);
     mark(4);
     SearchCounts *counts = reinterpret_cast<SearchCounts *>(ws.rank);
     if (a.K < kListCap)
@@ -2168,29 +2513,39 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
         if (a.events) (void)hipEventRecord(a.events[stage], a.stream);
     };
     const int vec4 = a.vec4;
-    const int keys_per = a.max_n > kKeysTwoFrom ? 2 : 1;  // points per thread
-    const long long kb = (static_cast<long long>(a.max_n) + kKeysBlock * keys_per - 1) / (kKeysBlock * keys_per);
+    const long long kb = (static_cast<long long>(a.max_n) + kKeysSpan - 1) / kKeysSpan;
     const int gkeys = static_cast<int>(kb < 1 ? 1 : kb);
     Dims dd;
     for (int p = 0; p < kMaxAxes; ++p) dd.c[p] = p < a.axes ? a.dims[p] : -1;
     mark(0);
+    // The histogram and its tile totals are cleared for the binning by atomics alone.
     hipLaunchKernelGGL(k_bounds, dim3(a.bounds_blocks, a.n_events), dim3(kBlock), 0, a.stream, a.d, dd, vec4,
-                       ws.ev, a.ev0, a.ev_from_arg, ws.part, ws.cell_count, ws.cells, ws.sums_cells,
-                       ws.tiles_cells_n, ws.ctr);
+                       ws.ev, a.ev0, a.ev_from_arg, ws.part, ws.cell_count, a.bin_span ? 0ll : ws.cells,
+                       ws.sums_cells, a.bin_span ? 0 : ws.tiles_cells_n, ws.ctr);
     mark(1);
-    if (keys_per == 2)
-        hipLaunchKernelGGL(k_keys<2>, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
-                           a.r, a.cell_div, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+    if (a.bin_span) {
+        const dim3 grid(static_cast<unsigned int>(a.max_n < 1 ? 1 : (a.max_n + a.bin_span - 1) / a.bin_span),
+                        a.n_events);
+        if (a.bin_span == kKeysBlock)
+            hipLaunchKernelGGL(k_bin<1>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
+                               ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+                               bin_ents(ws), bin_table(ws));
+        else
+            hipLaunchKernelGGL(k_bin<2>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
+                               ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+                               bin_ents(ws), bin_table(ws));
+        mark(2);
+        mark(3);
+    } else {
+        hipLaunchKernelGGL(k_keys, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
+                           a.r, a.cell_div, a.tile_points, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
                            ws.pcell, ws.rank, ws.cell_count, ws.sums_cells);
-    else
-        hipLaunchKernelGGL(k_keys<1>, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
-                           a.r, a.cell_div, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
-                           ws.pcell, ws.rank, ws.cell_count, ws.sums_cells);
-    mark(2);
-    hipLaunchKernelGGL(k_scan_cells, dim3(ws.tiles_cells_n), dim3(kBlock), 0, a.stream, ws.cell_count, ws.cells,
-                       ws.sums_cells, ws.tiles_cells_n, ws.cell_start, ws.wave_start,
-                       a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
-    mark(3);
+        mark(2);
+        hipLaunchKernelGGL(k_scan_cells, dim3(ws.tiles_cells_n), dim3(kBlock), 0, a.stream, ws.cell_count, ws.cells,
+                           ws.sums_cells, ws.tiles_cells_n, ws.cell_start, ws.wave_start,
+                           a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
+        mark(3);
+    }
     switch (a.dpad) {
         case 4: launch_rows<4>(a, ws, vec4); break;
         case 8: launch_rows<8>(a, ws, vec4); break;
