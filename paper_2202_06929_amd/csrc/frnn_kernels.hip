@@ -69,20 +69,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // product and sum rounded on its own.  Rows are zero-padded; adding +0 leaves a
 // sum unchanged, so padded rows give the same D as unpadded ones.  Partial sums of
 // non-negative terms never decrease, so s >= r2 after a prefix rejects exactly.
-template <int K0, int K1, int DP>
-__device__ __forceinline__ float add_terms(float s, const float (&a)[DP], const float *__restrict__ b) {
-#pragma unroll
-    for (int k = K0; k < K1; ++k) {
-        const float t = a[k] - b[k];
-        const float t2 = t * t;
-        s = s + t2;
-    }
-    return s;
-}
-
-// The same partial sum with the second row held in registers.
 template <int K0, int K1, int DP, int NB>
-__device__ __forceinline__ float add_terms_r(float s, const float (&a)[DP], const float (&b)[NB]) {
+__device__ __forceinline__ float add_terms(float s, const float (&a)[DP], const float (&b)[NB]) {
 #pragma unroll
     for (int k = K0; k < K1; ++k) {
         const float t = a[k] - b[k];
@@ -93,23 +81,61 @@ __device__ __forceinline__ float add_terms_r(float s, const float (&a)[DP], cons
 }
 
 template <int DP>
-__device__ __forceinline__ float sq_dist(const float (&a)[DP], const float *__restrict__ b) {
-    return add_terms<0, DP, DP>(0.0f, a, b);
+__device__ __forceinline__ float sq_dist(const float (&a)[DP], const float (&b)[DP]) {
+    return add_terms<0, DP, DP, DP>(0.0f, a, b);
 }
 
-// Row `s` of the zero-padded sorted points (DP is a multiple of 4, rows 16-byte aligned).
+// Terms before the first exact rejection test of the search: two for rows of up to 12
+// floats (a three-term test rejects few more pairs than two terms do, and the first
+// stage runs for every query and candidate; on the 300k-point 12-D event two, three and
+// four terms took 87.5, 88.7 and 89.6 us), three for rows of 16 and 24 floats, four for
+// wider ones (two terms took whole 120k-point builds with 32-, 48- and 64-float rows from
+// 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
+constexpr int search_lead(int dpad) { return dpad <= 12 ? 2 : (dpad < 32 ? 3 : 4); }
+
+// The sorted points, zero-padded to DP coordinates (a multiple of 4).  Rows of 32 floats
+// and more lie in two parts: the leading coordinates of all rows, which the search's first
+// stage reads for every candidate, side by side (16 bytes a row instead of one line each),
+// then the rest of each row (60k points of 32, 48 and 64 coordinates: whole builds 95, 88.7
+// and 121.7 us with whole rows, 88, 85.7 and 109.5 with split ones; of 16 and 24 equal, of
+// 8 to 12 1 to 3% slower, as the second stage's loads then cross lines).
 template <int DP>
-__device__ __forceinline__ void load_row(const float *__restrict__ sorted, unsigned int s, float (&c)[DP]) {
-    const float4 *row = reinterpret_cast<const float4 *>(sorted + static_cast<size_t>(s) * DP);
-#pragma unroll
-    for (int k = 0; k < DP / 4; ++k) {
-        const float4 v = row[k];
-        c[4 * k] = v.x;
-        c[4 * k + 1] = v.y;
-        c[4 * k + 2] = v.z;
-        c[4 * k + 3] = v.w;
+struct SortedRows {
+    static constexpr bool kSplit = DP >= 32;
+    static constexpr int kLead = search_lead(DP);
+    static constexpr int kTail = DP - kLead;
+    static constexpr int kLeadStride = kSplit ? kLead : DP;
+    static constexpr int kTailStride = kSplit ? kTail : DP;
+    const float *__restrict__ lead;
+    const float *__restrict__ tail;
+    static __device__ __forceinline__ size_t tail_at(long long rows) {
+        return kSplit ? static_cast<size_t>(rows) * kLead : static_cast<size_t>(kLead);
     }
-}
+    __device__ __forceinline__ SortedRows(const float *__restrict__ sorted, long long rows)
+        : lead(sorted), tail(sorted + tail_at(rows)) {}
+    __device__ __forceinline__ const float *lead_of(unsigned int s) const {
+        return lead + static_cast<size_t>(s) * kLeadStride;
+    }
+    __device__ __forceinline__ const float *tail_of(unsigned int s) const {
+        return tail + static_cast<size_t>(s) * kTailStride;
+    }
+    __device__ __forceinline__ void load(unsigned int s, float (&c)[DP]) const {
+        const float *a = lead_of(s), *b = tail_of(s);
+#pragma unroll
+        for (int k = 0; k < kLead; ++k) c[k] = a[k];
+#pragma unroll
+        for (int k = kLead; k < DP; ++k) c[k] = b[k - kLead];
+    }
+    static __device__ __forceinline__ void store(float *__restrict__ sorted, long long rows, unsigned int s,
+                                                 const float (&c)[DP]) {
+        float *a = sorted + static_cast<size_t>(s) * kLeadStride;
+        float *b = sorted + tail_at(rows) + static_cast<size_t>(s) * kTailStride;
+#pragma unroll
+        for (int k = 0; k < kLead; ++k) a[k] = c[k];
+#pragma unroll
+        for (int k = kLead; k < DP; ++k) b[k - kLead] = c[k];
+    }
+};
 
 // Cross-lane steps with DPP (GFX9 encodings): row_shr:n moves lane i - n of the
 // same 16-lane row into lane i (0 when that lane is in another row); row_bcast:15
@@ -795,7 +821,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int d, int vec4, const Event
                                                     const unsigned int *__restrict__ rank,
                                                     const unsigned int *__restrict__ cell_start,
                                                     const Counters *__restrict__ ctr,
-                                                    float *__restrict__ sorted,
+                                                    float *__restrict__ sorted, long long rows,
                                                     unsigned int *__restrict__ sorted_id) {
     // The point's packed cell, rank and row are requested before the abort flag is
     // known (they are in bounds whatever it says); the cell start, whose index needs
@@ -828,10 +854,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int d, int vec4, const Event
         int u[kMaxAxes];
         unpack_cell(pc, P.axes, u);
         const unsigned int slot = cell_start[static_cast<unsigned int>(E.cell0) + cell_key(u, P)] + rk;
-        float4 *out = reinterpret_cast<float4 *>(sorted + static_cast<size_t>(slot) * DP);
-#pragma unroll
-        for (int k = 0; k < DP / 4; ++k)
-            out[k] = make_float4(row[4 * k], row[4 * k + 1], row[4 * k + 2], row[4 * k + 3]);
+        SortedRows<DP>::store(sorted, rows, slot, row);
         // The original row and the packed cell of a sorted row sit side by side, so
         // the scattered write is one 8-byte store instead of two 4-byte ones.
         reinterpret_cast<uint2 *>(sorted_id)[slot] = make_uint2(static_cast<unsigned int>(gi), pc);
@@ -1108,10 +1131,7 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
             for (int k = 0; k < DP; ++k) row[k] = k < d ? src[k] : 0.0f;
         }
         const unsigned int slot = first_row + atomicAdd(&cursor[cell], 1u);
-        float4 *out = reinterpret_cast<float4 *>(sorted + static_cast<size_t>(slot) * DP);
-#pragma unroll
-        for (int k = 0; k < DP / 4; ++k)
-            out[k] = make_float4(row[4 * k], row[4 * k + 1], row[4 * k + 2], row[4 * k + 3]);
+        SortedRows<DP>::store(sorted, rows, slot, row);
         reinterpret_cast<uint2 *>(sorted_id)[slot] =
             make_uint2(static_cast<unsigned int>(E.row0) + x.x, x.y);
     };
@@ -1268,18 +1288,10 @@ struct RunMap {
 template <int DP>
 constexpr int kSearchWaves = DP <= 16 ? 8 : (DP == 48 ? 4 : 1);
 
-// Terms before the first exact rejection test: two for rows of up to 12 floats
-// (a three-term test rejects few more pairs than two terms do, and the first
-// stage runs for every query and candidate; on the 300k-point 12-D event two,
-// three and four terms took 87.5, 88.7 and 89.6 us), three for wider rows (two
-// terms took whole 120k-point builds with 32-, 48- and 64-float rows from
-// 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
-constexpr int search_lead(int dpad) { return dpad <= 12 ? 2 : 3; }
-
 // SEL: the cap K is below kListCap, so a list that fits may still need the K
 // nearest of its hits: the lists then also hold each hit's distance.
 template <int DP, bool SEL>
-__global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float *__restrict__ sorted,
+__global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float *__restrict__ sorted, long long rows,
                                                    const unsigned int *__restrict__ sorted_id,
                                                    const unsigned int *__restrict__ wave_start,
                                                    unsigned int *__restrict__ claims,
@@ -1301,6 +1313,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     __shared__ unsigned int cnt_all[SEL ? kWaves : 1][SEL ? kQT : 1];
     __shared__ unsigned int qcnt_all[kWaves][kQT];  // hits of each query of the batch
     constexpr int kLead = search_lead(DP);
+    const SortedRows<DP> pts(sorted, rows);
     // Coordinates kLead.. of the batch's queries, read by the second stage, for rows
     // wide enough that registers, not LDS, bound the waves per SIMD (32-float rows:
     // 29.1 us against 31.6 with the query rows loaded per entry; for 12-float rows the
@@ -1396,20 +1409,20 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         const float a3 = act ? racc[e] : 0.0f;
         const unsigned int q = static_cast<unsigned int>(ent >> 32);
         const unsigned int s2 = static_cast<unsigned int>(ent);
-        const float *crow = sorted + static_cast<size_t>(s2) * DP;
+        const float *crow = pts.tail_of(s2);
         float cc[DP], qq[DP];
 #pragma unroll
-        for (int k = kLead; k < DP; ++k) cc[k] = crow[k];
+        for (int k = kLead; k < DP; ++k) cc[k] = crow[k - kLead];
         if (kTailLds) {
 #pragma unroll
             for (int k = kLead; k < DP; ++k) qq[k] = qtail[q * kTail + (k - kLead)];
         } else {
-            const float *qrow = sorted + static_cast<size_t>(win + q) * DP;
+            const float *qrow = pts.tail_of(win + q);
 #pragma unroll
-            for (int k = kLead; k < DP; ++k) qq[k] = qrow[k];
+            for (int k = kLead; k < DP; ++k) qq[k] = qrow[k - kLead];
         }
         unsigned int j2 = sorted_id[2u * static_cast<size_t>(s2)];
-        const float D = add_terms_r<kLead, DP, DP, DP>(a3, cc, qq);
+        const float D = add_terms<kLead, DP, DP, DP>(a3, cc, qq);
         // The id is requested with the rows, not (as the compiler would have it) in a
         // round trip of its own once a pair has passed.
         asm volatile("" : "+v"(j2));
@@ -1484,30 +1497,25 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // The queries [q0, q1) of the batch, which share a cell, against the cell's M
     // candidates.
     auto search_cell = [&](unsigned int q0, unsigned int q1, unsigned int M) {
-        // Candidates are fetched one chunk ahead so that their latency overlaps
-        // the tests of the current chunk: each lane holds its candidate's first
-        // four coordinates (one 16-byte load).  Idle lanes read row 0 (any row
-        // is a valid address) and are masked out of every ballot.
-        // The values are masked where they are used, not here, so that nothing
+        // Candidates are fetched one chunk ahead so that their latency overlaps the
+        // tests of the current chunk: each lane holds its candidate's leading
+        // coordinates.  Idle lanes read row 0 (any row is a valid address) and are masked
+        // out of every ballot, where the values are used and not here, so that nothing
         // waits for the load before the tests of the current chunk.
-        constexpr int kHeld = 4;  // candidate coordinates held per lane
-        static_assert(kLead <= kHeld, "the first stage uses the held coordinates");
-        float cn[kHeld];
+        float cn[kLead];
         unsigned int sn;
         auto fetch = [&](unsigned int b) {
             const unsigned int srow = map.row(b);
             sn = b + lane < M ? srow : 0u;
-            const float4 v = *reinterpret_cast<const float4 *>(sorted + static_cast<size_t>(sn) * DP);
-            cn[0] = v.x;
-            cn[1] = v.y;
-            cn[2] = v.z;
-            cn[3] = v.w;
+            const float *v = pts.lead_of(sn);
+#pragma unroll
+            for (int k = 0; k < kLead; ++k) cn[k] = v[k];
         };
         fetch(0u);
         for (unsigned int base = 0; base < M; base += 64) {
-            float c[kHeld];
+            float c[kLead];
 #pragma unroll
-            for (int k = 0; k < kHeld; ++k) c[k] = cn[k];
+            for (int k = 0; k < kLead; ++k) c[k] = cn[k];
             const unsigned int s = sn;
             // Lanes past the last candidate fail every first-stage test.
             if (base + lane >= M) c[0] = INFINITY;
@@ -1522,7 +1530,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                     qc[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lead[k]), q));
                 // First stage: kLead terms for all 64 candidates; pairs that are not
                 // yet at r2 are queued (exact: the remaining terms only add).
-                const float acc = add_terms_r<0, kLead, kHeld, kLead>(0.0f, c, qc);
+                const float acc = add_terms<0, kLead, kLead, kLead>(0.0f, c, qc);
                 const unsigned long long m1 = __builtin_amdgcn_ballot_w64(acc < r2);
                 if (m1 == 0ull) continue;
                 if (acc < r2) {
@@ -1557,7 +1565,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                 next = sid[row];
                 if (kLeadAhead) {
 #pragma unroll
-                    for (int k = 0; k < kLead; ++k) next_lead[k] = sorted[static_cast<size_t>(row) * DP + k];
+                    for (int k = 0; k < kLead; ++k) next_lead[k] = pts.lead_of(row)[k];
                 }
             }
         };
@@ -1576,7 +1584,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
 #pragma unroll
             for (int k = 0; k < kLead; ++k)
                 lead[k] = kLeadAhead ? next_lead[k]
-                                     : sorted[static_cast<size_t>(min(win + lane, q_hi - 1u)) * DP + k];
+                                     : pts.lead_of(min(win + lane, q_hi - 1u))[k];
             // The lanes that start a cell, and the batch's end: after its last whole cell
             // (a batch never crosses into the next event).
             const unsigned int n = min(min(64u, q_hi - win), ev_end - win);
@@ -1608,7 +1616,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
             if (lane < kQT) qcnt[lane] = 0u;
             if (kTailLds)
                 for (unsigned int k = lane; k < nq * kTail; k += 64u)
-                    qtail[k] = sorted[static_cast<size_t>(win + k / kTail) * DP + kLead + k % kTail];
+                    qtail[k] = pts.tail_of(win + k / kTail)[k % kTail];
             // End of the cell that query t of the batch lies in.
             auto cell_end = [&](unsigned int t) {
                 const unsigned long long rest = t < 63u ? starts >> (t + 1u) : 0ull;
@@ -1785,7 +1793,7 @@ constexpr unsigned int kKeyCap = kPlaceWords / 2;
 // candidates again.  The kept ids are sorted by a bitonic network in LDS and
 // written, local to the query's event, to out[0, n_out).
 template <int DP>
-__device__ void long_list(const float *__restrict__ sorted, const unsigned int *__restrict__ sorted_id,
+__device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restrict__ sorted_id,
                           const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
                           unsigned int slot, float r2, unsigned int n_out, long long row0,
                           long long *__restrict__ out, unsigned int *__restrict__ wbuf,
@@ -1793,7 +1801,8 @@ __device__ void long_list(const float *__restrict__ sorted, const unsigned int *
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(wbuf);  // [kKeyCap]
     unsigned int *ids = wbuf;                                                  // [kMaxK], after the keys are read
     const int nruns = run_count(P);
-    for (int k = threadIdx.x; k < DP; k += kPlaceBlock) L.qv[k] = sorted[static_cast<size_t>(slot) * DP + k];
+    for (int k = threadIdx.x; k < DP; k += kPlaceBlock)
+        L.qv[k] = k < pts.kLead ? pts.lead_of(slot)[k] : pts.tail_of(slot)[k - pts.kLead];
     if (wave_id() == 0) {
         unsigned int start, pre, end;
         const RunLane rl = run_lane(P, false);
@@ -1823,7 +1832,7 @@ __device__ void long_list(const float *__restrict__ sorted, const unsigned int *
         }
         const unsigned int s = L.run_start[lo] + (m - L.run_pre[lo]);
         float c[DP];
-        load_row<DP>(sorted, s, c);
+        pts.load(s, c);
         const float D = sq_dist<DP>(c, q);
         ok = (D < r2) && (s != slot);
         return (static_cast<unsigned long long>(__float_as_uint(D)) << 32) | sorted_id[2u * s];
@@ -2075,7 +2084,7 @@ __device__ __forceinline__ void wave_select(const unsigned int *dist, unsigned i
 // against 1,024 and 4,096 (four workgroups) took the placement of a batch of 5.6M
 // points with 148,000 long lists from 560 to 458 us.
 template <int DP>
-__device__ __forceinline__ void wave_list(const float *__restrict__ sorted, const unsigned int *__restrict__ sorted_id,
+__device__ __forceinline__ void wave_list(const SortedRows<DP> &pts, const unsigned int *__restrict__ sorted_id,
                           const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
                           unsigned int slot, unsigned int pc, float r2, unsigned int n_out, long long row0,
                           long long *__restrict__ out, unsigned int *dist, unsigned int *ids, RunMap &map) {
@@ -2084,7 +2093,8 @@ __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, cons
     const RunLane rl = run_lane(P, false);
     wave_runs(pc, cell0, P, rl, rl.live, false, cell_start, start, pre, end);
     const unsigned int M = lane63(end);
-    const float *qrow = sorted + static_cast<size_t>(slot) * DP;
+    float qrow[DP];  // wave-uniform
+    pts.load(slot, qrow);
     unsigned int h = 0;
     map.keep(start, pre, end);
     map.begin(true, pre, end, 0u);
@@ -2094,7 +2104,7 @@ __device__ __forceinline__ void wave_list(const float *__restrict__ sorted, cons
         const unsigned int s = mm < M ? srow : slot;
         const unsigned int j = sorted_id[2u * static_cast<size_t>(s)];
         float c[DP];
-        load_row<DP>(sorted, s, c);
+        pts.load(s, c);
         const float D = sq_dist<DP>(c, qrow);
         const bool hit = D < r2 && s != slot;
         const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
@@ -2175,6 +2185,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     __shared__ LongLds<DP> L;
     __shared__ unsigned int map_all[kWaves][128];  // RunMap of each wave
     __shared__ unsigned int q_first[8], q_last[8], q_wave[9], q_huge[9];
+    const SortedRows<DP> pts(sorted, rows);
     const bool abort = ctr->abort != 0;
     const int b = static_cast<int>(blockIdx.x);
     const bool tile_block = b < tiles_kept;
@@ -2403,7 +2414,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
             }
             at = wave_sum(at);
             if (at + nq > cap) continue;  // cannot happen when E <= cap
-            wave_list<DP>(sorted, sorted_id, cell_start, P, cell0, slot, uniform(id.y), r2, nq, ev_lo, dst + at, lds,
+            wave_list<DP>(pts, sorted_id, cell_start, P, cell0, slot, uniform(id.y), r2, nq, ev_lo, dst + at, lds,
                           lds + kWaveKeys, map);
         }
     }
@@ -2427,7 +2438,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         if (at + nq > cap) continue;  // cannot happen when E <= cap
         const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
         const Plan P = plans[e];
-        long_list<DP>(sorted, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot, r2, nq,
+        long_list<DP>(pts, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot, r2, nq,
                       ev[e].row0, dst + at, wbuf, scratch, L);
     }
 }
@@ -2454,15 +2465,15 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     else
         hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
                            a.ev_from_arg, ws.plans,
-                           ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, ws.sorted_id);
+                           ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, rows, ws.sorted_id);
     mark(4);
     SearchCounts *counts = reinterpret_cast<SearchCounts *>(ws.rank);
     if (a.K < kListCap)
-        hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
+        hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
                            a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
     else
-        hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted,
+        hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
                            a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
     mark(5);
