@@ -101,6 +101,21 @@ constexpr int kMaxEvents = 65535;  // events per call (the second grid dimension
 // neighbours, or more than K without the search's own selection), which the
 // placement pass collects again; other lists sit at kListCap slots per original row.
 constexpr unsigned int kKeptLong = 1u << 31;
+// With this bit the list has kListCap + 1 to kExtCap entries: the low bits hold the count,
+// the bits between the number of its block of kListCap entries in the extension, where the
+// entries past its first kListCap lie.  The search keeps up to search_spill(DP) such
+// entries of a batch of queries (fewer where LDS would cost 48-float rows a workgroup).
+// A few percent of the queries of an ordinary event have such lists; collected again one
+// per wave they took the placement of a batch of 64 events (148,000 of 5.6M queries) to
+// 457 us, against 254 from the extension, of a 120k-point event to 14.8 against 12.4 and
+// of a 60k-point 32-D event to 16.1 against 11.6.  Denser graphs, whose spilled hits
+// overflow, lose 1 to 2%.
+constexpr unsigned int kKeptExt = 1u << 30;
+constexpr int kKeptExtBits = 6;
+constexpr unsigned int kKeptExtCount = (1u << kKeptExtBits) - 1u;
+constexpr int kExtCap = 32;
+constexpr int search_spill(int dpad) { return dpad == 48 ? 32 : 64; }
+constexpr long long kExtBlocksMax = 1 << (30 - kKeptExtBits);
 
 // One event of a call: its rows in the concatenated points and its share of the
 // cell-key space.  The first event starts at row 0 and cell 0.
@@ -183,14 +198,15 @@ struct Workspace {
     long long *edge_off;        // [n_events + 2] first edge of each event, then E, then a status
     unsigned int *pcell;        // [rows] packed cell coordinates of each point
     unsigned int *rank;         // [rows] arrival rank inside its cell; after the scatter, the search's SearchCounts
-    unsigned int *cell_count;   // [cells] histogram
+    unsigned int *cell_count;   // [cells] histogram or the tile binning's tables; in the search, the extension
     unsigned int *cell_start;   // [cells + 1] exclusive scan of the histogram
     unsigned long long *sums_cells;  // [tiles of cells + 1] per-tile histogram totals
     unsigned long long *sums_kept;   // [tiles of kPlaceTile rows] kept neighbours before the tile in its group
     unsigned long long *sums_kept2;  // [groups of kKeptGroup tiles] per-group kept totals
     float *sorted;              // [rows, dpad] points in cell order, zero-padded rows
     unsigned int *sorted_id;    // [2 rows] per sorted row: its original row, then its packed cell
-    unsigned int *kept;         // [rows] neighbours kept per original row (| kKeptLong for a long list)
+    unsigned int *kept;         // [rows] kept word per original row: the neighbours kept (| kKeptLong for a long
+                                // list), or kKeptExt, the list's block of the extension and the count
     unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists, queued per XCD in the part
                                 // of the XCD's rows
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries

@@ -36,6 +36,8 @@
 
 #include <float.h>
 
+#include <algorithm>
+
 #include "frnn_internal.h"
 
 #pragma clang fp contract(off)
@@ -49,6 +51,10 @@ __device__ __forceinline__ unsigned int prefix_count(unsigned long long mask) {
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+// Neighbours kept, from a query's kept word.
+__device__ __forceinline__ unsigned int kept_count(unsigned int w) {
+    return w & ((w & kKeptExt) != 0u ? kKeptExtCount : ~kKeptLong);
+}
 // Wave index inside the workgroup, marked wave-uniform for the compiler (so that
 // values derived from it live in scalar registers and feed scalar loads).
 __device__ __forceinline__ int wave_id() {
@@ -643,7 +649,7 @@ __device__ __forceinline__ unsigned int xcd_first_block(unsigned int x, unsigned
 // out: 87 us against 30 for 60,000 points with some 45 neighbours each, 45 against 22
 // for 20,000 in denser ones, 32.4 against 27.5 for a 120k-point event where 2% of the
 // lists are long.
-constexpr int kLongCount = 1, kHugeCount = 2;  // words of an XCD's first claim line
+constexpr int kLongCount = 1, kHugeCount = 2, kExtCount = 3;  // words of an XCD's first claim line
 __device__ __forceinline__ unsigned int *long_counter(unsigned int *claims, unsigned int xcd, int which) {
     return claims + xcd * kPools * kPoolStride + which;
 }
@@ -795,11 +801,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__res
         }
     }
     if (blockIdx.x == 0) {
-        static_assert(8 * kPools <= kBlock && kHugeCount < kPoolStride, "one claim line per thread");
+        static_assert(8 * kPools <= kBlock && kExtCount < kPoolStride, "one claim line per thread");
         if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
         if (threadIdx.x < 8) {
             *long_counter(claims, threadIdx.x, kLongCount) = 0u;
             *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
+            *long_counter(claims, threadIdx.x, kExtCount) = 0u;
         }
         if (W == 0) {  // no rows: every share is empty
             for (int t = threadIdx.x; t <= n_waves; t += kBlock) wave_start[t] = 0u;
@@ -1004,11 +1011,12 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     __shared__ uint2 scratch[2][kTWaves];
     if (ctr->abort) return;
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        static_assert(8 * kPools <= kTilesBlock && kHugeCount < kPoolStride, "one claim line per thread");
+        static_assert(8 * kPools <= kTilesBlock && kExtCount < kPoolStride, "one claim line per thread");
         if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
         if (threadIdx.x < 8) {
             *long_counter(claims, threadIdx.x, kLongCount) = 0u;
             *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
+            *long_counter(claims, threadIdx.x, kExtCount) = 0u;
         }
         if (threadIdx.x == 0) wave_start[n_pieces] = static_cast<unsigned int>(rows);
     }
@@ -1301,6 +1309,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                                                    unsigned int *__restrict__ kept,
                                                    unsigned int *__restrict__ temp,
                                                    unsigned int *__restrict__ long_slots,
+                                                   unsigned int *__restrict__ extension, unsigned int ext_cap,
                                                    Counters *__restrict__ ctr,
                                                    SearchCounts *__restrict__ counts, int prio) {
     // Queries per batch: 16 when the lists also hold distances (their LDS would
@@ -1312,6 +1321,11 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     __shared__ unsigned int pre_all[SEL ? kWaves : 1][SEL ? kQT : 1];
     __shared__ unsigned int cnt_all[SEL ? kWaves : 1][SEL ? kQT : 1];
     __shared__ unsigned int qcnt_all[kWaves][kQT];  // hits of each query of the batch
+    // Hits 16 .. 31 of the batch's queries: query << 8 | number, and the neighbour.
+    constexpr bool kSpill = !SEL;
+    constexpr int kSpillCap = search_spill(DP);
+    static_assert(kSpillCap <= 64, "a lane per spilled hit");
+    __shared__ uint2 spill_all[kSpill ? kWaves : 1][kSpill ? kSpillCap : 1];
     constexpr int kLead = search_lead(DP);
     const SortedRows<DP> pts(sorted, rows);
     // Coordinates kLead.. of the batch's queries, read by the second stage, for rows
@@ -1337,6 +1351,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     unsigned int *tpre = pre_all[SEL ? wave_id() : 0];
     unsigned int *tcnt = cnt_all[SEL ? wave_id() : 0];
     unsigned int *qcnt = qcnt_all[wave_id()];
+    uint2 *spill = spill_all[kSpill ? wave_id() : 0];
     float *qtail = tail_all[kTailLds ? wave_id() : 0];
     unsigned long long *ring = ring_all[wave_id()];
     float *racc = racc_all[wave_id()];
@@ -1385,13 +1400,25 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // written out together.
     unsigned int win = 0;             // sorted row of the batch's first query
     unsigned int head = 0, tail = 0;  // queued survivors [head, tail)
-    // A pair that passes the full test joins the list of query q of the batch.
+    unsigned int n_spilled = 0;       // hits kListCap .. kExtCap - 1 found in the batch (wave-uniform)
+    // A pair that passes the full test joins the list of query q of the batch.  Call with
+    // the whole wave active.
     auto keep = [&](bool pass, unsigned int q, unsigned int j, float D) {
+        unsigned int pos = 0xffffffffu;
         if (pass) {
-            const unsigned int pos = atomicAdd(&qcnt[q], 1u);
+            pos = atomicAdd(&qcnt[q], 1u);
             if (pos < static_cast<unsigned int>(kListCap)) {
                 lst[q * kListCap + pos] = j;
                 if (SEL) lstd[q * kListCap + pos] = __float_as_uint(D);
+            }
+        }
+        if (kSpill) {
+            const bool over = pos - static_cast<unsigned int>(kListCap) < static_cast<unsigned int>(kExtCap - kListCap);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(over);
+            if (m != 0ull) {
+                const unsigned int e = n_spilled + prefix_count(m);
+                if (over && e < static_cast<unsigned int>(kSpillCap)) spill[e] = make_uint2(q << 8 | pos, j);
+                n_spilled += static_cast<unsigned int>(__popcll(m));
             }
         }
     };
@@ -1432,8 +1459,10 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // Writes out the batch's nq lists, whose survivors are all finished; lane l takes
     // query l, whose original row is iq.  Kept counts for every query; lists that fit go
     // to their fixed place (kListCap slots per original row) as found, in 16-byte pieces,
-    // and the placement pass orders every such list by neighbour id; the sorted rows of
-    // longer ones are queued for the placement pass to collect again.  With the cap
+    // and the placement pass orders every such list by neighbour id; lists of up to kExtCap
+    // entries put the others in a block of the XCD's part of the extension; the sorted rows
+    // of longer ones (and of those that find no room in the batch's spilled hits or in the
+    // extension) are queued for the placement pass to collect again.  With the cap
     // binding (SEL and more than K hits), the entries of those lists are numbered through
     // a prefix over their lengths; each lane takes one entry, finds its query by binary
     // search, ranks it by its (D, j) key within its list (D >= 0, so its bits order like
@@ -1447,18 +1476,38 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         const unsigned int cnt = mine ? qcnt[lane] : 0u;
         const unsigned int Ku = static_cast<unsigned int>(K);
         const bool fits = mine && cnt <= static_cast<unsigned int>(kListCap) && (SEL || cnt <= Ku);
+        bool ext = kSpill && mine && cnt > static_cast<unsigned int>(kListCap) &&
+                   cnt <= min(static_cast<unsigned int>(kExtCap), Ku) &&
+                   n_spilled <= static_cast<unsigned int>(kSpillCap);
+        unsigned int block = 0u;
+        if (ext) {
+            block = atomicAdd(long_counter(claims, xcd, kExtCount), 1u);
+            ext = block < ext_cap;
+            block += xcd * ext_cap;
+        }
         if (mine) {
-            kept[iq] = min(cnt, Ku) | (fits ? 0u : kKeptLong);
+            kept[iq] = ext ? kKeptExt | block << kKeptExtBits | cnt : min(cnt, Ku) | (fits ? 0u : kKeptLong);
             if (cnt > Ku) ++capped;
+        }
+        if (kSpill && n_spilled) {
+            const unsigned int n = min(n_spilled, static_cast<unsigned int>(kSpillCap));
+            const uint2 x = spill[min(static_cast<unsigned int>(lane), n - 1u)];
+            const int q = static_cast<int>(x.x >> 8);
+            const unsigned int to = static_cast<unsigned int>(__shfl(static_cast<int>(block), q));
+            const bool yes = __shfl(ext ? 1 : 0, q) != 0;
+            if (yes && static_cast<unsigned int>(lane) < n)
+                extension[static_cast<size_t>(to) * kListCap + ((x.x & 255u) - kListCap)] = x.y;
+        }
+        if (mine && !ext) {
             if (!fits && cnt <= kWaveKeys)
                 long_slots[wave_start[x_first] + atomicAdd(long_counter(claims, xcd, kLongCount), 1u)] = win + lane;
             if (!fits && cnt > kWaveKeys)
                 long_slots[wave_start[x_end] - 1u - atomicAdd(long_counter(claims, xcd, kHugeCount), 1u)] = win + lane;
         }
-        if (fits && !(SEL && cnt > Ku)) {
+        if ((fits && !(SEL && cnt > Ku)) || ext) {
             const uint4 *from = reinterpret_cast<const uint4 *>(lst + lane * kListCap);
             uint4 *to = reinterpret_cast<uint4 *>(temp + static_cast<size_t>(iq) * kListCap);
-            for (unsigned int k = 0; 4u * k < cnt; ++k) to[k] = from[k];
+            for (unsigned int k = 0; 4u * k < min(cnt, static_cast<unsigned int>(kListCap)); ++k) to[k] = from[k];
         }
         if (SEL) {
             const unsigned int take = fits && cnt > Ku ? cnt : 0u;
@@ -1491,6 +1540,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                 }
             }
         }
+        n_spilled = 0u;
         wave_lds_sync();
     };
     float lead[kLead] = {};  // leading coordinates of the lane's query
@@ -1749,8 +1799,7 @@ __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const uns
     // A tile holds at most 256 x 4096 edges and a group 64 times that: 32 bits do.
 #pragma unroll
     for (int k = 0; k < kTilesPerWave; ++k) {
-        const unsigned int v = (c[k].x & ~kKeptLong) + (c[k].y & ~kKeptLong) + (c[k].z & ~kKeptLong) +
-                               (c[k].w & ~kKeptLong);
+        const unsigned int v = kept_count(c[k].x) + kept_count(c[k].y) + kept_count(c[k].z) + kept_count(c[k].w);
         const unsigned int t = wave_sum(v);
         if (lane_id() == 0) tile_sum[wave_id() * kTilesPerWave + k] = t;
     }
@@ -1955,12 +2004,13 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
 // The lists a single wave collects: at most kWaveKeys hits.
 
 // Sorts R values per lane ascending, element r of lane l at position 64 r + l, by a
-// bitonic network: exchanges at distances of 64 and more stay inside a lane.
-template <int R>
+// bitonic network: exchanges at distances of 64 and more stay inside a lane.  SIZE below
+// 64 sorts each group of that many lanes by itself.
+template <int R, int SIZE = 64 * R>
 __device__ __forceinline__ void wave_sort(unsigned int (&v)[R]) {
     const unsigned int lane = static_cast<unsigned int>(lane_id());
 #pragma unroll
-    for (unsigned int k = 2; k <= 64u * R; k <<= 1) {
+    for (unsigned int k = 2; k <= static_cast<unsigned int>(SIZE); k <<= 1) {
 #pragma unroll
         for (unsigned int j = k >> 1; j > 0; j >>= 1) {
             if (j >= 64u) {
@@ -1978,7 +2028,7 @@ __device__ __forceinline__ void wave_sort(unsigned int (&v)[R]) {
 #pragma unroll
                 for (unsigned int r = 0; r < R; ++r) {
                     const unsigned int p = static_cast<unsigned int>(__shfl_xor(static_cast<int>(v[r]), j));
-                    const bool up = (((r * 64u) | lane) & k) == 0u;
+                    const bool up = (((r * 64u) | lane) & k) == 0u || k == static_cast<unsigned int>(SIZE);
                     const bool low = (lane & j) == 0u;
                     v[r] = up == low ? min(v[r], p) : max(v[r], p);
                 }
@@ -2160,6 +2210,8 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                                                        const unsigned int *__restrict__ long_counts,
                                                        const unsigned int *__restrict__ wave_start,
                                                        unsigned int search_blocks,
+                                                       const unsigned int *__restrict__ extension,
+                                                       unsigned int ext_cap,
                                                        const unsigned int *__restrict__ temp,
                                                        const float *__restrict__ sorted,
                                                        const unsigned int *__restrict__ sorted_id,
@@ -2181,6 +2233,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     unsigned int *wdst = wbuf;
     unsigned char *wq = reinterpret_cast<unsigned char *>(wbuf + kOwnerWindow);  // the query, in the block
     __shared__ unsigned int il_s[kPlaceTile];  // event-local row of each of the block's queries
+    __shared__ uint2 ext_s[kPlaceTile];  // the block's queries with extended lists, and their kept words
+    __shared__ unsigned int n_ext;
+    if (threadIdx.x == 0) n_ext = 0u;    // counted after the next barrier
     __shared__ unsigned long long scratch[kWaves];
     __shared__ LongLds<DP> L;
     __shared__ unsigned int map_all[kWaves][128];  // RunMap of each wave
@@ -2197,9 +2252,10 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     // of the tile totals below.
     const bool mine = !abort && q < cnt;
     const unsigned int kraw = mine ? kept[i0 + q] : 0u;
-    const unsigned int kq = kraw & ~kKeptLong;
+    const unsigned int kq = kept_count(kraw);
+    const bool is_ext = mine && (kraw & kKeptExt) != 0u;
     const bool is_long = mine && (kraw & kKeptLong) != 0u;
-    const bool fixed = mine && kq > 0u && !is_long;
+    const bool fixed = mine && kq > 0u && !is_long && !is_ext;
     unsigned int v[kListCap];
     if (fixed) {
         const uint4 *l4 = reinterpret_cast<const uint4 *>(temp + static_cast<size_t>(i0 + q) * kListCap);
@@ -2242,7 +2298,8 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         rep.heavy = 0u;
         for (unsigned int x = 0; x < 8u && !abort; ++x)
             rep.heavy += long_counts[x * kPools * kPoolStride + kLongCount] +
-                         long_counts[x * kPools * kPoolStride + kHugeCount];
+                         long_counts[x * kPools * kPoolStride + kHugeCount] +
+                         min(long_counts[x * kPools * kPoolStride + kExtCount], ext_cap);
         rep.n_cells = P.n_cells;
         for (int p = 0; p < kMaxAxes; ++p) {
             rep.G[p] = P.G[p];
@@ -2256,6 +2313,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         const unsigned int oq = static_cast<unsigned int>(oq64);
         if (q < cnt) o[q] = oq;
         if (q == cnt - 1) o[cnt] = oq + kq;
+        if (is_ext) ext_s[atomicAdd(&n_ext, 1u)] = make_uint2(static_cast<unsigned int>(q), kraw);
         __syncthreads();
         // Edge ranges of the events whose first row lies in this block (events with no
         // rows at the very end start at E).
@@ -2314,7 +2372,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                         wdst[pw] = v[u] - brow;
                     }
                 }
-            } else if (is_long) {
+            } else if (is_long || is_ext) {
                 const unsigned int a0 = oq > w0 ? oq - w0 : 0u;
                 const unsigned int a1 = oq + kq > w0 ? min(oq + kq - w0, wend) : 0u;
                 for (unsigned int pw = a0; pw < a1; ++pw) {
@@ -2330,6 +2388,22 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                 if (dv != kSkip) dst[at] = dv;
             }
             __syncthreads();
+        }
+        // Extended lists, one per half wave: the first kListCap neighbours from the query's
+        // fixed place, the others from its block of the extension, sorted across 32 lanes.
+        for (unsigned int x0 = 2u * wave_id(); x0 < n_ext; x0 += 2u * kWaves) {
+            const unsigned int l = threadIdx.x & 31u, x = x0 + (static_cast<unsigned int>(lane_id()) >> 5);
+            const uint2 w = ext_s[min(x, n_ext - 1u)];
+            const unsigned int count = x < n_ext ? w.y & kKeptExtCount : 0u;
+            const unsigned int block = (w.y & ~kKeptExt) >> kKeptExtBits;
+            const unsigned int *from = l < static_cast<unsigned int>(kListCap)
+                                           ? temp + static_cast<size_t>(i0 + w.x) * kListCap + l
+                                           : extension + static_cast<size_t>(block) * kListCap + (l - kListCap);
+            unsigned int id[1] = {0xffffffffu};
+            if (l < count) id[0] = *from;
+            wave_sort<1, 32>(id);
+            const unsigned int base = static_cast<unsigned int>(i0) + w.x - il_s[w.x];  // the event's first row
+            if (l < count) dst[static_cast<long long>(pre + o[w.x]) + l] = id[0] - base;
         }
     }
     if (abort || overflow) return;
@@ -2399,12 +2473,12 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
             const long long x0 = static_cast<long long>(t) * kPlaceTile + 4 * lane_id();
             if (x0 < gi) {  // then x0 .. x0 + 3 lie in the array (256-byte aligned, padded)
                 const uint4 c = *reinterpret_cast<const uint4 *>(kept + x0);
-                at += c.x & ~kKeptLong;
-                if (x0 + 1 < gi) at += c.y & ~kKeptLong;
-                if (x0 + 2 < gi) at += c.z & ~kKeptLong;
-                if (x0 + 3 < gi) at += c.w & ~kKeptLong;
+                at += kept_count(c.x);
+                if (x0 + 1 < gi) at += kept_count(c.y);
+                if (x0 + 2 < gi) at += kept_count(c.z);
+                if (x0 + 3 < gi) at += kept_count(c.w);
             }
-            const unsigned int nq = uniform(kept[gi]) & ~kKeptLong;
+            const unsigned int nq = kept_count(uniform(kept[gi]));
             if (gi < ev_lo || gi >= ev_end) {
                 const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
                 P = plans[e];
@@ -2432,9 +2506,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         unsigned long long at = 0, all = 0;
         tile_prefix(t, at, all);
         const long long x = static_cast<long long>(t) * kPlaceTile + threadIdx.x;
-        if (x < gi) at += kept[x] & ~kKeptLong;
+        if (x < gi) at += kept_count(kept[x]);
         at = block_sum(at, scratch);
-        const unsigned int nq = kept[gi] & ~kKeptLong;
+        const unsigned int nq = kept_count(kept[gi]);
         if (at + nq > cap) continue;  // cannot happen when E <= cap
         const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
         const Plan P = plans[e];
@@ -2467,15 +2541,21 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
                            a.ev_from_arg, ws.plans,
                            ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, rows, ws.sorted_id);
     mark(4);
+    // The extension's blocks take the memory of the histogram (or of the binning's tables),
+    // read for the last time before the search: an eighth each XCD.
+    const unsigned int ext_cap =
+        static_cast<unsigned int>(std::min<long long>(ws.cells / kListCap, kExtBlocksMax) / 8);
     SearchCounts *counts = reinterpret_cast<SearchCounts *>(ws.rank);
     if (a.K < kListCap)
         hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.cell_count, ext_cap, ws.ctr, counts,
+                           a.search_prio);
     else
         hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
                            ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.ctr, counts, a.search_prio);
+                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.cell_count, ext_cap, ws.ctr, counts,
+                           a.search_prio);
     mark(5);
     // One block per group of tiles, and one for the search's counts.
     hipLaunchKernelGGL(k_kept_sums, dim3(ws.groups_kept_n + 1), dim3(kSumsBlock), 0, a.stream, rows, ws.kept,
@@ -2485,7 +2565,7 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     hipLaunchKernelGGL(k_place<DP>, dim3(static_cast<unsigned int>(place_blocks)), dim3(kPlaceBlock), 0, a.stream,
                        rows, ws.ev, a.n_events, ws.kept, ws.sums_kept, ws.sums_kept2, ws.groups_kept_n,
                        ws.tiles_kept_n, ws.long_slots, ws.claims, ws.wave_start,
-                       static_cast<unsigned int>(a.search_blocks), ws.temp, ws.sorted, ws.sorted_id, ws.cell_start, a.r2, a.K,
+                       static_cast<unsigned int>(a.search_blocks), ws.cell_count, ext_cap, ws.temp, ws.sorted, ws.sorted_id, ws.cell_start, a.r2, a.K,
                        a.src, a.dst, a.edge_capacity, ws.plans, ws.ctr, a.edge_off_out ? a.edge_off_out : ws.edge_off,
                        a.report_out ? a.report_out : ws.report);
 }
