@@ -45,9 +45,10 @@
 namespace frnn {
 namespace {
 
-__device__ __forceinline__ unsigned int prefix_count(unsigned long long mask) {
+// base plus the set bits below the lane's own.
+__device__ __forceinline__ unsigned int prefix_count(unsigned long long mask, unsigned int base = 0u) {
     return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned int>(mask >> 32),
-                                     __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(mask), 0u));
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(mask), base));
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
@@ -1205,12 +1206,14 @@ __device__ __forceinline__ RunLane run_lane(const Plan &P, bool halves) {
 // With `halves`, lanes 32.. do the same for a second cell (their pc), numbered by
 // itself.  Call with the whole wave active; a cell's candidate count is `end` in the
 // last lane of its half (or of the wave).
+// FOUR: the plan has four binned axes (and then reach 1).
+template <bool FOUR>
 __device__ __forceinline__ void wave_runs(unsigned int pc, unsigned int cell0, const Plan &P, const RunLane &rl,
                                           bool live, bool halves, const unsigned int *__restrict__ cell_start,
                                           unsigned int &start, unsigned int &pre, unsigned int &end) {
-    const int R = P.reach;
+    const int R = FOUR ? 1 : P.reach;
     int u[kMaxAxes];
-    unpack_cell(pc, P.axes, u);
+    unpack_cell(pc, FOUR ? 4 : P.axes, u);
     // Branch-free: every lane loads (a lane without a run reads the event's first
     // row of cells, a valid address) and keeps its run only if it is inside the grid
     // (the unsigned comparisons also reject negative coordinates).  An event has at most
@@ -1280,9 +1283,7 @@ struct RunMap {
         // Runs that start at or before the lane's candidate: the marks up to its own.
         const unsigned long long above = m >> 1;
         const unsigned int base = before + static_cast<unsigned int>(m & 1ull) - 1u;
-        const unsigned int k = __builtin_amdgcn_mbcnt_hi(
-            static_cast<unsigned int>(above >> 32),
-            __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(above), base));
+        const unsigned int k = prefix_count(above, base);
         before += static_cast<unsigned int>(__popcll(m));
         return off[k & 63u] + b + static_cast<unsigned int>(lane_id());
     }
@@ -1298,7 +1299,9 @@ constexpr int kSearchWaves = DP <= 16 ? 8 : (DP == 48 ? 4 : 1);
 
 // SEL: the cap K is below kListCap, so a list that fits may still need the K
 // nearest of its hits: the lists then also hold each hit's distance.
-template <int DP, bool SEL>
+// FOUR: the call bins four axes, so that the shape of a cell's neighbourhood is known and
+// takes no scalar registers.
+template <int DP, bool SEL, bool FOUR>
 __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float *__restrict__ sorted, long long rows,
                                                    const unsigned int *__restrict__ sorted_id,
                                                    const unsigned int *__restrict__ wave_start,
@@ -1389,7 +1392,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     unsigned int *claim = claims + (xcd * kPools + pool) * kPoolStride;
     Plan P;
     RunLane rl;
-    bool halves = false;  // a cell's runs fit half a wave: the runs of two cells are built at once
+    bool halves = FOUR;  // a cell's runs fit half a wave: the runs of two cells are built at once
     unsigned int cell0 = 0;
     unsigned int ev_end = 0;  // first row after the current event
     const uint2 *__restrict__ sid = reinterpret_cast<const uint2 *>(sorted_id);
@@ -1584,7 +1587,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                 const unsigned long long m1 = __builtin_amdgcn_ballot_w64(acc < r2);
                 if (m1 == 0ull) continue;
                 if (acc < r2) {
-                    const unsigned int e = (tail + prefix_count(m1)) & (kRing - 1);
+                    const unsigned int e = prefix_count(m1, tail) & (kRing - 1);
                     ring[e] = (static_cast<unsigned long long>(uniform(q)) << 32) | s;
                     racc[e] = acc;
                 }
@@ -1627,7 +1630,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
                 const EventDesc E = ev[e];
                 cell0 = static_cast<unsigned int>(E.cell0);
                 ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
-                halves = run_count(P) <= 32;
+                halves = FOUR || run_count(P) <= 32;
                 rl = run_lane(P, halves);
             }
             const unsigned int v_orig = next.x, v_pc = next.y;
@@ -1676,16 +1679,16 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
             for (unsigned int t0 = 0; t0 < nq;) {
                 // The runs of this cell and, in the other half of the wave, of the next.
                 const unsigned int t1 = cell_end(t0);
-                const bool two = halves && t1 < nq;
+                const bool two = (FOUR || halves) && t1 < nq;
                 const unsigned int t2 = two ? cell_end(t1) : t1;
                 const unsigned int pc0 = __builtin_amdgcn_readlane(v_pc, t0);
                 const unsigned int pc1 = __builtin_amdgcn_readlane(v_pc, two ? t1 : t0);
-                const bool second = halves && lane >= 32;
+                const bool second = (FOUR || halves) && lane >= 32;
                 unsigned int start, pre, end;
-                wave_runs(second ? pc1 : pc0, cell0, P, rl, rl.live && (!second || two), halves, cell_start, start,
+                wave_runs<FOUR>(second ? pc1 : pc0, cell0, P, rl, rl.live && (!second || two), FOUR || halves, cell_start, start,
                           pre, end);
                 const unsigned long long some = map.keep(start, pre, end);
-                const unsigned int m_first = __builtin_amdgcn_readlane(end, halves ? 31 : 63);
+                const unsigned int m_first = __builtin_amdgcn_readlane(end, FOUR || halves ? 31 : 63);
                 const unsigned int m_second = lane63(end);
                 map.begin(!second, pre, end, 0u);
 #pragma clang loop unroll(disable)
@@ -1738,23 +1741,25 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
 // reads group g's counts, four per lane and load and all of a lane's loads issued
 // together, and writes each tile's prefix inside the group and the group's total, so
 // that a row's output position is the totals of the groups before it (a few loads for
-// a whole wave), its tile's prefix and the counts before it in its tile.  The last
-// workgroup, which has no group, sums the search's per-workgroup counts for the
-// report, beside the others and off the placement pass's path.
+// a whole wave), its tile's prefix and the counts before it in its tile.  The workgroups
+// past the groups sum the search's per-workgroup counts for the report, beside the others
+// and off the placement pass's path.
 __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const unsigned int *__restrict__ kept,
                                                           unsigned long long *__restrict__ tile_pre,
                                                           unsigned long long *__restrict__ group_sum, int tiles_kept,
                                                           const SearchCounts *__restrict__ counts,
-                                                          int search_blocks, Counters *__restrict__ ctr) {
+                                                          int search_blocks, int groups,
+                                                          Counters *__restrict__ ctr) {
     constexpr int kSumsWaves = kSumsBlock / 64;
     constexpr int kTilesPerWave = kKeptGroup / kSumsWaves;
     static_assert(kTilesPerWave * kSumsWaves == kKeptGroup && kPlaceTile == 256, "four counts per lane and tile");
     if (ctr->abort) return;
-    if (blockIdx.x == gridDim.x - 1) {
+    if (static_cast<int>(blockIdx.x) >= groups) {
         __shared__ unsigned long long red[3][kSumsWaves];
         unsigned long long t = 0, sv = 0, cp = 0;
-#pragma unroll 8
-        for (int k = threadIdx.x; k < search_blocks; k += kSumsBlock) {
+        const int step = (static_cast<int>(gridDim.x) - groups) * kSumsBlock;
+        for (int k = (static_cast<int>(blockIdx.x) - groups) * kSumsBlock + static_cast<int>(threadIdx.x);
+             k < search_blocks; k += step) {
             t += counts[k].tested;
             sv += counts[k].survived;
             cp += counts[k].capped;
@@ -1775,9 +1780,10 @@ __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const uns
                 sv += red[1][w];
                 cp += red[2][w];
             }
-            ctr->tested = t;
-            ctr->survived = sv;
-            ctr->capped = static_cast<unsigned int>(cp);
+            // Cleared by the bounds pass; one workgroup per 2,048 counts adds to them.
+            atomicAdd(&ctr->tested, t);
+            atomicAdd(&ctr->survived, sv);
+            if (cp) atomicAdd(&ctr->capped, static_cast<unsigned int>(cp));
         }
         return;
     }
@@ -1855,7 +1861,7 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
     if (wave_id() == 0) {
         unsigned int start, pre, end;
         const RunLane rl = run_lane(P, false);
-        wave_runs(sorted_id[2u * slot + 1u], cell0, P, rl, rl.live, false, cell_start, start, pre, end);
+        wave_runs<false>(sorted_id[2u * slot + 1u], cell0, P, rl, rl.live, false, cell_start, start, pre, end);
         const unsigned int M = lane63(end);
         L.run_start[lane_id()] = start;
         L.run_pre[lane_id()] = pre;
@@ -2141,7 +2147,7 @@ __device__ __forceinline__ void wave_list(const SortedRows<DP> &pts, const unsig
     const int lane = lane_id();
     unsigned int start, pre, end;
     const RunLane rl = run_lane(P, false);
-    wave_runs(pc, cell0, P, rl, rl.live, false, cell_start, start, pre, end);
+    wave_runs<false>(pc, cell0, P, rl, rl.live, false, cell_start, start, pre, end);
     const unsigned int M = lane63(end);
     float qrow[DP];  // wave-uniform
     pts.load(slot, qrow);
@@ -2546,20 +2552,18 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const unsigned int ext_cap =
         static_cast<unsigned int>(std::min<long long>(ws.cells / kListCap, kExtBlocksMax) / 8);
     SearchCounts *counts = reinterpret_cast<SearchCounts *>(ws.rank);
-    if (a.K < kListCap)
-        hipLaunchKernelGGL((k_search<DP, true>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
-                           ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.cell_count, ext_cap, ws.ctr, counts,
-                           a.search_prio);
-    else
-        hipLaunchKernelGGL((k_search<DP, false>), dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows,
-                           ws.sorted_id, ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans,
-                           a.r2, a.K, ws.kept, ws.temp, ws.long_slots, ws.cell_count, ext_cap, ws.ctr, counts,
-                           a.search_prio);
+    auto search = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(a.search_blocks), dim3(kBlock), 0, a.stream, ws.sorted, rows, ws.sorted_id,
+                           ws.wave_start, ws.claims, ws.ev, a.n_events, ws.cell_start, ws.plans, a.r2, a.K, ws.kept,
+                           ws.temp, ws.long_slots, ws.cell_count, ext_cap, ws.ctr, counts, a.search_prio);
+    };
+    if (a.K < kListCap) a.axes == 4 ? search(k_search<DP, true, true>) : search(k_search<DP, true, false>);
+    else a.axes == 4 ? search(k_search<DP, false, true>) : search(k_search<DP, false, false>);
     mark(5);
-    // One block per group of tiles, and one for the search's counts.
-    hipLaunchKernelGGL(k_kept_sums, dim3(ws.groups_kept_n + 1), dim3(kSumsBlock), 0, a.stream, rows, ws.kept,
-                       ws.sums_kept, ws.sums_kept2, ws.tiles_kept_n, counts, a.search_blocks, ws.ctr);
+    // One block per group of tiles, and one per 2,048 counts of the search.
+    hipLaunchKernelGGL(k_kept_sums, dim3(ws.groups_kept_n + (a.search_blocks + 2047) / 2048), dim3(kSumsBlock), 0,
+                       a.stream, rows, ws.kept, ws.sums_kept, ws.sums_kept2, ws.tiles_kept_n, counts,
+                       a.search_blocks, ws.groups_kept_n, ws.ctr);
     mark(6);
     const int place_blocks = ws.tiles_kept_n > kPlaceMinBlocks ? ws.tiles_kept_n : kPlaceMinBlocks;
     hipLaunchKernelGGL(k_place<DP>, dim3(static_cast<unsigned int>(place_blocks)), dim3(kPlaceBlock), 0, a.stream,
@@ -2573,8 +2577,8 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
 template <int DP>
 int occupancy_blocks(bool sel) {
     int per_cu = 0;
-    const hipError_t e = sel ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, true>, kBlock, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, false>, kBlock, 0);
+    const hipError_t e = sel ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, true, true>, kBlock, 0)
+                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, false, true>, kBlock, 0);
     if (e != hipSuccess || per_cu < 1)
         per_cu = 1;
     int dev = 0, cus = 0;
