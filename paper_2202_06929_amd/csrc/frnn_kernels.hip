@@ -100,47 +100,53 @@ __device__ __forceinline__ float sq_dist(const float (&a)[DP], const float (&b)[
 // 0.173, 0.292 and 0.558 ms to 0.204, 0.423 and 1.126 ms).
 constexpr int search_lead(int dpad) { return dpad <= 12 ? 2 : (dpad < 32 ? 3 : 4); }
 
-// The sorted points, zero-padded to DP coordinates (a multiple of 4).  Rows of 32 floats
-// and more lie in two parts: the leading coordinates of all rows, which the search's first
-// stage reads for every candidate, side by side (16 bytes a row instead of one line each),
-// then the rest of each row (60k points of 32, 48 and 64 coordinates: whole builds 95, 88.7
-// and 121.7 us with whole rows, 88, 85.7 and 109.5 with split ones; of 16 and 24 equal, of
-// 8 to 12 1 to 3% slower, as the second stage's loads then cross lines).
+// The sorted points, zero-padded to DP coordinates (a multiple of 4).  Rows of 12 floats
+// and more lie in two parts: the first four coordinates of all rows, of which the search's
+// first stage reads two to four for every candidate, side by side (16 bytes a row instead
+// of a line or a good part of one each), then the rest of each row.  Whole builds with
+// whole and with split rows: 300k points of 12 coordinates 129.8 and 127.1 us, 60k of 16
+// 55.5 and 54.2, of 32, 48 and 64 95, 88.7 and 121.7 against 88, 85.7 and 103.8; with rows
+// of 8 a dense 60k-point event 122.8 and 124.8, a batch of 5.6M points 1416 and 1424.
+constexpr int kSplitFrom = 12;
+
 template <int DP>
 struct SortedRows {
-    static constexpr bool kSplit = DP >= 32;
+    static constexpr bool kSplit = DP >= kSplitFrom;
     static constexpr int kLead = search_lead(DP);
-    static constexpr int kTail = DP - kLead;
-    static constexpr int kLeadStride = kSplit ? kLead : DP;
-    static constexpr int kTailStride = kSplit ? kTail : DP;
+    static constexpr int kHead = kSplit ? 4 : kLead;  // coordinates in the leading part
+    static constexpr int kTail = DP - kLead;          // coordinates of the second stage
+    static constexpr int kLeadStride = kSplit ? kHead : DP;
+    static constexpr int kRestStride = kSplit ? DP - kHead : DP;
     const float *__restrict__ lead;
-    const float *__restrict__ tail;
-    static __device__ __forceinline__ size_t tail_at(long long rows) {
-        return kSplit ? static_cast<size_t>(rows) * kLead : static_cast<size_t>(kLead);
+    const float *__restrict__ rest;
+    static __device__ __forceinline__ size_t rest_at(long long rows) {
+        return kSplit ? static_cast<size_t>(rows) * kHead : static_cast<size_t>(kHead);
     }
     __device__ __forceinline__ SortedRows(const float *__restrict__ sorted, long long rows)
-        : lead(sorted), tail(sorted + tail_at(rows)) {}
+        : lead(sorted), rest(sorted + rest_at(rows)) {}
     __device__ __forceinline__ const float *lead_of(unsigned int s) const {
         return lead + static_cast<size_t>(s) * kLeadStride;
     }
-    __device__ __forceinline__ const float *tail_of(unsigned int s) const {
-        return tail + static_cast<size_t>(s) * kTailStride;
+    __device__ __forceinline__ float at(unsigned int s, int k) const {
+        return k < kHead ? lead_of(s)[k] : rest[static_cast<size_t>(s) * kRestStride + (k - kHead)];
     }
+    // Coordinates from FROM on.
+    template <int FROM>
     __device__ __forceinline__ void load(unsigned int s, float (&c)[DP]) const {
-        const float *a = lead_of(s), *b = tail_of(s);
+        const float *a = lead_of(s), *b = rest + static_cast<size_t>(s) * kRestStride;
 #pragma unroll
-        for (int k = 0; k < kLead; ++k) c[k] = a[k];
+        for (int k = FROM; k < kHead; ++k) c[k] = a[k];
 #pragma unroll
-        for (int k = kLead; k < DP; ++k) c[k] = b[k - kLead];
+        for (int k = FROM > kHead ? FROM : kHead; k < DP; ++k) c[k] = b[k - kHead];
     }
     static __device__ __forceinline__ void store(float *__restrict__ sorted, long long rows, unsigned int s,
                                                  const float (&c)[DP]) {
         float *a = sorted + static_cast<size_t>(s) * kLeadStride;
-        float *b = sorted + tail_at(rows) + static_cast<size_t>(s) * kTailStride;
+        float *b = sorted + rest_at(rows) + static_cast<size_t>(s) * kRestStride;
 #pragma unroll
-        for (int k = 0; k < kLead; ++k) a[k] = c[k];
+        for (int k = 0; k < kHead; ++k) a[k] = c[k];
 #pragma unroll
-        for (int k = kLead; k < DP; ++k) b[k - kLead] = c[k];
+        for (int k = kHead; k < DP; ++k) b[k - kHead] = c[k];
     }
 };
 
@@ -995,7 +1001,6 @@ template <int DP>
 __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span, const EventDesc *__restrict__ ev,
                                                        EventDesc ev0, int ev_from_arg,
                                                        const Plan *__restrict__ plans,
-                                                       const Counters *__restrict__ ctr,
                                                        const uint2 *__restrict__ ents,
                                                        const unsigned short *__restrict__ table,
                                                        unsigned int *__restrict__ cell_start,
@@ -1010,7 +1015,6 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     __shared__ unsigned int seg_pre[kBinMaxShares];   // points of the tile in the shares before
     __shared__ unsigned int seg_from[kBinMaxShares];  // where the share's points of the tile lie in ents
     __shared__ uint2 scratch[2][kTWaves];
-    if (ctr->abort) return;
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         static_assert(8 * kPools <= kTilesBlock && kExtCount < kPoolStride, "one claim line per thread");
         if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
@@ -1024,7 +1028,7 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     const EventDesc E = ev_from_arg ? ev0 : ev[blockIdx.y];
     const Plan P = plans[blockIdx.y];
     const int t = static_cast<int>(blockIdx.x);
-    if (t >= P.n_tiles || E.n == 0) return;
+    if (P.abort || t >= P.n_tiles || E.n == 0) return;
     // The tile's segment of every share (one share per thread).
     static_assert(kBinMaxShares == kTilesBlock, "one share per thread");
     const int shares = bin_shares(E.n, span);
@@ -1058,15 +1062,37 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
         cell = cell_key(u, P) - key0;
         return x;
     };
-    // A thread's first kHeld points stay in registers between the two passes.
+    auto fetch = [&](uint2 x, float (&row)[DP]) {
+        if (vec4) {
+            const float4 *src = reinterpret_cast<const float4 *>(E.pts + static_cast<size_t>(x.x) * d);
+#pragma unroll
+            for (int k = 0; k < DP / 4; ++k) {
+                float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (4 * k < d) w = src[k];
+                row[4 * k] = w.x;
+                row[4 * k + 1] = w.y;
+                row[4 * k + 2] = w.z;
+                row[4 * k + 3] = w.w;
+            }
+        } else {
+            const float *src = E.pts + static_cast<size_t>(x.x) * d;
+#pragma unroll
+            for (int k = 0; k < DP; ++k) row[k] = k < d ? src[k] : 0.0f;
+        }
+    };
+    // A thread's first kHeld points stay in registers between the two passes, narrow
+    // rows with them: they are requested here, and arrive while the cells are counted.
     constexpr int kHeld = 2;
+    constexpr bool kRowsAhead = DP <= 12;
     uint2 held[kHeld];
     unsigned int held_cell[kHeld];
+    float held_row[kRowsAhead ? kHeld : 1][DP];
 #pragma unroll
     for (int m = 0; m < kHeld; ++m) {
         const unsigned int q = m * kTilesBlock + threadIdx.x;
         if (q < n_tile) {
             held[m] = point(q, held_cell[m]);
+            if (kRowsAhead) fetch(held[m], held_row[m]);
             atomicAdd(&cursor[held_cell[m]], 1u);
         }
     }
@@ -1121,24 +1147,7 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     }
     __syncthreads();
     // The rows, each to the next place of its cell.
-    auto place = [&](uint2 x, unsigned int cell) {
-        float row[DP];
-        if (vec4) {
-            const float4 *src = reinterpret_cast<const float4 *>(E.pts + static_cast<size_t>(x.x) * d);
-#pragma unroll
-            for (int k = 0; k < DP / 4; ++k) {
-                float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (4 * k < d) w = src[k];
-                row[4 * k] = w.x;
-                row[4 * k + 1] = w.y;
-                row[4 * k + 2] = w.z;
-                row[4 * k + 3] = w.w;
-            }
-        } else {
-            const float *src = E.pts + static_cast<size_t>(x.x) * d;
-#pragma unroll
-            for (int k = 0; k < DP; ++k) row[k] = k < d ? src[k] : 0.0f;
-        }
+    auto place = [&](uint2 x, unsigned int cell, const float (&row)[DP]) {
         const unsigned int slot = first_row + atomicAdd(&cursor[cell], 1u);
         SortedRows<DP>::store(sorted, rows, slot, row);
         reinterpret_cast<uint2 *>(sorted_id)[slot] =
@@ -1146,11 +1155,16 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     };
 #pragma unroll
     for (int m = 0; m < kHeld; ++m)
-        if (m * kTilesBlock + threadIdx.x < n_tile) place(held[m], held_cell[m]);
+        if (m * kTilesBlock + threadIdx.x < n_tile) {
+            if (!kRowsAhead) fetch(held[m], held_row[kRowsAhead ? m : 0]);
+            place(held[m], held_cell[m], held_row[kRowsAhead ? m : 0]);
+        }
     for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
         unsigned int cell;
         const uint2 x = point(q, cell);
-        place(x, cell);
+        float row[DP];
+        fetch(x, row);
+        place(x, cell, row);
     }
 }
 
@@ -1347,7 +1361,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     __shared__ unsigned long long tested_w[kWaves];
     __shared__ unsigned long long survived_w[kWaves];
     __shared__ unsigned int capped_w[kWaves];
-    if (ctr->abort) return;
+    const unsigned int abort = ctr->abort;
     unsigned int *lst = lst_all[wave_id()];
     unsigned int *lstd = lstd_all[SEL ? wave_id() : 0];
     unsigned int capped = 0;
@@ -1390,7 +1404,14 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     const unsigned int pools = min(static_cast<unsigned int>(kPools), xnb);
     const unsigned int pool = xblk % pools;
     unsigned int *claim = claims + (xcd * kPools + pool) * kPoolStride;
-    Plan P;
+    // The wave's first share and, of a single event, the plan are requested with the abort
+    // flag (the shares' memory holds whatever it did when that is set).
+    unsigned int piece = x_first + xblk * kWaves + wave_id();
+    unsigned int q_lo = wave_start[piece];
+    unsigned int q_hi = wave_start[piece + 1u];
+    Plan P = plans[0];
+    asm volatile("" : "+s"(q_lo), "+s"(q_hi), "+s"(P.G[0]));
+    if (abort) return;
     RunLane rl;
     bool halves = FOUR;  // a cell's runs fit half a wave: the runs of two cells are built at once
     unsigned int cell0 = 0;
@@ -1439,17 +1460,13 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         const float a3 = act ? racc[e] : 0.0f;
         const unsigned int q = static_cast<unsigned int>(ent >> 32);
         const unsigned int s2 = static_cast<unsigned int>(ent);
-        const float *crow = pts.tail_of(s2);
         float cc[DP], qq[DP];
-#pragma unroll
-        for (int k = kLead; k < DP; ++k) cc[k] = crow[k - kLead];
+        pts.template load<kLead>(s2, cc);
         if (kTailLds) {
 #pragma unroll
             for (int k = kLead; k < DP; ++k) qq[k] = qtail[q * kTail + (k - kLead)];
         } else {
-            const float *qrow = pts.tail_of(win + q);
-#pragma unroll
-            for (int k = kLead; k < DP; ++k) qq[k] = qrow[k - kLead];
+            pts.template load<kLead>(win + q, qq);
         }
         unsigned int j2 = sorted_id[2u * static_cast<size_t>(s2)];
         const float D = add_terms<kLead, DP, DP, DP>(a3, cc, qq);
@@ -1600,13 +1617,11 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         }
         tested += static_cast<unsigned long long>(M) * (q1 - q0);
     };
-    for (unsigned int piece = x_first + xblk * kWaves + wave_id(); piece < x_end;) {
+    while (piece < x_end) {
         // The next piece is claimed before this one is worked off, so that the claim's
         // round trip overlaps the first loads.
         unsigned int claimed = 0;
         if (kPieces > 1 && lane == 0) claimed = atomicAdd(claim, 1u);
-        const unsigned int q_lo = wave_start[piece];
-        const unsigned int q_hi = wave_start[piece + 1u];
         // The lane's query of a batch: its original row and packed cell, and the leading
         // coordinates of its row.
         // (16-float rows have no registers left to hold the latter ahead.)
@@ -1626,7 +1641,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         for (win = q_lo; win < q_hi;) {
             if (win >= ev_end) {
                 const int e = n_events == 1 ? 0 : find_event(ev, n_events, win);
-                P = plans[e];
+                if (n_events > 1) P = plans[e];
                 const EventDesc E = ev[e];
                 cell0 = static_cast<unsigned int>(E.cell0);
                 ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
@@ -1669,7 +1684,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
             if (lane < kQT) qcnt[lane] = 0u;
             if (kTailLds)
                 for (unsigned int k = lane; k < nq * kTail; k += 64u)
-                    qtail[k] = pts.tail_of(win + k / kTail)[k % kTail];
+                    qtail[k] = pts.at(win + k / kTail, kLead + k % kTail);
             // End of the cell that query t of the batch lies in.
             auto cell_end = [&](unsigned int t) {
                 const unsigned long long rest = t < 63u ? starts >> (t + 1u) : 0ull;
@@ -1710,6 +1725,10 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
             win = after;
         }
         piece = kPieces > 1 ? x_dyn + pool + __builtin_amdgcn_readfirstlane(claimed) * pools : x_end;
+        if (kPieces > 1 && piece < x_end) {
+            q_lo = wave_start[piece];
+            q_hi = wave_start[piece + 1u];
+        }
     }
     capped = wave_sum(capped);
     if (lane == 0) {
@@ -1753,8 +1772,8 @@ __global__ __launch_bounds__(kSumsBlock) void k_kept_sums(long long n, const uns
     constexpr int kSumsWaves = kSumsBlock / 64;
     constexpr int kTilesPerWave = kKeptGroup / kSumsWaves;
     static_assert(kTilesPerWave * kSumsWaves == kKeptGroup && kPlaceTile == 256, "four counts per lane and tile");
-    if (ctr->abort) return;
     if (static_cast<int>(blockIdx.x) >= groups) {
+        if (ctr->abort) return;
         __shared__ unsigned long long red[3][kSumsWaves];
         unsigned long long t = 0, sv = 0, cp = 0;
         const int step = (static_cast<int>(gridDim.x) - groups) * kSumsBlock;
@@ -1857,7 +1876,7 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
     unsigned int *ids = wbuf;                                                  // [kMaxK], after the keys are read
     const int nruns = run_count(P);
     for (int k = threadIdx.x; k < DP; k += kPlaceBlock)
-        L.qv[k] = k < pts.kLead ? pts.lead_of(slot)[k] : pts.tail_of(slot)[k - pts.kLead];
+        L.qv[k] = pts.at(slot, k);
     if (wave_id() == 0) {
         unsigned int start, pre, end;
         const RunLane rl = run_lane(P, false);
@@ -1887,7 +1906,7 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
         }
         const unsigned int s = L.run_start[lo] + (m - L.run_pre[lo]);
         float c[DP];
-        pts.load(s, c);
+        pts.template load<0>(s, c);
         const float D = sq_dist<DP>(c, q);
         ok = (D < r2) && (s != slot);
         return (static_cast<unsigned long long>(__float_as_uint(D)) << 32) | sorted_id[2u * s];
@@ -2150,7 +2169,7 @@ __device__ __forceinline__ void wave_list(const SortedRows<DP> &pts, const unsig
     wave_runs<false>(pc, cell0, P, rl, rl.live, false, cell_start, start, pre, end);
     const unsigned int M = lane63(end);
     float qrow[DP];  // wave-uniform
-    pts.load(slot, qrow);
+    pts.template load<0>(slot, qrow);
     unsigned int h = 0;
     map.keep(start, pre, end);
     map.begin(true, pre, end, 0u);
@@ -2160,7 +2179,7 @@ __device__ __forceinline__ void wave_list(const SortedRows<DP> &pts, const unsig
         const unsigned int s = mm < M ? srow : slot;
         const unsigned int j = sorted_id[2u * static_cast<size_t>(s)];
         float c[DP];
-        pts.load(s, c);
+        pts.template load<0>(s, c);
         const float D = sq_dist<DP>(c, qrow);
         const bool hit = D < r2 && s != slot;
         const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
@@ -2256,14 +2275,12 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     // The query's kept count and its list of up to kListCap (at the query's own
     // fixed place) are requested first, so that their round trips overlap the sums
     // of the tile totals below.
-    const bool mine = !abort && q < cnt;
-    const unsigned int kraw = mine ? kept[i0 + q] : 0u;
-    const unsigned int kq = kept_count(kraw);
-    const bool is_ext = mine && (kraw & kKeptExt) != 0u;
-    const bool is_long = mine && (kraw & kKeptLong) != 0u;
-    const bool fixed = mine && kq > 0u && !is_long && !is_ext;
+    // (Neither waits for the abort flag, nor the list for the count: a place that holds no
+    // list is read for nothing.)
+    unsigned int kraw = 0u;
     unsigned int v[kListCap];
-    if (fixed) {
+    if (q < cnt) {
+        kraw = kept[i0 + q];
         const uint4 *l4 = reinterpret_cast<const uint4 *>(temp + static_cast<size_t>(i0 + q) * kListCap);
 #pragma unroll
         for (int c = 0; c < kListCap / 4; ++c) {
@@ -2274,6 +2291,12 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
             v[4 * c + 3] = w.w;
         }
     }
+    const bool mine = !abort && q < cnt;
+    kraw = mine ? kraw : 0u;
+    const unsigned int kq = kept_count(kraw);
+    const bool is_ext = mine && (kraw & kKeptExt) != 0u;
+    const bool is_long = mine && (kraw & kKeptLong) != 0u;
+    const bool fixed = mine && kq > 0u && !is_long && !is_ext;
     // Kept neighbours before tile t (and all of them), one part per thread.
     auto tile_prefix = [&](int t, unsigned long long &before, unsigned long long &all) {
         const int gt = t / kKeptGroup;
@@ -2539,7 +2562,7 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const int gs = static_cast<int>(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
     if (a.bin_span)
         hipLaunchKernelGGL(k_tiles<DP>, dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events), dim3(kTilesBlock),
-                           0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0, a.ev_from_arg, ws.plans, ws.ctr,
+                           0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0, a.ev_from_arg, ws.plans,
                            bin_ents(ws), bin_table(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
                            a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
     else
