@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
 
 // ------------------------------------------------------------------- keys
 
-// Wave 0 of a block folds the bounds partials and lane 0 derives the grid.
+// Wave 0 of a block folds the bounds partials and derives the grid, lane p axis p.
 // Every block derives the same plan from the same partials (min/max are exact).
 // Axes from `axes` on are not binned: one cell each.
 __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, float r,
@@ -477,7 +477,6 @@ __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, 
         mx[p] = wave_max(mx[p]);
     }
     bad = wave_any(bad);
-    if (lane_id() != 0) return;
     // Cell edge r (1 + 2^-10) / cell_div.  A pair that passes the float32 test has
     // |x_p - y_p| < r exactly along every coordinate (partial sums never exceed D,
     // rounding is monotone); the 2^-10 margin absorbs the float32 rounding of the
@@ -487,44 +486,44 @@ __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, 
     const float cbase = (r * 1.0009765625f) / static_cast<float>(cell_div);
     const int axis_max = axes == 4 ? kGridAxisMax4 : kGridAxisMax3;
     const float axis_soft = axes == 4 ? 250.0f : 1000.0f;
-    float c[kMaxAxes], ext[kMaxAxes];
-    int G[kMaxAxes];
+    const int p = lane_id() & (kMaxAxes - 1);
+    float lo = mn[0], hi = mx[0];
+#pragma unroll
+    for (int k = 1; k < kMaxAxes; ++k) {
+        lo = p == k ? mn[k] : lo;
+        hi = p == k ? mx[k] : hi;
+    }
     // An axis whose extent is not a finite float (no points, or max - min
     // overflowing), or that is not binned, gets a single cell: inv_c = 0 puts
     // every point in cell 0.
-    bool single[kMaxAxes];
-    for (int p = 0; p < kMaxAxes; ++p) {
-        ext[p] = mx[p] - mn[p];
-        single[p] = p >= axes || !(ext[p] >= 0.0f && ext[p] <= FLT_MAX);
-        if (!(mn[p] <= mx[p])) mn[p] = 0.0f;
-        c[p] = cbase;
-        if (!single[p] && ext[p] / c[p] > axis_soft) c[p] = ext[p] / axis_soft;
-    }
+    const float ext = hi - lo;
+    bool single = p >= axes || !(ext >= 0.0f && ext <= FLT_MAX);
+    if (!(lo <= hi)) lo = 0.0f;
+    float c = cbase;
+    if (!single && ext / c > axis_soft) c = ext / axis_soft;
     // Grow the cells until the grid fits cells_max (bounded: after 128 rounds of
     // x1.25 every finite extent spans one cell).
+    int G = 1;
+    long long total = 1;
     for (int round = 0;; ++round) {
-        long long total = 1;
-        for (int p = 0; p < kMaxAxes; ++p) {
-            float g = single[p] ? 1.0f : floorf(ext[p] / c[p]) + 1.0f;
-            if (!(g <= static_cast<float>(axis_max))) g = static_cast<float>(axis_max);
-            if (!(g >= 1.0f)) g = 1.0f;
-            G[p] = static_cast<int>(g);
-            total *= G[p];
-        }
+        float g = single ? 1.0f : floorf(ext / c) + 1.0f;
+        if (!(g <= static_cast<float>(axis_max))) g = static_cast<float>(axis_max);
+        if (!(g >= 1.0f)) g = 1.0f;
+        G = static_cast<int>(g);
+        total = static_cast<long long>(__builtin_amdgcn_readlane(G, 0)) * __builtin_amdgcn_readlane(G, 1) *
+                __builtin_amdgcn_readlane(G, 2) * __builtin_amdgcn_readlane(G, 3);
         if (total <= cells_max) break;
-        if (round >= 128) {
-            for (int p = 0; p < kMaxAxes; ++p) single[p] = true;
-            continue;
-        }
-        for (int p = 0; p < kMaxAxes; ++p) c[p] *= 1.25f;
+        if (round >= 128) single = true;
+        else c *= 1.25f;
     }
-    for (int p = 0; p < kMaxAxes; ++p) {
-        out->lo[p] = p < axes ? mn[p] : 0.0f;
-        out->c[p] = single[p] ? INFINITY : c[p];
-        out->inv_c[p] = single[p] ? 0.0f : 1.0f / c[p];
-        out->G[p] = G[p];
+    if (lane_id() < kMaxAxes) {
+        out->lo[p] = p < axes ? lo : 0.0f;
+        out->c[p] = single ? INFINITY : c;
+        out->inv_c[p] = single ? 0.0f : 1.0f / c;
+        out->G[p] = G;
     }
-    out->n_cells = G[0] * G[1] * G[2] * G[3];
+    if (lane_id() != 0) return;
+    out->n_cells = static_cast<int>(total);
     out->reach = cell_div;
     out->abort = bad;
     out->axes = axes;
