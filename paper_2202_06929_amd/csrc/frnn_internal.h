@@ -28,7 +28,10 @@ constexpr int kMaxK = 4096;
 constexpr int kMaxPieceCount = 98304;
 // A cell's fixed cost in the search (its runs' bounds, its candidates' first
 // loads), in queries, when the queries are divided among the waves by work.
-constexpr unsigned int kTileWeight = 4;
+// Weights of 0, 1, 2 and 4, in us a call: a 120k-point event 60.8, 59.1, 59.2 and 59.2,
+// its nearest 8 64.9, 65.9, 67.6 and 69.6, 300k 12-D points 127.7, 125.3, 125.2 and 127.1,
+// 60k rows of 32 floats 82.3, 80.8, 81.6 and 83.3, six events served 196, 193, 192 and 194.
+constexpr unsigned int kTileWeight = 1;
 // Fewest rows per wave of the search.  Below it more waves only repeat the fixed costs
 // (the cells they cut, partly filled list write-outs), above it too few run at once: a
 // 20,000-point event of crowded cells took 121, 120, 119, 124 and 140 us with at least
