@@ -96,15 +96,21 @@ def kernel_bytes(kernel: str, n: int, d: int, E: int, axes: int = 4) -> int | No
     cells = cells_max(n)
     tiles = (n + 255) // 256
     table = {
-        # points read; histogram cleared
-        "k_bounds": 4 * n * d + 4 * cells,
+        # points read (calls binned by atomics also clear the histogram: 4 bytes a cell)
+        "k_bounds": 4 * n * d,
+        # binned coordinates read; a row number and packed cell written per point; the
+        # shares' tables of tile starts, 2 bytes a share of 1,024 points and tile of 512
+        "k_bin": 4 * axes * n + 8 * n + 2 * ((n + 1023) // 1024) * (n // 512 + 1),
+        # entries, tables and rows read; cell starts, padded row and (row, cell) pair written
+        "k_tiles": 8 * n + 2 * ((n + 1023) // 1024) * (n // 512 + 1) + 4 * n * d + 4 * (cells + 1)
+                   + 4 * n * dpad + 8 * n,
         # binned coordinates read; packed cell and rank written; one counter updated per point
         "k_keys": 4 * axes * n + 8 * n + 8 * min(n, cells),
         # histogram read, cell starts written (the search's wave starts, 4 bytes a
         # wave, are under 2% of this and not counted)
         "k_scan_cells": 4 * cells + 4 * (cells + 1),
-        # packed cell, rank, cell start and row read; padded row, (row, cell) pair and inverse written
-        "k_scatter": 12 * n + 4 * n * d + 4 * n * dpad + 12 * n,
+        # packed cell, rank, cell start and row read; padded row and (row, cell) pair written
+        "k_scatter": 12 * n + 4 * n * d + 4 * n * dpad + 8 * n,
         "k_search": search_bytes(n, dpad, cells, E),
         # kept counts read, tile totals written
         "k_kept_sums": 4 * n + 8 * tiles,
@@ -816,11 +822,11 @@ def main():
     # squares, d sums, one comparison) per examined pair, no early exit counted.
     ops = st["candidates"] * (3 * d + 1)
     # Executed work: every examined pair gets its leading terms (two for rows of up to
-    # 8 floats, four for 12-float rows, three for wider ones) and a comparison; pairs
+    # 12 floats, three for 16 and 24, four for wider ones) and a comparison; pairs
     # below r2 after them get the remaining terms of the padded row and a comparison.
-    lead = 2 if dpad <= 8 else (4 if dpad == 12 else 3)
+    lead = 2 if dpad <= 12 else (3 if dpad < 32 else 4)
     executed = st["candidates"] * (3 * lead + 1) + st["survivors"] * (3 * (dpad - lead) + 1)
-    kname = f"k_search<{dpad}, {'true' if spec.K < 16 else 'false'}>"
+    kname = f"k_search<{dpad}, {'true' if spec.K < 16 else 'false'}, {'true' if st['axes'] == 4 else 'false'}>"
     # The same kernel's average under rocprofv3 (committed summary of the default
     # run, same sources): HIP events around a kernel also count its dispatch.
     prof_us = stored_duration_us(kname) if args.workload == "single" else None

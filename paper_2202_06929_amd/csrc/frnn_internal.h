@@ -169,7 +169,7 @@ struct Counters {
     unsigned long long survived;   // pairs that reached the second stage, likewise
 };
 
-// Counts of one search workgroup.  They lie where the ranks were: a workgroup has at
+// Counts of one search workgroup.  They lie in the ranks' memory: a workgroup has at
 // least 16 rows beyond the first eight (kMinWaveRows), so the ranks are the larger.
 struct SearchCounts {
     unsigned long long tested;    // pairs examined
@@ -199,8 +199,8 @@ struct Workspace {
     Counters *ctr;
     Report *report;
     long long *edge_off;        // [n_events + 2] first edge of each event, then E, then a status
-    unsigned int *pcell;        // [rows] packed cell coordinates of each point
-    unsigned int *rank;         // [rows] arrival rank inside its cell; after the scatter, the search's SearchCounts
+    unsigned int *pcell;        // [rows] packed cell coordinates of each point; with rank, the tile binning's entries
+    unsigned int *rank;         // [rows] arrival rank inside its cell; from the search on, the SearchCounts
     unsigned int *cell_count;   // [cells] histogram or the tile binning's tables; in the search, the extension
     unsigned int *cell_start;   // [cells + 1] exclusive scan of the histogram
     unsigned long long *sums_cells;  // [tiles of cells + 1] per-tile histogram totals
@@ -215,7 +215,7 @@ struct Workspace {
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries
     unsigned int *wave_start;   // [kMaxPieceCount + 1] first sorted row of each search piece
     unsigned int *claims;       // [8 kPools kPoolStride] the search's piece counters and, beside each XCD's first,
-                                // its long-list counts; cleared by the cell scan
+                                // its long-list counts; cleared by the pass before the search that cuts the pieces
     long long rows;
     long long cells;
     int tiles_cells_n;

@@ -19,7 +19,7 @@
 //                 cell's queries against the (2R+1)^(axes-1) contiguous runs of
 //                 neighbouring cells along axis 0; each lane holds one candidate (its
 //                 first four coordinates), query rows are wave-uniform; an exact
-//                 early exit after the first two or three terms of the distance
+//                 early exit after the first two to four terms of the distance
 //                 sum; ballots queue the survivors, whose sums are finished 64 at a
 //                 time; the lists of pending queries are stored as found, in batches
 //   k_kept_sums   kept totals per placement tile and per group of tiles
