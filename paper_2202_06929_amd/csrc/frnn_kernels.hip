@@ -1852,6 +1852,59 @@ struct LongLds {
     unsigned long long prefix;
 };
 
+// Sorts R values per lane ascending, element r of lane l at position 64 r + l, by a
+// bitonic network: exchanges at distances of 64 and more stay inside a lane.  SIZE below
+// 64 sorts each group of that many lanes by itself.  FROM = SIZE runs the last stage
+// alone, which sorts values that rise and then fall.
+template <int R, int SIZE = 64 * R, int FROM = 2>
+__device__ __forceinline__ void wave_sort(unsigned int (&v)[R]) {
+    const unsigned int lane = static_cast<unsigned int>(lane_id());
+#pragma unroll
+    for (unsigned int k = FROM; k <= static_cast<unsigned int>(SIZE); k <<= 1) {
+#pragma unroll
+        for (unsigned int j = k >> 1; j > 0; j >>= 1) {
+            if (j >= 64u) {
+#pragma unroll
+                for (unsigned int r = 0; r < R; ++r) {
+                    const unsigned int o = r ^ (j / 64u);
+                    if (o > r) {
+                        const unsigned int lo = min(v[r], v[o]), hi = max(v[r], v[o]);
+                        const bool up = ((r * 64u) & k) == 0u;  // k >= 128 here
+                        v[r] = up ? lo : hi;
+                        v[o] = up ? hi : lo;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (unsigned int r = 0; r < R; ++r) {
+                    const unsigned int p = static_cast<unsigned int>(__shfl_xor(static_cast<int>(v[r]), j));
+                    const bool up = (((r * 64u) | lane) & k) == 0u || k == static_cast<unsigned int>(SIZE);
+                    const bool low = (lane & j) == 0u;
+                    v[r] = up == low ? min(v[r], p) : max(v[r], p);
+                }
+            }
+        }
+    }
+}
+
+// Loads h ids from LDS, sorts them and writes them local to their event.
+template <int R>
+__device__ __forceinline__ void wave_emit(const unsigned int *ids, unsigned int h, long long row0,
+                                          long long *__restrict__ out) {
+    unsigned int v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
+        v[r] = e < h ? ids[e] : 0xffffffffu;
+    }
+    wave_sort<R>(v);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
+        if (e < h) out[e] = static_cast<long long>(v[r]) - row0;
+    }
+}
+
 // Hit keys a long list keeps in LDS (the two window arrays of the placement pass);
 // a list with more hits is selected by enumerating its candidates again per pass.
 constexpr unsigned int kKeyCap = kPlaceWords / 2;
@@ -1863,12 +1916,14 @@ constexpr unsigned int kKeyCap = kPlaceWords / 2;
 // (the cap binds) the n_out-th smallest key is found by an MSB-first radix select
 // (8 passes of 8 bits; in each pass a scan over the 256 bin counts finds the bin
 // that holds it), over the keys in LDS or, past kKeyCap hits, by enumerating the
-// candidates again.  The kept ids are sorted by a bitonic network in LDS and
-// written, local to the query's event, to out[0, n_out).
+// candidates again.  A list below the cap keeps all its hits, whose ids alone are
+// collected.  The ids are sorted by a bitonic network whose exchanges at distances
+// below 512 stay in a wave's registers (up to 512 ids by one wave), and written, local
+// to the query's event, to out[0, n_out).
 template <int DP>
 __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restrict__ sorted_id,
                           const unsigned int *__restrict__ cell_start, const Plan &P, unsigned int cell0,
-                          unsigned int slot, float r2, unsigned int n_out, long long row0,
+                          unsigned int slot, float r2, unsigned int n_out, unsigned int K, long long row0,
                           long long *__restrict__ out, unsigned int *__restrict__ wbuf,
                           unsigned long long *__restrict__ scratch, LongLds<DP> &L) {
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(wbuf);  // [kKeyCap]
@@ -1923,20 +1978,25 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
         __syncthreads();
     };
 
-    // Every hit, keyed, into LDS (as many as fit).
+    // Every hit into LDS, keyed (as many as fit) or, below the cap, its id alone.
+    const bool all = n_out < K;
     for (unsigned int m = threadIdx.x; m < M; m += kPlaceBlock) {
         bool ok;
         const unsigned long long key = hit_key(m, ok);
         if (ok) {
             const unsigned int pos = atomicAdd(&L.fill, 1u);
-            if (pos < kKeyCap) keys[pos] = key;
+            if (all) {
+                if (pos < static_cast<unsigned int>(kMaxK)) ids[pos] = static_cast<unsigned int>(key);
+            } else if (pos < kKeyCap) {
+                keys[pos] = key;
+            }
         }
     }
     __syncthreads();
     const unsigned int h = L.fill;
     const bool in_lds = h <= kKeyCap;
     unsigned long long limit = ~0ull;  // keep hits with key <= limit
-    if (h > n_out) {
+    if (!all && h > n_out) {
         if (threadIdx.x == 0) {
             L.prefix = 0ull;
             L.left = n_out;
@@ -1967,7 +2027,9 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
     // The kept ids, compacted into LDS (keys in LDS are read into registers first,
     // since the ids overwrite them).
     constexpr int kPer = kKeyCap / kPlaceBlock;
-    if (in_lds) {
+    if (all) {
+        // already there
+    } else if (in_lds) {
         unsigned long long mine[kPer];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
@@ -2001,83 +2063,51 @@ __device__ void long_list(const SortedRows<DP> &pts, const unsigned int *__restr
     // Bitonic sort of the ids by value; slots past the ids found hold the largest
     // value (only a corrupted kept count could leave any of them in [0, n_out)).
     const unsigned int found = min(L.fill, static_cast<unsigned int>(kMaxK));
-    unsigned int size = 1;
+    constexpr unsigned int kChunk = 512;
+    static_assert(kMaxK % kChunk == 0, "whole chunks");
+    unsigned int size = kChunk;
     while (size < n_out) size <<= 1;
     for (unsigned int e = found + threadIdx.x; e < size; e += kPlaceBlock) ids[e] = 0xffffffffu;
     __syncthreads();
-    for (unsigned int k = 2; k <= size; k <<= 1) {
-        for (unsigned int j = k >> 1; j > 0; j >>= 1) {
-            for (unsigned int e = threadIdx.x; e < size; e += kPlaceBlock) {
-                const unsigned int o = e ^ j;
-                if (o > e) {
-                    const unsigned int a = ids[e], b = ids[o];
-                    const bool up = (e & k) == 0;
-                    if ((a > b) == up) {
-                        ids[e] = b;
-                        ids[o] = a;
-                    }
-                }
+    if (n_out <= kChunk) {
+        if (wave_id() == 0) {
+            if (n_out <= 64u) wave_emit<1>(ids, n_out, row0, out);
+            else if (n_out <= 128u) wave_emit<2>(ids, n_out, row0, out);
+            else if (n_out <= 256u) wave_emit<4>(ids, n_out, row0, out);
+            else wave_emit<kChunk / 64>(ids, n_out, row0, out);
+        }
+        __syncthreads();
+        return;
+    }
+    for (unsigned int k = kChunk; k <= size; k <<= 1) {
+        for (unsigned int j = k >> 1; j >= kChunk; j >>= 1) {
+            for (unsigned int p = threadIdx.x; p < size / 2; p += kPlaceBlock) {
+                const unsigned int e = 2u * (p & ~(j - 1u)) | (p & (j - 1u));  // the pair's lower place
+                const unsigned int a = ids[e], b = ids[e + j];
+                const bool up = (e & k) == 0;
+                ids[e] = up ? min(a, b) : max(a, b);
+                ids[e + j] = up ? max(a, b) : min(a, b);
             }
             __syncthreads();
         }
+        // The rest of the stage, a chunk per wave; falling chunks as their complements.
+        for (unsigned int e0 = wave_id() * kChunk; e0 < size; e0 += kWaves * kChunk) {
+            const unsigned int flip = (e0 & k) == 0 ? 0u : 0xffffffffu;
+            unsigned int v[kChunk / 64];
+#pragma unroll
+            for (int r = 0; r < static_cast<int>(kChunk / 64); ++r) v[r] = ids[e0 + 64u * r + lane_id()] ^ flip;
+            if (k == kChunk) wave_sort<kChunk / 64>(v);
+            else wave_sort<kChunk / 64, kChunk, kChunk>(v);
+#pragma unroll
+            for (int r = 0; r < static_cast<int>(kChunk / 64); ++r) ids[e0 + 64u * r + lane_id()] = v[r] ^ flip;
+        }
+        __syncthreads();
     }
     for (unsigned int t = threadIdx.x; t < n_out; t += kPlaceBlock) out[t] = static_cast<long long>(ids[t]) - row0;
     __syncthreads();
 }
 
 // The lists a single wave collects: at most kWaveKeys hits.
-
-// Sorts R values per lane ascending, element r of lane l at position 64 r + l, by a
-// bitonic network: exchanges at distances of 64 and more stay inside a lane.  SIZE below
-// 64 sorts each group of that many lanes by itself.
-template <int R, int SIZE = 64 * R>
-__device__ __forceinline__ void wave_sort(unsigned int (&v)[R]) {
-    const unsigned int lane = static_cast<unsigned int>(lane_id());
-#pragma unroll
-    for (unsigned int k = 2; k <= static_cast<unsigned int>(SIZE); k <<= 1) {
-#pragma unroll
-        for (unsigned int j = k >> 1; j > 0; j >>= 1) {
-            if (j >= 64u) {
-#pragma unroll
-                for (unsigned int r = 0; r < R; ++r) {
-                    const unsigned int o = r ^ (j / 64u);
-                    if (o > r) {
-                        const unsigned int lo = min(v[r], v[o]), hi = max(v[r], v[o]);
-                        const bool up = ((r * 64u) & k) == 0u;  // k >= 128 here
-                        v[r] = up ? lo : hi;
-                        v[o] = up ? hi : lo;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (unsigned int r = 0; r < R; ++r) {
-                    const unsigned int p = static_cast<unsigned int>(__shfl_xor(static_cast<int>(v[r]), j));
-                    const bool up = (((r * 64u) | lane) & k) == 0u || k == static_cast<unsigned int>(SIZE);
-                    const bool low = (lane & j) == 0u;
-                    v[r] = up == low ? min(v[r], p) : max(v[r], p);
-                }
-            }
-        }
-    }
-}
-
-// Loads h ids from LDS, sorts them and writes them local to their event.
-template <int R>
-__device__ __forceinline__ void wave_emit(const unsigned int *ids, unsigned int h, long long row0,
-                                          long long *__restrict__ out) {
-    unsigned int v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
-        v[r] = e < h ? ids[e] : 0xffffffffu;
-    }
-    wave_sort<R>(v);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const unsigned int e = 64u * r + static_cast<unsigned int>(lane_id());
-        if (e < h) out[e] = static_cast<long long>(v[r]) - row0;
-    }
-}
 
 // Keeps the `want` smallest of h hits by (D, id), want < h, and compacts their ids to
 // the front of ids.  The want-th smallest D is found bit by bit from the top (D >= 0,
@@ -2400,11 +2430,27 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
                         wdst[pw] = v[u] - brow;
                     }
                 }
-            } else if (is_long || is_ext) {
-                const unsigned int a0 = oq > w0 ? oq - w0 : 0u;
-                const unsigned int a1 = oq + kq > w0 ? min(oq + kq - w0, wend) : 0u;
+            }
+            // Positions of lists written elsewhere: up to kOwnSpan by the list's thread, more
+            // by its wave.  (All by the thread alone, a call with 8,000 lists of 4,000
+            // took 29.1 ms, 2.2 so; 20,000 lists of 500 1.04 and 0.51.)
+            constexpr unsigned int kOwnSpan = 128;
+            const bool other = is_long || is_ext;
+            const unsigned int a0 = other && oq > w0 ? oq - w0 : 0u;
+            const unsigned int a1 = other && oq + kq > w0 ? min(oq + kq - w0, wend) : 0u;
+            const bool wide = a1 > a0 && a1 - a0 > kOwnSpan;
+            if (!wide) {
                 for (unsigned int pw = a0; pw < a1; ++pw) {
                     wq[pw] = static_cast<unsigned char>(q);
+                    wdst[pw] = kSkip;
+                }
+            }
+            for (unsigned long long m = __builtin_amdgcn_ballot_w64(wide); m != 0ull; m &= m - 1ull) {
+                const int owner = __builtin_ctzll(m);
+                const unsigned int lo = __builtin_amdgcn_readlane(a0, owner);
+                const unsigned int hi = __builtin_amdgcn_readlane(a1, owner);
+                for (unsigned int pw = lo + lane_id(); pw < hi; pw += 64u) {
+                    wq[pw] = static_cast<unsigned char>(wave_id() * 64 + owner);
                     wdst[pw] = kSkip;
                 }
             }
@@ -2541,7 +2587,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         const int e = n_events == 1 ? 0 : find_event(ev, n_events, gi);
         const Plan P = plans[e];
         long_list<DP>(pts, sorted_id, cell_start, P, static_cast<unsigned int>(ev[e].cell0), slot, r2, nq,
-                      ev[e].row0, dst + at, wbuf, scratch, L);
+                      static_cast<unsigned int>(K), ev[e].row0, dst + at, wbuf, scratch, L);
     }
 }
 
