@@ -194,7 +194,7 @@ Workspace layout(void *base, long long rows, long long cells, int n_events, int 
     ws.long_slots = cv.take<unsigned int>(rows);
     ws.temp = cv.take<unsigned int>(static_cast<size_t>(rows) * kListCap);
     ws.wave_start = cv.take<unsigned int>(static_cast<size_t>(kMaxPieceCount) + 1);
-    ws.claims = cv.take<unsigned int>(8 * kPools * kPoolStride);
+    ws.claims = cv.take<unsigned int>(8 * kClaimStride);
     ws.rows = rows;
     ws.cells = cells;
     ws.tiles_cells_n = static_cast<int>(tiles_cells);
@@ -268,15 +268,14 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
     // rows that an XCD's resident waves work on at a time fit its L2.
     {
         const int resident = search_blocks_cached(a.dpad, K < kListCap);
-        const int pieces = search_pieces(a.dpad);
-        const long long per_piece = rows / (static_cast<long long>(resident) * kWaves * pieces);
+        const long long per_piece = rows / (static_cast<long long>(resident) * kWaves);
         long long m = per_piece / kRowsPerPiece + 1;
         if (config && config->grid_mult > 0) m = config->grid_mult;
         long long b = resident * m;
         // Small calls: at least kMinWaveRows rows per wave, and one workgroup per XCD.
         const long long most = (rows + kWaves * kMinWaveRows - 1) / (kWaves * kMinWaveRows);
         if (b > most) b = most < 8 ? 8 : most;
-        const long long room = kMaxPieceCount / (kWaves * pieces);
+        const long long room = kMaxPieceCount / kWaves;
         a.search_blocks = static_cast<int>(b > room ? room : b);
         a.search_prio = a.search_blocks <= resident ? 1 : 0;
     }

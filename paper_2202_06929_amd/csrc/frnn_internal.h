@@ -44,19 +44,7 @@ constexpr long long kMinWaveRows = 4;
 // events of 610k points in all 251, 246 and 249 us with pieces of up to 128, 32 and 16
 // rows, a 300k-point 12-D event 156.5 and 154.7 us with up to 128 and 32.
 constexpr long long kRowsPerPiece = 32;
-// The search's queries are cut into search_pieces(DP) pieces of equal work per
-// wave: each wave takes one piece of its XCD's share, then claims the share's
-// other pieces one at a time from kPools counters per XCD, so that waves that
-// finish early take work from the others.  Rows of up to 24 floats keep one piece
-// per wave: their queries cost about the same, and the claims and the cells cut
-// twice cost more than they even out (the 120k-point 8-D search took 34.9 us with
-// two pieces against 30.9 with one; whole 120k-point builds with 16- and 24-float
-// rows 0.089 and 0.120 ms against 0.085 and 0.117).  Wider rows, whose queries
-// cost more and which run fewer waves per SIMD, take two (32-, 48- and 64-float
-// rows: 0.173, 0.292 and 0.558 ms against 0.181, 0.340 and 0.713 with one).
-constexpr int search_pieces(int dpad) { return dpad <= 24 ? 1 : 2; }
-constexpr int kPools = 8;
-constexpr int kPoolStride = 32;  // counters 128 bytes apart
+constexpr int kClaimStride = 32;  // words between the XCDs' counters: 128 bytes
 constexpr int kKeysBlock = 1024;     // threads per workgroup of the key/histogram pass
 constexpr int kKeysPer = 2;          // points per thread of the key/histogram pass
 constexpr int kKeysSpan = kKeysBlock * kKeysPer;
@@ -214,8 +202,8 @@ struct Workspace {
                                 // of the XCD's rows
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries
     unsigned int *wave_start;   // [kMaxPieceCount + 1] first sorted row of each search piece
-    unsigned int *claims;       // [8 kPools kPoolStride] the search's piece counters and, beside each XCD's first,
-                                // its long-list counts; cleared by the pass before the search that cuts the pieces
+    unsigned int *claims;       // [8 kClaimStride] each XCD's counts of long lists and of extension blocks;
+                                // cleared by the pass before the search that cuts the pieces
     long long rows;
     long long cells;
     int tiles_cells_n;

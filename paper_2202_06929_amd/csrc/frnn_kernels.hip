@@ -655,9 +655,9 @@ __device__ __forceinline__ unsigned int xcd_first_block(unsigned int x, unsigned
 // out: 87 us against 30 for 60,000 points with some 45 neighbours each, 45 against 22
 // for 20,000 in denser ones, 32.4 against 27.5 for a 120k-point event where 2% of the
 // lists are long.
-constexpr int kLongCount = 1, kHugeCount = 2, kExtCount = 3;  // words of an XCD's first claim line
+constexpr int kLongCount = 1, kHugeCount = 2, kExtCount = 3;  // words of an XCD's line of counters
 __device__ __forceinline__ unsigned int *long_counter(unsigned int *claims, unsigned int xcd, int which) {
-    return claims + xcd * kPools * kPoolStride + which;
+    return claims + xcd * kClaimStride + which;
 }
 
 // floor(a / b) for a < 2^52, b > 0: the quotient rounded in double is within one
@@ -807,8 +807,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_cells(const unsigned int *__res
         }
     }
     if (blockIdx.x == 0) {
-        static_assert(8 * kPools <= kBlock && kExtCount < kPoolStride, "one claim line per thread");
-        if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
+        static_assert(kExtCount < kClaimStride, "a line per XCD");
         if (threadIdx.x < 8) {
             *long_counter(claims, threadIdx.x, kLongCount) = 0u;
             *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
@@ -1015,8 +1014,7 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     __shared__ unsigned int seg_from[kBinMaxShares];  // where the share's points of the tile lie in ents
     __shared__ uint2 scratch[2][kTWaves];
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        static_assert(8 * kPools <= kTilesBlock && kExtCount < kPoolStride, "one claim line per thread");
-        if (threadIdx.x < 8 * kPools) claims[threadIdx.x * kPoolStride] = 0u;
+        static_assert(kExtCount < kClaimStride, "a line per XCD");
         if (threadIdx.x < 8) {
             *long_counter(claims, threadIdx.x, kLongCount) = 0u;
             *long_counter(claims, threadIdx.x, kHugeCount) = 0u;
@@ -1379,33 +1377,24 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     unsigned long long tested = 0;    // pairs examined (wave-uniform, as the next)
     unsigned long long survived = 0;  // pairs that reached the second stage
 
-    // The cell scan cuts the queries, in cell order, into kPieces pieces per wave
-    // (one for rows of up to 24 floats, two for wider ones) of equal work (its
+    // The queries, in cell order, are cut into a piece per wave, of equal work (its
     // cells' fixed costs plus its queries; a piece may start or end inside a cell,
     // so a dense cell is split instead of holding up one wave).
     // Workgroups are dealt to the 8 XCDs round-robin; the workgroups of one XCD
-    // take a contiguous share of the pieces, so that they share their rows in its
-    // L2: each wave first takes one piece of the share, then claims the share's
-    // remaining pieces one at a time from one of the XCD's counters (workgroup w
-    // of the XCD uses counter w mod kPools, which hands out every kPools-th piece),
-    // so that a wave that finishes early takes work the others have not started.
-    // A wave's pieces only move forward in row order.  With one piece per wave
-    // the claims compile out.
-    constexpr int kPieces = search_pieces(DP);
+    // take a contiguous share of the pieces, so that they share their rows in its L2.
+    // (Two pieces a wave, the second claimed from counters per XCD: 60k rows of 32, 48
+    // and 64 floats 80.6, 74.3 and 88.5 us a call, 77.8, 71.3 and 86.3 with one; a
+    // 120k-point 8-D event 63.0 against 58.6.)
     const unsigned int nb = gridDim.x;
     const unsigned int xcd = blockIdx.x % 8u;
     const unsigned int xb0 = xcd_first_block(xcd, nb);
     const unsigned int xnb = xcd_first_block(xcd + 1u, nb) - xb0;  // workgroups on this XCD
     const unsigned int xblk = blockIdx.x / 8u;              // this workgroup's number on its XCD
-    const unsigned int x_first = kPieces * kWaves * xb0;    // the XCD's first piece
-    const unsigned int x_dyn = x_first + kWaves * xnb;      // its first claimed piece
-    const unsigned int x_end = x_first + kPieces * kWaves * xnb;
-    const unsigned int pools = min(static_cast<unsigned int>(kPools), xnb);
-    const unsigned int pool = xblk % pools;
-    unsigned int *claim = claims + (xcd * kPools + pool) * kPoolStride;
-    // The wave's first share and, of a single event, the plan are requested with the abort
+    const unsigned int x_first = kWaves * xb0;  // the XCD's first piece
+    const unsigned int x_end = x_first + kWaves * xnb;
+    // The wave's share and, of a single event, the plan are requested with the abort
     // flag (the shares' memory holds whatever it did when that is set).
-    unsigned int piece = x_first + xblk * kWaves + wave_id();
+    const unsigned int piece = x_first + xblk * kWaves + wave_id();
     unsigned int q_lo = wave_start[piece];
     unsigned int q_hi = wave_start[piece + 1u];
     Plan P = plans[0];
@@ -1616,118 +1605,107 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
         }
         tested += static_cast<unsigned long long>(M) * (q1 - q0);
     };
-    while (piece < x_end) {
-        // The next piece is claimed before this one is worked off, so that the claim's
-        // round trip overlaps the first loads.
-        unsigned int claimed = 0;
-        if (kPieces > 1 && lane == 0) claimed = atomicAdd(claim, 1u);
-        // The lane's query of a batch: its original row and packed cell, and the leading
-        // coordinates of its row.
-        // (16-float rows have no registers left to hold the latter ahead.)
-        constexpr bool kLeadAhead = DP != 16;
-        uint2 next = make_uint2(0u, 0u);
-        float next_lead[kLead] = {};
-        auto fetch_query = [&](unsigned int row) {
-            if (row < q_hi) {
-                next = sid[row];
-                if (kLeadAhead) {
+    // The lane's query of a batch: its original row and packed cell, and the leading
+    // coordinates of its row.
+    // (16-float rows have no registers left to hold the latter ahead.)
+    constexpr bool kLeadAhead = DP != 16;
+    uint2 next = make_uint2(0u, 0u);
+    float next_lead[kLead] = {};
+    auto fetch_query = [&](unsigned int row) {
+        if (row < q_hi) {
+            next = sid[row];
+            if (kLeadAhead) {
 #pragma unroll
-                    for (int k = 0; k < kLead; ++k) next_lead[k] = pts.lead_of(row)[k];
-                }
+                for (int k = 0; k < kLead; ++k) next_lead[k] = pts.lead_of(row)[k];
             }
+        }
+    };
+    fetch_query(q_lo + lane);
+    for (win = q_lo; win < q_hi;) {
+        if (win >= ev_end) {
+            const int e = n_events == 1 ? 0 : find_event(ev, n_events, win);
+            if (n_events > 1) P = plans[e];
+            const EventDesc E = ev[e];
+            cell0 = static_cast<unsigned int>(E.cell0);
+            ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
+            halves = FOUR || run_count(P) <= 32;
+            rl = run_lane(P, halves);
+        }
+        const unsigned int v_orig = next.x, v_pc = next.y;
+#pragma unroll
+        for (int k = 0; k < kLead; ++k)
+            lead[k] = kLeadAhead ? next_lead[k]
+                                 : pts.lead_of(min(win + lane, q_hi - 1u))[k];
+        // The lanes that start a cell, and the batch's end: after its last whole cell
+        // (a batch never crosses into the next event).
+        const unsigned int n = min(min(64u, q_hi - win), ev_end - win);
+        const unsigned int pc_before = dpp_move<kWaveShr1>(v_pc);  // with every lane active
+        const unsigned long long starts = __builtin_amdgcn_ballot_w64((v_pc != pc_before) | (lane == 0)) &
+                                          (n < 64u ? (1ull << n) - 1ull : ~0ull);
+        unsigned int nq = n;
+        if (n > static_cast<unsigned int>(kQT)) {
+            const unsigned long long ends = (starts >> 1) & ((1ull << kQT) - 1ull);  // bit b: a batch of b + 1
+            nq = ends ? 64u - static_cast<unsigned int>(__builtin_clzll(ends)) : static_cast<unsigned int>(kQT);
+        }
+        // The next batch's queries are requested before this one is worked off.
+        const unsigned int after = win + nq;
+        fetch_query(after + lane);
+        if (prio) {
+            // A SIMD issues the oldest ready wave first, so with every workgroup
+            // resident from the start the waves dispatched last finish last and
+            // the SIMD runs its final stretch with few waves.  Issue priority
+            // falls as a wave works off its share (3 in the first quarter, 0 in
+            // the last), so that waves behind are issued first and the waves of
+            // a SIMD finish closer together.
+            const unsigned int left = q_hi - win;
+            const unsigned int share = q_hi - q_lo;
+            if (4u * left > 3u * share) __builtin_amdgcn_s_setprio(3);
+            else if (4u * left > 2u * share) __builtin_amdgcn_s_setprio(2);
+            else if (4u * left > share) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
+        if (lane < kQT) qcnt[lane] = 0u;
+        if (kTailLds)
+            for (unsigned int k = lane; k < nq * kTail; k += 64u)
+                qtail[k] = pts.at(win + k / kTail, kLead + k % kTail);
+        // End of the cell that query t of the batch lies in.
+        auto cell_end = [&](unsigned int t) {
+            const unsigned long long rest = t < 63u ? starts >> (t + 1u) : 0ull;
+            const unsigned int e = rest ? t + 1u + static_cast<unsigned int>(__builtin_ctzll(rest)) : 64u;
+            return min(e, nq);
         };
-        fetch_query(q_lo + lane);
-        for (win = q_lo; win < q_hi;) {
-            if (win >= ev_end) {
-                const int e = n_events == 1 ? 0 : find_event(ev, n_events, win);
-                if (n_events > 1) P = plans[e];
-                const EventDesc E = ev[e];
-                cell0 = static_cast<unsigned int>(E.cell0);
-                ev_end = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
-                halves = FOUR || run_count(P) <= 32;
-                rl = run_lane(P, halves);
-            }
-            const unsigned int v_orig = next.x, v_pc = next.y;
-#pragma unroll
-            for (int k = 0; k < kLead; ++k)
-                lead[k] = kLeadAhead ? next_lead[k]
-                                     : pts.lead_of(min(win + lane, q_hi - 1u))[k];
-            // The lanes that start a cell, and the batch's end: after its last whole cell
-            // (a batch never crosses into the next event).
-            const unsigned int n = min(min(64u, q_hi - win), ev_end - win);
-            const unsigned int pc_before = dpp_move<kWaveShr1>(v_pc);  // with every lane active
-            const unsigned long long starts = __builtin_amdgcn_ballot_w64((v_pc != pc_before) | (lane == 0)) &
-                                              (n < 64u ? (1ull << n) - 1ull : ~0ull);
-            unsigned int nq = n;
-            if (n > static_cast<unsigned int>(kQT)) {
-                const unsigned long long ends = (starts >> 1) & ((1ull << kQT) - 1ull);  // bit b: a batch of b + 1
-                nq = ends ? 64u - static_cast<unsigned int>(__builtin_clzll(ends)) : static_cast<unsigned int>(kQT);
-            }
-            // The next batch's queries are requested before this one is worked off.
-            const unsigned int after = win + nq;
-            fetch_query(after + lane);
-            if (prio) {
-                // A SIMD issues the oldest ready wave first, so with every workgroup
-                // resident from the start the waves dispatched last finish last and
-                // the SIMD runs its final stretch with few waves.  Issue priority
-                // falls as a wave works off its share (3 in the first quarter, 0 in
-                // the last), so that waves behind are issued first and the waves of
-                // a SIMD finish closer together.
-                const unsigned int left = q_hi - win;
-                const unsigned int share = q_hi - q_lo;
-                if (4u * left > 3u * share) __builtin_amdgcn_s_setprio(3);
-                else if (4u * left > 2u * share) __builtin_amdgcn_s_setprio(2);
-                else if (4u * left > share) __builtin_amdgcn_s_setprio(1);
-                else __builtin_amdgcn_s_setprio(0);
-            }
-            if (lane < kQT) qcnt[lane] = 0u;
-            if (kTailLds)
-                for (unsigned int k = lane; k < nq * kTail; k += 64u)
-                    qtail[k] = pts.at(win + k / kTail, kLead + k % kTail);
-            // End of the cell that query t of the batch lies in.
-            auto cell_end = [&](unsigned int t) {
-                const unsigned long long rest = t < 63u ? starts >> (t + 1u) : 0ull;
-                const unsigned int e = rest ? t + 1u + static_cast<unsigned int>(__builtin_ctzll(rest)) : 64u;
-                return min(e, nq);
-            };
-            for (unsigned int t0 = 0; t0 < nq;) {
-                // The runs of this cell and, in the other half of the wave, of the next.
-                const unsigned int t1 = cell_end(t0);
-                const bool two = (FOUR || halves) && t1 < nq;
-                const unsigned int t2 = two ? cell_end(t1) : t1;
-                const unsigned int pc0 = __builtin_amdgcn_readlane(v_pc, t0);
-                const unsigned int pc1 = __builtin_amdgcn_readlane(v_pc, two ? t1 : t0);
-                const bool second = (FOUR || halves) && lane >= 32;
-                unsigned int start, pre, end;
-                wave_runs<FOUR>(second ? pc1 : pc0, cell0, P, rl, rl.live && (!second || two), FOUR || halves, cell_start, start,
-                          pre, end);
-                const unsigned long long some = map.keep(start, pre, end);
-                const unsigned int m_first = __builtin_amdgcn_readlane(end, FOUR || halves ? 31 : 63);
-                const unsigned int m_second = lane63(end);
-                map.begin(!second, pre, end, 0u);
+        for (unsigned int t0 = 0; t0 < nq;) {
+            // The runs of this cell and, in the other half of the wave, of the next.
+            const unsigned int t1 = cell_end(t0);
+            const bool two = (FOUR || halves) && t1 < nq;
+            const unsigned int t2 = two ? cell_end(t1) : t1;
+            const unsigned int pc0 = __builtin_amdgcn_readlane(v_pc, t0);
+            const unsigned int pc1 = __builtin_amdgcn_readlane(v_pc, two ? t1 : t0);
+            const bool second = (FOUR || halves) && lane >= 32;
+            unsigned int start, pre, end;
+            wave_runs<FOUR>(second ? pc1 : pc0, cell0, P, rl, rl.live && (!second || two), FOUR || halves, cell_start, start,
+                      pre, end);
+            const unsigned long long some = map.keep(start, pre, end);
+            const unsigned int m_first = __builtin_amdgcn_readlane(end, FOUR || halves ? 31 : 63);
+            const unsigned int m_second = lane63(end);
+            map.begin(!second, pre, end, 0u);
 #pragma clang loop unroll(disable)
-                for (unsigned int M = m_first, q = t0, qe = t1;;) {
-                    search_cell(q, qe, M);
-                    if (qe == t2) break;
-                    q = t1;
-                    qe = t2;
-                    M = m_second;
-                    map.begin(second, pre, end, static_cast<unsigned int>(__popcll(some & 0xffffffffull)));
-                }
-                t0 = t2;
+            for (unsigned int M = m_first, q = t0, qe = t1;;) {
+                search_cell(q, qe, M);
+                if (qe == t2) break;
+                q = t1;
+                qe = t2;
+                M = m_second;
+                map.begin(second, pre, end, static_cast<unsigned int>(__popcll(some & 0xffffffffull)));
             }
-            if (tail != head) {
-                finish_rows(head, tail - head);
-                head = tail;
-            }
-            flush(nq, v_orig);
-            win = after;
+            t0 = t2;
         }
-        piece = kPieces > 1 ? x_dyn + pool + __builtin_amdgcn_readfirstlane(claimed) * pools : x_end;
-        if (kPieces > 1 && piece < x_end) {
-            q_lo = wave_start[piece];
-            q_hi = wave_start[piece + 1u];
+        if (tail != head) {
+            finish_rows(head, tail - head);
+            head = tail;
         }
+        flush(nq, v_orig);
+        win = after;
     }
     capped = wave_sum(capped);
     if (lane == 0) {
@@ -2355,9 +2333,9 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
         rep.capped = abort ? 0u : ctr->capped;
         rep.heavy = 0u;
         for (unsigned int x = 0; x < 8u && !abort; ++x)
-            rep.heavy += long_counts[x * kPools * kPoolStride + kLongCount] +
-                         long_counts[x * kPools * kPoolStride + kHugeCount] +
-                         min(long_counts[x * kPools * kPoolStride + kExtCount], ext_cap);
+            rep.heavy += long_counts[x * kClaimStride + kLongCount] +
+                         long_counts[x * kClaimStride + kHugeCount] +
+                         min(long_counts[x * kClaimStride + kExtCount], ext_cap);
         rep.n_cells = P.n_cells;
         for (int p = 0; p < kMaxAxes; ++p) {
             rep.G[p] = P.G[p];
@@ -2485,11 +2463,11 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
     // the lists of each kind before it.
     if (threadIdx.x < 64) {
         const unsigned int x = min(threadIdx.x, 7u);
-        const unsigned int *c = long_counts + x * kPools * kPoolStride;
+        const unsigned int *c = long_counts + x * kClaimStride;
         const unsigned int n_wave = threadIdx.x < 8 ? c[kLongCount] : 0u;
         const unsigned int n_huge = threadIdx.x < 8 ? c[kHugeCount] : 0u;
-        const unsigned int first = wave_start[search_pieces(DP) * kWaves * xcd_first_block(x, search_blocks)];
-        const unsigned int last = wave_start[search_pieces(DP) * kWaves * xcd_first_block(x + 1u, search_blocks)];
+        const unsigned int first = wave_start[kWaves * xcd_first_block(x, search_blocks)];
+        const unsigned int last = wave_start[kWaves * xcd_first_block(x + 1u, search_blocks)];
         const unsigned int wave_inc = wave_scan_add(n_wave), huge_inc = wave_scan_add(n_huge);
         if (threadIdx.x < 8) {
             q_first[x] = first;
@@ -2609,7 +2587,7 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
         hipLaunchKernelGGL(k_tiles<DP>, dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events), dim3(kTilesBlock),
                            0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0, a.ev_from_arg, ws.plans,
                            bin_ents(ws), bin_table(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
-                           a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
+                           a.search_blocks * kWaves, ws.rows, ws.claims);
     else
         hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
                            a.ev_from_arg, ws.plans,
@@ -2706,7 +2684,7 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
         mark(2);
         hipLaunchKernelGGL(k_scan_cells, dim3(ws.tiles_cells_n), dim3(kBlock), 0, a.stream, ws.cell_count, ws.cells,
                            ws.sums_cells, ws.tiles_cells_n, ws.cell_start, ws.wave_start,
-                           a.search_blocks * kWaves * search_pieces(a.dpad), ws.rows, ws.claims);
+                           a.search_blocks * kWaves, ws.rows, ws.claims);
         mark(3);
     }
     switch (a.dpad) {
