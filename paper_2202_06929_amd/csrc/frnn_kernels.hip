@@ -910,6 +910,27 @@ __device__ __forceinline__ uint2 block_prefix2(uint2 v, uint2 *scratch, uint2 &t
 
 __device__ __forceinline__ int bin_shares(int n, int span) { return (n + span - 1) / span; }
 
+// The event, and the share or tile of it, that a block works on.  Grids are (blocks of
+// the largest event, n_events) as a rule.  Where most of those blocks would find nothing
+// to do (a large event among many small ones) the grid has one dimension, in which event
+// e's blocks begin at blocks_before: one for every `rows` rows before it, rounded down,
+// and `extra` for every event before it.
+__host__ __device__ __forceinline__ long long blocks_before(long long row0, long long e, int rows, int extra) {
+    return row0 / rows + e * extra;
+}
+__device__ __forceinline__ int2 event_block(const EventDesc *__restrict__ ev, int flat_events, int rows, int extra) {
+    if (flat_events == 0) return make_int2(blockIdx.y, blockIdx.x);
+    int lo = 0, hi = flat_events - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (blocks_before(ev[mid].row0, mid, rows, extra) <= static_cast<long long>(blockIdx.x)) lo = mid;
+        else hi = mid - 1;
+    }
+    return make_int2(lo, static_cast<int>(blockIdx.x - blocks_before(ev[lo].row0, lo, rows, extra)));
+}
+// Tiles of an event of n rows: 2n / tile_points of them, and at most these more.
+constexpr int kTilesExtra = 10;
+
 // Grid (shares, n_events): block (b, e) takes rows [b span, (b + 1) span) of event e.  It
 // writes each row's number and packed cell in the order of the rows' tiles to the same
 // range of ents, and where each tile starts in the share to row b of the event's table
@@ -917,22 +938,24 @@ __device__ __forceinline__ int bin_shares(int n, int span) { return (n + span - 
 template <int kPer>
 __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, float r, int cell_div,
                                                     int tile_points, const EventDesc *__restrict__ ev, EventDesc ev0, int ev_from_arg,
+                                                    int flat_events,
                                                     const BoundsPartial *__restrict__ part, int nparts,
                                                     Plan *__restrict__ plans, Counters *__restrict__ ctr,
                                                     uint2 *__restrict__ ents, unsigned short *__restrict__ table) {
     __shared__ Plan P;
     __shared__ unsigned int start[kBinMaxTiles];  // rows per tile, then where the tile starts
     __shared__ uint2 scratch[kKeysBlock / 64];
-    const int e = blockIdx.y;
-    const EventDesc E = ev_from_arg ? ev0 : ev[e];
     constexpr int kSpan = kKeysBlock * kPer;
-    if (blockIdx.x != 0 && static_cast<long long>(blockIdx.x) * kSpan >= E.n) return;
+    const int2 at = event_block(ev, flat_events, kSpan, 1);
+    const int e = at.x, share = at.y;
+    const EventDesc E = ev_from_arg ? ev0 : ev[e];
+    if (share != 0 && static_cast<long long>(share) * kSpan >= E.n) return;
     // The binned coordinates are loaded before the plan is derived so that the two
     // latencies overlap.
     float x[kPer][kMaxAxes];
 #pragma unroll
     for (int m = 0; m < kPer; ++m) {
-        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+        const int i = share * kSpan + m * kKeysBlock + threadIdx.x;
 #pragma unroll
         for (int p = 0; p < kMaxAxes; ++p) x[m][p] = 0.0f;
         if (i < E.n) {
@@ -946,7 +969,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
         derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points, &P);
     for (int t = threadIdx.x; t < kBinMaxTiles; t += kKeysBlock) start[t] = 0u;
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (share == 0 && threadIdx.x == 0) {
         plans[e] = P;
         if (P.abort) atomicOr(&ctr->abort, 1u);
     }
@@ -955,7 +978,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
     unsigned int tile[kPer], rank[kPer], pc[kPer];
 #pragma unroll
     for (int m = 0; m < kPer; ++m) {
-        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+        const int i = share * kSpan + m * kKeysBlock + threadIdx.x;
         if (i >= E.n) continue;
         int u[kMaxAxes];
 #pragma unroll
@@ -973,14 +996,14 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
     c = make_uint4(pre, pre + c.x, pre + c.x + c.y, pre + c.x + c.y + c.z);
     *reinterpret_cast<uint4 *>(start + 4 * threadIdx.x) = c;
     __syncthreads();
-    unsigned short *row = table + 2 * E.cell0 + static_cast<size_t>(blockIdx.x) * (n_tiles + 1);
+    unsigned short *row = table + 2 * E.cell0 + static_cast<size_t>(share) * (n_tiles + 1);
     for (int t = threadIdx.x; t <= n_tiles; t += kKeysBlock)
         row[t] = static_cast<unsigned short>(t < n_tiles ? start[t] : all.x);
 #pragma unroll
     for (int m = 0; m < kPer; ++m) {
-        const int i = blockIdx.x * kSpan + m * kKeysBlock + threadIdx.x;
+        const int i = share * kSpan + m * kKeysBlock + threadIdx.x;
         if (i >= E.n) continue;
-        ents[E.row0 + static_cast<long long>(blockIdx.x) * kSpan + start[tile[m]] + rank[m]] =
+        ents[E.row0 + static_cast<long long>(share) * kSpan + start[tile[m]] + rank[m]] =
             make_uint2(static_cast<unsigned int>(i), pc[m]);
     }
 }
@@ -997,7 +1020,8 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
 // the cost).
 template <int DP>
 __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span, const EventDesc *__restrict__ ev,
-                                                       EventDesc ev0, int ev_from_arg,
+                                                       EventDesc ev0, int ev_from_arg, int flat_events,
+                                                       int rows_per_tile,
                                                        const Plan *__restrict__ plans,
                                                        const uint2 *__restrict__ ents,
                                                        const unsigned short *__restrict__ table,
@@ -1022,9 +1046,10 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
         }
         if (threadIdx.x == 0) wave_start[n_pieces] = static_cast<unsigned int>(rows);
     }
-    const EventDesc E = ev_from_arg ? ev0 : ev[blockIdx.y];
-    const Plan P = plans[blockIdx.y];
-    const int t = static_cast<int>(blockIdx.x);
+    const int2 which = event_block(ev, flat_events, rows_per_tile, kTilesExtra);
+    const int t = which.y;
+    const EventDesc E = ev_from_arg ? ev0 : ev[which.x];
+    const Plan P = plans[which.x];
     if (P.abort || t >= P.n_tiles || E.n == 0) return;
     // The tile's segment of every share (one share per thread).
     static_assert(kBinMaxShares == kTilesBlock, "one share per thread");
@@ -2574,6 +2599,16 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
 uint2 *bin_ents(const Workspace &ws) { return reinterpret_cast<uint2 *>(ws.pcell); }
 unsigned short *bin_table(const Workspace &ws) { return reinterpret_cast<unsigned short *>(ws.cell_count); }
 
+// Binning through tiles in a one-dimensional grid (event_block): where the largest event
+// has more than kFlatFrom times the mean.  Whole synchronous batches, two and one
+// dimensions: 200k points with 300 events of 50 502 and 315 us (29 times the mean), 300k
+// with 20 of 20k 278 and 262 (9), 100k with 10 of 10k 148 and 141 (5.5), 200k with 3 of
+// 100k 221 and 211 (1.6), 64 events of 20k to 150k 1,370 both ways.
+constexpr long long kFlatFrom = 2;
+bool flat_grid(const LaunchArgs &a, long long rows) {
+    return a.n_events > 1 && static_cast<long long>(a.max_n) * a.n_events > kFlatFrom * rows;
+}
+
 // Launches the stages whose kernels depend on the padded row width.
 template <int DP>
 void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
@@ -2583,15 +2618,19 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const long long rows = ws.rows;
     const long long nb = (static_cast<long long>(a.max_n) + kBlock - 1) / kBlock;
     const int gs = static_cast<int>(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
-    if (a.bin_span)
-        hipLaunchKernelGGL(k_tiles<DP>, dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events), dim3(kTilesBlock),
-                           0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0, a.ev_from_arg, ws.plans,
+    if (a.bin_span) {
+        const int flat = flat_grid(a, rows) ? a.n_events : 0;
+        const dim3 grid = flat ? dim3(static_cast<unsigned int>(blocks_before(rows, a.n_events, a.tile_points / 2, kTilesExtra) + 1))
+                               : dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events);
+        hipLaunchKernelGGL(k_tiles<DP>, grid, dim3(kTilesBlock), 0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0,
+                           a.ev_from_arg, flat, a.tile_points / 2, ws.plans,
                            bin_ents(ws), bin_table(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
                            a.search_blocks * kWaves, ws.rows, ws.claims);
-    else
+    } else {
         hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
                            a.ev_from_arg, ws.plans,
                            ws.pcell, ws.rank, ws.cell_start, ws.ctr, ws.sorted, rows, ws.sorted_id);
+    }
     mark(4);
     // The extension's blocks take the memory of the histogram (or of the binning's tables),
     // read for the last time before the search: an eighth each XCD.
@@ -2665,15 +2704,17 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
                        ws.sums_cells, a.bin_span ? 0 : ws.tiles_cells_n, ws.ctr);
     mark(1);
     if (a.bin_span) {
-        const dim3 grid(static_cast<unsigned int>(a.max_n < 1 ? 1 : (a.max_n + a.bin_span - 1) / a.bin_span),
-                        a.n_events);
+        const int flat = flat_grid(a, ws.rows) ? a.n_events : 0;
+        const dim3 grid = flat ? dim3(static_cast<unsigned int>(blocks_before(ws.rows, a.n_events, a.bin_span, 1) + 1))
+                               : dim3(static_cast<unsigned int>(a.max_n < 1 ? 1 : (a.max_n + a.bin_span - 1) / a.bin_span),
+                                      a.n_events);
         if (a.bin_span == kKeysBlock)
             hipLaunchKernelGGL(k_bin<1>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
-                               ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+                               ws.ev, a.ev0, a.ev_from_arg, flat, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
                                bin_ents(ws), bin_table(ws));
         else
             hipLaunchKernelGGL(k_bin<2>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
-                               ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+                               ws.ev, a.ev0, a.ev_from_arg, flat, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
                                bin_ents(ws), bin_table(ws));
         mark(2);
         mark(3);
