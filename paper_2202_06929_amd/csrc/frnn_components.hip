@@ -229,6 +229,10 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_minhook(const long long *__rest
 // of a run of equal pairs swaps (42,000 edges lead between 1,670 pairs of trees there),
 // and a failed swap that finds the wanted parent is done.  Walking and swapping edge by
 // edge, four per lane in turn, took 17 us, and 36 against 33 on 2.4M scored edges.
+// Edges in no order of their sources (neither rising nor falling over a wave's first 64)
+// hold no such runs, and fuller waves only contend more: those are joined in turn (whole
+// calls: 1M edges of a random graph 1,020 to 1,530 us by the queue and 870 in turn, the
+// 120k-point event's edges shuffled 72.6 and 68.5; a falling path 257 and 877).
 __global__ __launch_bounds__(kCcBlock) void k_cc_hook(const long long *__restrict__ src,
                                                       const long long *__restrict__ dst, long long n_edges,
                                                       long long n, const float *__restrict__ scores,
@@ -255,11 +259,24 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_hook(const long long *__restric
             ra[j] = static_cast<unsigned int>(a);
             rb[j] = static_cast<unsigned int>(b);
         }
+        const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(ra[0]), 1));
+        const bool later = act[0] && lane != 0;
+        const bool mixed = __builtin_amdgcn_ballot_w64(later && a_prev > ra[0]) != 0ull &&
+                           __builtin_amdgcn_ballot_w64(later && a_prev < ra[0]) != 0ull;
         // Endpoints with the same parent are in one tree already: no walk to the roots.
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
             ra[j] = act[j] ? ld(parent + ra[j]) : 0u;
             rb[j] = act[j] ? ld(parent + rb[j]) : 0u;
+        }
+        if (mixed) {
+#pragma unroll
+            for (int j = 0; j < kPerLane; ++j) {
+                if (!act[j] || ra[j] == rb[j]) continue;
+                cc_find2(parent, ra[j], rb[j]);
+                if (ra[j] != rb[j]) cc_union(parent, ra[j], rb[j], state);
+            }
+            continue;
         }
         unsigned int queued = 0;
 #pragma unroll
