@@ -1,6 +1,6 @@
 """Long lists at the edges of the placement pass's own collection.
 
-A wave collects a list of up to 1,024 hits (in 1, 2, 4, 8 or 16 registers per lane)
+A wave collects a list of up to 512 hits (in 1, 2, 4 or 8 registers per lane)
 and a workgroup a larger one; with the cap binding, the nearest K are selected bit by
 bit, ties in D by id.  Clump sizes put lists at both sides of each of those widths;
 copies of one point make every distance of a list equal.  Edges against the CPU
