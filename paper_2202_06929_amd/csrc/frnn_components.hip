@@ -12,8 +12,9 @@
 //   k_cc_hook     one lane per kept edge: find both roots (plain reads: the only
 //                 writes of this kernel are the hooks, device-scope atomics that are
 //                 performed beyond the per-XCD caches and cost memory traffic), hook
-//                 the larger root under the smaller one with a compare-and-swap,
-//                 retry from the new roots if another thread hooked it first
+//                 the larger root under the smaller one with a compare-and-swap if a
+//                 device-scope load still finds it a root, retry from the new roots
+//                 if another thread hooked it first
 //   k_cc_label    label[v] = root of v (path halving); counts the roots; the last
 //                 workgroup writes the component count and the status
 // Parent pointers only ever point to smaller ids (hooks go from the larger root
@@ -24,8 +25,8 @@
 // an ancestor, because entries only ever move up the tree, so a find returns a
 // vertex of the right tree, perhaps not its current root.  Equal results therefore
 // prove two vertices share a tree.  Hooks are device-scope compare-and-swaps on
-// the presumed root; a failed one returns that vertex's current parent, a
-// strictly smaller id, and the hook resumes from there, so every retry makes
+// the presumed root; where it is none any more its current parent, a strictly
+// smaller id, is known, and the hook resumes from there, so every retry makes
 // progress on fresh data.  Path-halving stores (labeling pass) are device-scope
 // atomic stores.
 
@@ -78,13 +79,6 @@ __device__ unsigned int cc_find(unsigned int *parent, unsigned int x) {
     }
 }
 
-// Orders the LDS accesses of one wave.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Root of x by plain reads (no path halving).
 __device__ __forceinline__ unsigned int cc_root(unsigned int *parent, unsigned int x) {
     for (;;) {
@@ -125,9 +119,13 @@ __device__ void cc_find2(unsigned int *parent, unsigned int &x, unsigned int &y)
 }
 
 // Joins the trees of u and v: hooks the larger root under the smaller with a
-// compare-and-swap.  u and v need not be roots: a failed swap returns the larger
-// vertex's current parent, a strictly smaller id, and the join resumes from its
-// root, so the larger of the pair decreases every round.
+// compare-and-swap.  u and v need not be roots: where the larger one is none any more, its
+// current parent is a strictly smaller id, and the join resumes from that one's root, so
+// the larger of the pair decreases every round.  A device-scope load tells first whether
+// it is still a root: most are not where many edges join the same trees, and swaps of one
+// address wait for each other (1M edges of a random graph over 200,000 vertices, whole
+// calls: 1,020 to 1,050 us with the swap alone, 220 to 235 with the load before it, four
+// edges a lane in both; the 120k-point event's graph 44.2 and 42.6).
 __device__ void cc_union(unsigned int *parent, unsigned int u, unsigned int v, CcState *state) {
     for (unsigned int round = 0; u != v; ++round) {
         if (round >= kMaxHookRounds) {
@@ -135,12 +133,12 @@ __device__ void cc_union(unsigned int *parent, unsigned int u, unsigned int v, C
             return;
         }
         const unsigned int hi = u > v ? u : v, lo = u > v ? v : u;
-        unsigned int expected = hi;
-        if (__hip_atomic_compare_exchange_strong(parent + hi, &expected, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT))
+        unsigned int now = __hip_atomic_load(parent + hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (now == hi && __hip_atomic_compare_exchange_strong(parent + hi, &now, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT))
             return;
-        if (expected == lo) return;  // joined meanwhile, as most failed swaps find
-        u = cc_root(parent, expected);
+        if (now == lo) return;  // joined meanwhile
+        u = cc_root(parent, now);
         v = lo;
     }
 }
@@ -166,144 +164,116 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_init(unsigned int *parent, long
 // vertex is hooked at most under one neighbour, a valid union of two trees, as
 // every vertex is still a root before this pass.  Whatever this pass leaves
 // unjoined, the union-find pass joins.
-// Edges (or vertices) per lane in the hook and label passes: their loads are all
-// issued before any is used, so a wave keeps several round trips in flight.
-constexpr int kPerLane = 4;
-
 __global__ __launch_bounds__(kCcBlock) void k_cc_minhook(const long long *__restrict__ src,
                                                          const long long *__restrict__ dst, long long n_edges,
                                                          long long n, const float *__restrict__ scores,
                                                          float threshold, unsigned int *parent) {
+    constexpr unsigned int kNone = 0xffffffffu;  // past the end or out of range (reported by the hook pass)
     const int lane = static_cast<int>(threadIdx.x & 63u);
-    constexpr long long kWaveSpan = 64 * kPerLane;
-    const long long span = static_cast<long long>(kCcBlock) * kPerLane;
-    const long long stride = static_cast<long long>(gridDim.x) * span;
+    const long long stride = static_cast<long long>(gridDim.x) * kCcBlock;
     const unsigned long long below = (1ull << lane) - 1ull;
     // Wave-aligned bases, so that every lane of a wave takes the same trip count.
-    for (long long e0 = static_cast<long long>(blockIdx.x) * span + (threadIdx.x >> 6) * kWaveSpan; e0 < n_edges;
+    for (long long e0 = static_cast<long long>(blockIdx.x) * kCcBlock + (threadIdx.x & ~63u); e0 < n_edges;
          e0 += stride) {
-        constexpr unsigned int kNone = 0xffffffffu;  // past the end or out of range (reported by the hook pass)
-        unsigned int a[kPerLane], t[kPerLane];
-        bool kept[kPerLane];
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const long long e = e0 + 64 * j + lane;
-            const bool in = e < n_edges;
-            const long long x = in ? src[e] : -1, y = in ? dst[e] : -1;
-            const bool ok = x >= 0 && x < n && y >= 0 && y < n;
-            a[j] = ok ? static_cast<unsigned int>(x) : kNone;
-            t[j] = ok ? static_cast<unsigned int>(y) : kNone;
-            kept[j] = ok && !(scores && !(scores[e] > threshold));
+        const long long e = e0 + lane;
+        const bool in = e < n_edges;
+        const long long x = in ? src[e] : -1, y = in ? dst[e] : -1;
+        const bool ok = x >= 0 && x < n && y >= 0 && y < n;
+        const unsigned int a = ok ? static_cast<unsigned int>(x) : kNone;
+        const unsigned int t = ok ? static_cast<unsigned int>(y) : kNone;
+        const bool kept = ok && !(scores && !(scores[e] > threshold));
+        const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(a), 1));
+        const unsigned int t_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(t), 1));
+        const bool head = lane == 0 || a_prev != a;
+        if (__builtin_amdgcn_ballot_w64(!head && t_prev > t) == 0ull) {
+            // Targets ascend within every source, as in the graph builder's lists: a
+            // source's smallest kept target is its first.
+            const unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
+            const unsigned long long keeps = __builtin_amdgcn_ballot_w64(kept);
+            const unsigned long long run = ~0ull << (63 - __builtin_clzll(heads & (below | (1ull << lane))));
+            if (kept && (keeps & below & run) == 0ull && t < a) atomicMin(parent + a, t);
+            continue;
         }
+        // Minimum over the lanes at or after this one with the same source.
+        unsigned int m = kept ? t : kNone;
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(a[j]), 1));
-            const unsigned int t_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(t[j]), 1));
-            const bool head = lane == 0 || a_prev != a[j];
-            if (__builtin_amdgcn_ballot_w64(!head && t_prev > t[j]) == 0ull) {
-                // Targets ascend within every source, as in the graph builder's lists: a
-                // source's smallest kept target is its first.
-                const unsigned long long heads = __builtin_amdgcn_ballot_w64(head);
-                const unsigned long long keeps = __builtin_amdgcn_ballot_w64(kept[j]);
-                const unsigned long long run = ~0ull << (63 - __builtin_clzll(heads & (below | (1ull << lane))));
-                if (kept[j] && (keeps & below & run) == 0ull && t[j] < a[j]) atomicMin(parent + a[j], t[j]);
-                continue;
-            }
-            // Minimum over the lanes at or after this one with the same source.
-            unsigned int m = kept[j] ? t[j] : kNone;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned int a2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(a[j]), o));
-                const unsigned int m2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(m), o));
-                if (lane + o < 64 && a2 == a[j] && m2 < m) m = m2;
-            }
-            if (head && a[j] != kNone && m < a[j]) atomicMin(parent + a[j], m);
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int a2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(a), o));
+            const unsigned int m2 = static_cast<unsigned int>(__shfl_down(static_cast<int>(m), o));
+            if (lane + o < 64 && a2 == a && m2 < m) m = m2;
         }
+        if (head && a != kNone && m < a) atomicMin(parent + a, m);
     }
 }
 
-// Each wave takes 64 kPerLane edges at a time.  Most have endpoints with the same
-// parent (after the min-neighbour pass) and are done; the others are queued in LDS as
-// pairs of parents and joined 64 at a time, one per lane: what the pass waits for is its
-// compare-and-swaps (8.6 us without them, 15.6 with, on 1.06M edges), so only the first
-// of a run of equal pairs swaps (42,000 edges lead between 1,670 pairs of trees there),
-// and a failed swap that finds the wanted parent is done.  Walking and swapping edge by
-// edge, four per lane in turn, took 17 us, and 36 against 33 on 2.4M scored edges.
-// Edges in no order of their sources (neither rising nor falling over a wave's first 64)
-// hold no such runs, and fuller waves only contend more: those are joined in turn (whole
-// calls: 1M edges of a random graph 1,020 to 1,530 us by the queue and 870 in turn, the
-// 120k-point event's edges shuffled 72.6 and 68.5; a falling path 257 and 877).
+// One edge per lane.  Most edges' endpoints have the same parent (after the min-neighbour
+// pass) and are done; the others find their roots and join them.  What the pass waits for
+// is its chain of round trips and its swaps, so as many edges as fit are in flight at once
+// (four per lane in turn: a 120k-point event's graph of 1.06M edges 42.6 us a call
+// against 41.1, scored 52.7 and 48.5).  Joining lanes that follow each other with the same
+// two trees, as a source's edges do, leave the join to the first of them (1M edges inside
+// clusters of ten vertices 54.1 us if only lanes side by side do, 47.5 so).
+//
+// Where a lane's smaller root is the larger root of the joining lane before or after it (a
+// path's edges in either direction), hooking each under the next would build a tree as
+// deep as the path, which the labeling pass then climbs: such lanes hook under the end of
+// their chain in the wave instead, found by doubling.  Every pair is still joined: each
+// lane of a chain joins its larger root with the chain's end, and so with the root it
+// would have hooked under, which is the next lane's larger root.  A path of 200,000
+// vertices in rising order takes 58 us (890 without), in falling order 57 (890), one of
+// 100 vertices 25.6 (31.6).
+//
+// No order of the edges is singled out: 1M edges to random vertices take 175 us sorted by
+// their source and 205 unsorted.  (Edges queued per wave and joined 64 at a time from the
+// queue, with the swap alone: 1,540 and 1,040 to 1,160.)
 __global__ __launch_bounds__(kCcBlock) void k_cc_hook(const long long *__restrict__ src,
                                                       const long long *__restrict__ dst, long long n_edges,
                                                       long long n, const float *__restrict__ scores,
                                                       float threshold, unsigned int *parent, CcState *state) {
-    __shared__ uint2 queue_all[kCcBlock / 64][64 * kPerLane];
     const int lane = static_cast<int>(threadIdx.x & 63u);
-    uint2 *queue = queue_all[threadIdx.x >> 6];
-    constexpr long long kWaveSpan = 64 * kPerLane;
-    const long long span = static_cast<long long>(kCcBlock) * kPerLane;
-    const long long stride = static_cast<long long>(gridDim.x) * span;
-    for (long long e0 = static_cast<long long>(blockIdx.x) * span + (threadIdx.x >> 6) * kWaveSpan; e0 < n_edges;
+    const long long stride = static_cast<long long>(gridDim.x) * kCcBlock;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (long long e0 = static_cast<long long>(blockIdx.x) * kCcBlock + (threadIdx.x & ~63u); e0 < n_edges;
          e0 += stride) {
-        unsigned int ra[kPerLane], rb[kPerLane];
-        bool act[kPerLane];
+        const long long e = e0 + lane;
+        bool act = e < n_edges && !(scores && !(scores[e] > threshold));
+        const long long a = act ? src[e] : 0, b = act ? dst[e] : 0;
+        if (act && (a < 0 || a >= n || b < 0 || b >= n)) {
+            atomicOr(&state->status, 1u);
+            act = false;
+        }
+        unsigned int x = act ? ld(parent + a) : 0u, y = act ? ld(parent + b) : 0u;
+        if (x != y) cc_find2(parent, x, y);
+        const unsigned int hi = max(x, y);
+        unsigned int lo = min(x, y);
+        const bool join = hi != lo;
+        const unsigned long long joins = __builtin_amdgcn_ballot_w64(join);
+        if (joins == 0ull) continue;
+        // The joining lanes beside this one (itself at the ends).
+        const unsigned long long lower = joins & below, higher = joins & ~below & ~(1ull << lane);
+        const int before = lower ? 63 - __builtin_clzll(lower) : lane;
+        const int after = higher ? __builtin_ctzll(higher) : lane;
+        const unsigned int hi_before = static_cast<unsigned int>(__shfl(static_cast<int>(hi), before));
+        const unsigned int lo_before = static_cast<unsigned int>(__shfl(static_cast<int>(lo), before));
+        const unsigned int hi_after = static_cast<unsigned int>(__shfl(static_cast<int>(hi), after));
+        const bool repeated = before != lane && hi_before == hi && lo_before == lo;
+        const bool up = join && hi_before == lo;
+        const bool down = join && hi_after == lo;
+        if (__builtin_amdgcn_ballot_w64(up || down) != 0ull) {
+            int next = up ? before : (down ? after : lane);  // larger roots fall along a chain: it ends
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const long long e = e0 + 64 * j + lane;
-            act[j] = e < n_edges && !(scores && !(scores[e] > threshold));
-            const long long a = act[j] ? src[e] : 0, b = act[j] ? dst[e] : 0;
-            if (act[j] && (a < 0 || a >= n || b < 0 || b >= n)) {
-                atomicOr(&state->status, 1u);
-                act[j] = false;
+            for (int k = 0; k < 6; ++k) {
+                lo = static_cast<unsigned int>(__shfl(static_cast<int>(lo), next));
+                next = __shfl(next, next);
             }
-            ra[j] = static_cast<unsigned int>(a);
-            rb[j] = static_cast<unsigned int>(b);
         }
-        const unsigned int a_prev = static_cast<unsigned int>(__shfl_up(static_cast<int>(ra[0]), 1));
-        const bool later = act[0] && lane != 0;
-        const bool mixed = __builtin_amdgcn_ballot_w64(later && a_prev > ra[0]) != 0ull &&
-                           __builtin_amdgcn_ballot_w64(later && a_prev < ra[0]) != 0ull;
-        // Endpoints with the same parent are in one tree already: no walk to the roots.
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            ra[j] = act[j] ? ld(parent + ra[j]) : 0u;
-            rb[j] = act[j] ? ld(parent + rb[j]) : 0u;
-        }
-        if (mixed) {
-#pragma unroll
-            for (int j = 0; j < kPerLane; ++j) {
-                if (!act[j] || ra[j] == rb[j]) continue;
-                cc_find2(parent, ra[j], rb[j]);
-                if (ra[j] != rb[j]) cc_union(parent, ra[j], rb[j], state);
-            }
-            continue;
-        }
-        unsigned int queued = 0;
-#pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
-            const bool join = act[j] && ra[j] != rb[j];
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(join);
-            if (join)
-                queue[queued + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned int>(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo(static_cast<unsigned int>(m), 0u))] =
-                    make_uint2(ra[j], rb[j]);
-            queued += static_cast<unsigned int>(__popcll(m));
-        }
-        wave_lds_sync();
-        for (unsigned int q0 = 0; q0 < queued; q0 += 64u) {
-            const unsigned int q = q0 + lane;
-            uint2 r = q < queued ? queue[q] : make_uint2(0u, 0u);
-            cc_find2(parent, r.x, r.y);
-            const unsigned int hi = max(r.x, r.y), lo = min(r.x, r.y);
-            // A source's edges are neighbours in the queue and mostly lead from one tree
-            // to one other: the first of each run joins them.
-            const unsigned int hi_before = static_cast<unsigned int>(__shfl_up(static_cast<int>(hi), 1));
-            const unsigned int lo_before = static_cast<unsigned int>(__shfl_up(static_cast<int>(lo), 1));
-            if (hi != lo && (lane == 0 || hi != hi_before || lo != lo_before)) cc_union(parent, hi, lo, state);
-        }
-        wave_lds_sync();
+        if (join && !repeated) cc_union(parent, hi, lo, state);
     }
 }
+
+// Vertices per lane in the label pass: their loads are all issued before any is used, so a
+// wave keeps several round trips in flight.
+constexpr int kPerLane = 4;
 
 // Labels every vertex with its root and counts the roots; the last workgroup to
 // finish writes the caller's result [n_components, status].
@@ -378,11 +348,11 @@ int enqueue(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_v
     const long long n = n_vertices;
     hipLaunchKernelGGL(k_cc_init, dim3(grid_for(n)), dim3(kCcBlock), 0, s, parent, n, state);
     if (n_edges > 0)
-        hipLaunchKernelGGL(k_cc_minhook, dim3(grid_for((n_edges + kPerLane - 1) / kPerLane)), dim3(kCcBlock), 0, s,
+        hipLaunchKernelGGL(k_cc_minhook, dim3(grid_for(n_edges)), dim3(kCcBlock), 0, s,
                            reinterpret_cast<const long long *>(src), reinterpret_cast<const long long *>(dst),
                            static_cast<long long>(n_edges), n, scores, threshold, parent);
     if (n_edges > 0)
-        hipLaunchKernelGGL(k_cc_hook, dim3(grid_for((n_edges + kPerLane - 1) / kPerLane)), dim3(kCcBlock), 0, s,
+        hipLaunchKernelGGL(k_cc_hook, dim3(grid_for(n_edges)), dim3(kCcBlock), 0, s,
                            reinterpret_cast<const long long *>(src), reinterpret_cast<const long long *>(dst),
                            static_cast<long long>(n_edges), n, scores, threshold, parent, state);
     if (n > 0)
