@@ -75,6 +75,31 @@ constexpr int bin_tiles_bound(long long n, int tile_points) {
     return static_cast<int>(by_points > by_cells ? by_points : by_cells);
 }
 static_assert(bin_tiles_bound(kBinMaxRows, kTilePointsMin) <= kBinMaxTiles + 1, "the tiles of an event fit k_bin's LDS");
+// Tiles of many points are shared among workgroups of k_tiles: cells are of one size, so
+// that points that crowd into few of them (narrow axes beside an outlier) would leave a
+// whole event to one workgroup.  A tile of crowd_part points, eight times what a tile is
+// aimed at, or more gets a workgroup for each crowd_part of them beside its own.  Its points
+// are counted before by the shares that hold many of them (crowd_reported: three quarters
+// of the tile's mean share, so that a count comes short by less than three quarters of
+// crowd_points); ordinary tiles' shares stay below and add nothing.
+// 120k points in one tile: 581 us for the rows' stage by one workgroup, 64 in parts; the
+// whole build 782 and 257 us, of 400k points 2,490 and 1,355.
+// (tile_points is a power of two: quotients are shifts.)
+constexpr int crowd_shift(int tile_points) { return __builtin_ctz(tile_points) + 3; }
+constexpr int crowd_part(int tile_points) { return 1 << crowd_shift(tile_points); }
+constexpr int crowd_points(int tile_points, int shares) {
+    return 16 * shares > crowd_part(tile_points) ? 16 * shares : crowd_part(tile_points);
+}
+constexpr bool crowd_reported(unsigned int points, int tile_points, int shares) {
+    return (points & 0xffffu) * ((4u * shares) & 0xffffu) >= 3u * static_cast<unsigned int>(crowd_points(tile_points, shares));
+}
+// Where the counts of an event's tiles begin: an event of crowd_part rows and more has at
+// most 2n / tile_points + 1 tiles, fewer than lie before the next event's.
+constexpr long long crowd_at(long long row0, int tile_points) { return row0 >> (__builtin_ctz(tile_points) - 2); }
+// Workgroups beside a tile's own, for its count.
+constexpr int crowd_more(int counted, int tile_points, int shares) {
+    return counted >= crowd_points(tile_points, shares) ? counted >> crowd_shift(tile_points) : 0;
+}
 constexpr int kPlaceBlock = 256;     // threads per workgroup of the placement pass
 constexpr int kPlaceTile = 256;      // queries per workgroup of the placement pass (and kept tile)
 constexpr int kKeptGroup = 64;       // kept tiles per group (one workgroup of the kept-totals pass)
@@ -186,7 +211,8 @@ struct Workspace {
     BoundsPartial *part;        // [n_events * kBoundsBlocks]
     Counters *ctr;
     Report *report;
-    long long *edge_off;        // [n_events + 2] first edge of each event, then E, then a status
+    long long *edge_off;        // [n_events + 2] first edge of each event, then E, then a status; before the
+                                // search, the sums of the events' counts of crowded tiles
     unsigned int *pcell;        // [rows] packed cell coordinates of each point; with rank, the tile binning's entries
     unsigned int *rank;         // [rows] arrival rank inside its cell; from the search on, the SearchCounts
     unsigned int *cell_count;   // [cells] histogram or the tile binning's tables; in the search, the extension
@@ -197,7 +223,8 @@ struct Workspace {
     float *sorted;              // [rows, dpad] points in cell order, zero-padded rows
     unsigned int *sorted_id;    // [2 rows] per sorted row: its original row, then its packed cell
     unsigned int *kept;         // [rows] kept word per original row: the neighbours kept (| kKeptLong for a long
-                                // list), or kKeptExt, the list's block of the extension and the count
+                                // list), or kKeptExt, the list's block of the extension and the count; before
+                                // the search, the counts of crowded tiles (crowd_at)
     unsigned int *long_slots;   // [rows] sorted rows of the queries with long lists, queued per XCD in the part
                                 // of the XCD's rows
     unsigned int *temp;         // [rows * kListCap] neighbour lists of up to kListCap entries

@@ -327,19 +327,20 @@ struct BoundsAcc {
 };
 
 // Grid (bounds blocks, n_events): block (b, e) folds a share of event e's rows.
-// The first blocks also clear the histogram, tile totals and counters of the call.
+// The first blocks also clear the counters of the call and what its binning counts in: the
+// histogram and the tile totals, or the crowded tiles' counts and their sums.
 __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
                                                    int vec4, EventDesc *__restrict__ ev, EventDesc ev0,
                                                    int ev_from_arg, BoundsPartial *__restrict__ part,
-                                                   unsigned int *__restrict__ cell_count, long long cells,
-                                                   unsigned long long *__restrict__ sums_cells, int tiles_cells,
+                                                   unsigned int *__restrict__ counts, long long n_counts,
+                                                   unsigned long long *__restrict__ sums, int n_sums,
                                                    Counters *__restrict__ ctr) {
     const long long nblk = static_cast<long long>(gridDim.x) * gridDim.y;
     const long long bid = static_cast<long long>(blockIdx.y) * gridDim.x + blockIdx.x;
     const long long gtid = bid * kBlock + threadIdx.x;
     const long long gstride = nblk * kBlock;
-    for (long long c = gtid; c < cells; c += gstride) cell_count[c] = 0u;
-    for (long long c = gtid; c < tiles_cells; c += gstride) sums_cells[c] = 0ull;
+    for (long long c = gtid; c < n_counts; c += gstride) counts[c] = 0u;
+    for (long long c = gtid; c < n_sums; c += gstride) sums[c] = 0ull;
     if (gtid == 0) {
         Counters z = {};
         *ctr = z;
@@ -916,7 +917,7 @@ __device__ __forceinline__ int bin_shares(int n, int span) { return (n + span - 
 // e's blocks begin at blocks_before: one for every `rows` rows before it, rounded down,
 // and `extra` for every event before it.
 __host__ __device__ __forceinline__ long long blocks_before(long long row0, long long e, int rows, int extra) {
-    return row0 / rows + e * extra;
+    return static_cast<unsigned int>(row0) / static_cast<unsigned int>(rows) + e * extra;  // rows below 2^31
 }
 __device__ __forceinline__ int2 event_block(const EventDesc *__restrict__ ev, int flat_events, int rows, int extra) {
     if (flat_events == 0) return make_int2(blockIdx.y, blockIdx.x);
@@ -928,20 +929,29 @@ __device__ __forceinline__ int2 event_block(const EventDesc *__restrict__ ev, in
     }
     return make_int2(lo, static_cast<int>(blockIdx.x - blocks_before(ev[lo].row0, lo, rows, extra)));
 }
-// Tiles of an event of n rows: 2n / tile_points of them, and at most these more.
+// Blocks of k_tiles for an event of n rows: 2n / tile_points tiles and n / crowd_part more
+// parts of crowded ones, that is one block for every tile_block_rows rows, and at most these
+// more.
 constexpr int kTilesExtra = 10;
+__host__ __device__ constexpr int tile_block_rows(int tile_points) {
+    static_assert(crowd_part(512) == 8 * 512, "17 blocks for 8 tile_points rows");
+    return 8 * tile_points / 17;
+}
 
 // Grid (shares, n_events): block (b, e) takes rows [b span, (b + 1) span) of event e.  It
 // writes each row's number and packed cell in the order of the rows' tiles to the same
 // range of ents, and where each tile starts in the share to row b of the event's table
-// (n_tiles + 1 entries, in the event's part of the histogram's memory).
+// (n_tiles + 1 entries, in the event's part of the histogram's memory).  A tile of which
+// the share holds many points gets them added to its count (crowd_reported).
 template <int kPer>
 __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, float r, int cell_div,
                                                     int tile_points, const EventDesc *__restrict__ ev, EventDesc ev0, int ev_from_arg,
                                                     int flat_events,
                                                     const BoundsPartial *__restrict__ part, int nparts,
                                                     Plan *__restrict__ plans, Counters *__restrict__ ctr,
-                                                    uint2 *__restrict__ ents, unsigned short *__restrict__ table) {
+                                                    uint2 *__restrict__ ents, unsigned short *__restrict__ table,
+                                                    unsigned int *__restrict__ crowd,
+                                                    unsigned long long *__restrict__ crowd_sum) {
     __shared__ Plan P;
     __shared__ unsigned int start[kBinMaxTiles];  // rows per tile, then where the tile starts
     __shared__ uint2 scratch[kKeysBlock / 64];
@@ -991,6 +1001,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
     // Four consecutive tiles per thread.
     static_assert(kBinMaxTiles == 4 * kKeysBlock, "four tiles per thread");
     uint4 c = *reinterpret_cast<const uint4 *>(start + 4 * threadIdx.x);
+    const unsigned int held[4] = {c.x, c.y, c.z, c.w};
     uint2 all;
     const unsigned int pre = block_prefix2<kKeysBlock / 64>(make_uint2(c.x + c.y + c.z + c.w, 0u), scratch, all).x;
     c = make_uint4(pre, pre + c.x, pre + c.x + c.y, pre + c.x + c.y + c.z);
@@ -1006,6 +1017,20 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
         ents[E.row0 + static_cast<long long>(share) * kSpan + start[tile[m]] + rank[m]] =
             make_uint2(static_cast<unsigned int>(i), pc[m]);
     }
+    const int shares = bin_shares(E.n, kSpan);
+    const bool many = E.n >= crowd_points(tile_points, shares) &&
+                      crowd_reported(max(max(held[0], held[1]), max(held[2], held[3])), tile_points, shares);
+    if (__builtin_amdgcn_ballot_w64(many) != 0ull) {
+        unsigned int sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (many && crowd_reported(held[k], tile_points, shares)) {
+                atomicAdd(crowd + crowd_at(E.row0, tile_points) + 4 * threadIdx.x + k, held[k]);
+                sum += held[k];
+            }
+        sum = wave_sum(sum);
+        if (lane_id() == 0) atomicAdd(crowd_sum + e, static_cast<unsigned long long>(sum));
+    }
 }
 
 // Grid (tiles, n_events): block (t, e) finishes tile t of event e: its points' cells
@@ -1018,13 +1043,20 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
 // its tile it starts at the same share of the tile's weight, at the query that many
 // weight units past its cell's fixed cost (at the cell's first query if it falls within
 // the cost).
+//
+// A crowded tile (crowd_points) is worked off in parts, each the points of a run of shares:
+// part 0 by the tile's own block, the others by blocks past the event's tiles, which find
+// theirs by a prefix over the tiles' counts.  Every part counts all of the tile's points,
+// those of earlier parts apart, so that it knows where its own go in each cell.
 template <int DP>
 __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span, const EventDesc *__restrict__ ev,
                                                        EventDesc ev0, int ev_from_arg, int flat_events,
-                                                       int rows_per_tile,
+                                                       int tile_points,
                                                        const Plan *__restrict__ plans,
                                                        const uint2 *__restrict__ ents,
                                                        const unsigned short *__restrict__ table,
+                                                       const unsigned int *__restrict__ crowd,
+                                                       const unsigned long long *__restrict__ crowd_sum,
                                                        unsigned int *__restrict__ cell_start,
                                                        float *__restrict__ sorted,
                                                        unsigned int *__restrict__ sorted_id,
@@ -1033,10 +1065,11 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     constexpr int kTWaves = kTilesBlock / 64;
     constexpr int kCells = 1 << kTileShiftMax;
     __shared__ __align__(16) unsigned int cursor[kCells];  // points per cell, then where the cell starts in the tile
-    __shared__ __align__(16) unsigned int weight[kCells];  // weight before the cell in the tile
-    __shared__ unsigned int seg_pre[kBinMaxShares];   // points of the tile in the shares before
+    __shared__ __align__(16) unsigned int weight[kCells];  // weight before the cell in the tile (a part's later points first)
+    __shared__ unsigned int seg_pre[kBinMaxShares + 1];  // points of the tile in the shares before (past the last: all)
     __shared__ unsigned int seg_from[kBinMaxShares];  // where the share's points of the tile lie in ents
-    __shared__ uint2 scratch[2][kTWaves];
+    __shared__ uint2 scratch[3][kTWaves];
+    __shared__ int2 my_part;
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         static_assert(kExtCount < kClaimStride, "a line per XCD");
         if (threadIdx.x < 8) {
@@ -1046,14 +1079,41 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
         }
         if (threadIdx.x == 0) wave_start[n_pieces] = static_cast<unsigned int>(rows);
     }
-    const int2 which = event_block(ev, flat_events, rows_per_tile, kTilesExtra);
-    const int t = which.y;
+    const int2 which = event_block(ev, flat_events, tile_block_rows(tile_points), kTilesExtra);
+    int t = which.y;
     const EventDesc E = ev_from_arg ? ev0 : ev[which.x];
     const Plan P = plans[which.x];
-    if (P.abort || t >= P.n_tiles || E.n == 0) return;
+    // Points of crowded tiles: a vector load, so that only the blocks that use it at once wait.
+    const unsigned int crowded_v = static_cast<unsigned int>(
+        __hip_atomic_load(crowd_sum + which.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
+    if (P.abort || E.n == 0) return;
+    const int shares = bin_shares(E.n, span);
+    const unsigned int *__restrict__ counts = crowd + crowd_at(E.row0, tile_points);
+    int part = 0;
+    if (t >= P.n_tiles) {
+        // The x-th of the parts past the first of the event's tiles.
+        const unsigned int x = static_cast<unsigned int>(t - P.n_tiles);
+        if (x >= uniform(crowded_v) >> crowd_shift(tile_points)) return;
+        const int per = (P.n_tiles + kTilesBlock - 1) / kTilesBlock;
+        const int t0 = min(static_cast<int>(threadIdx.x) * per, P.n_tiles), t1 = min(t0 + per, P.n_tiles);
+        unsigned int more = 0;
+        for (int k = t0; k < t1; ++k) more += crowd_more(static_cast<int>(counts[k]), tile_points, shares);
+        uint2 all;
+        unsigned int before = block_prefix2<kTWaves>(make_uint2(more, 0u), scratch[2], all).x;
+        if (x >= all.x) return;
+        if (before <= x && x < before + more) {
+            for (int k = t0; k < t1; ++k) {
+                const unsigned int m = crowd_more(static_cast<int>(counts[k]), tile_points, shares);
+                if (before <= x && x < before + m) my_part = make_int2(k, static_cast<int>(x - before) + 1);
+                before += m;
+            }
+        }
+        __syncthreads();
+        t = static_cast<int>(uniform(static_cast<unsigned int>(my_part.x)));
+        part = static_cast<int>(uniform(static_cast<unsigned int>(my_part.y)));
+    }
     // The tile's segment of every share (one share per thread).
     static_assert(kBinMaxShares == kTilesBlock, "one share per thread");
-    const int shares = bin_shares(E.n, span);
     unsigned int from = 0, len = 0;
     if (static_cast<int>(threadIdx.x) < shares) {
         const unsigned short *row = table + 2 * E.cell0 + static_cast<size_t>(threadIdx.x) * (P.n_tiles + 1) + t;
@@ -1063,13 +1123,38 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     const unsigned int key0 = static_cast<unsigned int>(t) << P.tile_shift;  // the tile's first cell
     const int cells = min(1 << P.tile_shift, P.n_cells - static_cast<int>(key0));
     for (int c = threadIdx.x; c < cells; c += kTilesBlock) cursor[c] = 0u;
+    const unsigned int counted = uniform(crowded_v) ? counts[t] : 0u;
+    const int parts = crowd_more(static_cast<int>(counted), tile_points, shares) + 1;
+    const bool whole = parts == 1;
+    if (!whole)
+        for (int c = threadIdx.x; c < cells; c += kTilesBlock) weight[c] = 0u;
     uint2 sums;  // the tile's points, and the points of the event's tiles before it
     seg_pre[threadIdx.x] = block_prefix2<kTWaves>(make_uint2(len, from), scratch[0], sums).x;
     seg_from[threadIdx.x] = threadIdx.x * static_cast<unsigned int>(span) + from;
     const unsigned int n_tile = sums.x;
+    if (threadIdx.x == 0) seg_pre[kBinMaxShares] = n_tile;
     const unsigned int first_row = static_cast<unsigned int>(E.row0) + sums.y;
     __syncthreads();
     const uint2 *__restrict__ mine = ents + E.row0;
+    // The part's shares and points.
+    auto first_share = [&](int k) {  // the first share that starts at the k-th part or later
+        const unsigned int from = static_cast<unsigned int>(static_cast<unsigned long long>(n_tile) * k / parts);
+        int lo = 0, hi = shares;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (seg_pre[mid] < from) lo = mid + 1;
+            else hi = mid;
+        }
+        return lo;
+    };
+    unsigned int q_from = 0, q_to = n_tile;
+    int s_from = 0;
+    if (!whole) {
+        s_from = first_share(part);
+        const int s_to = part + 1 == parts ? shares : first_share(part + 1);
+        q_from = seg_pre[s_from];
+        q_to = seg_pre[s_to];
+    }
     // The tile's q-th point: its row in the event, and its cell in the tile.
     auto point = [&](unsigned int q, unsigned int &cell) {
         int lo = 0, hi = shares - 1;  // the last share that starts at or before it
@@ -1112,16 +1197,41 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
 #pragma unroll
     for (int m = 0; m < kHeld; ++m) {
         const unsigned int q = m * kTilesBlock + threadIdx.x;
-        if (q < n_tile) {
+        if (whole && q < n_tile) {
             held[m] = point(q, held_cell[m]);
             if (kRowsAhead) fetch(held[m], held_row[m]);
             atomicAdd(&cursor[held_cell[m]], 1u);
         }
     }
-    for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
-        unsigned int cell;
-        point(q, cell);
-        atomicAdd(&cursor[cell], 1u);
+    if (whole) {
+        for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
+            unsigned int cell;
+            point(q, cell);
+            atomicAdd(&cursor[cell], 1u);
+        }
+    } else {
+        // Sixteen lanes a share (a line of its entries), as many loads in flight as a share
+        // of a crowded tile has use for.
+        constexpr unsigned int kLanes = 16, kAhead = 8;
+        const unsigned int l = threadIdx.x % kLanes;
+        for (int s = threadIdx.x / kLanes; s < shares; s += kTilesBlock / kLanes) {
+            const unsigned int n_seg = seg_pre[s + 1] - seg_pre[s];
+            const uint2 *seg = mine + seg_from[s];
+            unsigned int *to = s < s_from ? cursor : weight;
+            for (unsigned int o = l; o < n_seg; o += kLanes * kAhead) {
+                unsigned int pc[kAhead];
+#pragma unroll
+                for (unsigned int u = 0; u < kAhead; ++u)
+                    if (o + kLanes * u < n_seg) pc[u] = seg[o + kLanes * u].y;
+#pragma unroll
+                for (unsigned int u = 0; u < kAhead; ++u) {
+                    if (o + kLanes * u >= n_seg) continue;
+                    int c[kMaxAxes];
+                    unpack_cell(pc[u], P.axes, c);
+                    atomicAdd(&to[cell_key(c, P) - key0], 1u);
+                }
+            }
+        }
     }
     __syncthreads();
     // Points and weight before each cell: consecutive cells per thread.
@@ -1129,24 +1239,26 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     const int c0 = min(static_cast<int>(threadIdx.x) * per, cells), c1 = min(c0 + per, cells);
     uint2 run = make_uint2(0u, 0u);
     for (int c = c0; c < c1; ++c) {
-        const unsigned int v = cursor[c];
+        const unsigned int v = cursor[c] + (whole ? 0u : weight[c]);
         run.x += v;
         run.y += v + (v ? kTileWeight : 0u);
     }
     uint2 all;
     run = block_prefix2<kTWaves>(run, scratch[1], all);
     for (int c = c0; c < c1; ++c) {
-        const unsigned int v = cursor[c];
-        cursor[c] = run.x;
+        const unsigned int first = cursor[c], v = first + (whole ? 0u : weight[c]);
+        cursor[c] = run.x + (whole ? 0u : first);  // past the points of earlier parts
         weight[c] = run.y;
         run.x += v;
         run.y += v + (v ? kTileWeight : 0u);
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < cells; c += kTilesBlock) cell_start[E.cell0 + key0 + c] = first_row + cursor[c];
-    if (t == P.n_tiles - 1 && threadIdx.x == 0)
-        cell_start[E.cell0 + P.n_cells] = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
-    if (n_tile) {
+    if (part == 0) {
+        for (int c = threadIdx.x; c < cells; c += kTilesBlock) cell_start[E.cell0 + key0 + c] = first_row + cursor[c];
+        if (t == P.n_tiles - 1 && threadIdx.x == 0)
+            cell_start[E.cell0 + P.n_cells] = static_cast<unsigned int>(E.row0) + static_cast<unsigned int>(E.n);
+    }
+    if (n_tile && part == 0) {
         // Pieces k with first_row <= k rows / n_pieces < first_row + n_tile.
         const unsigned long long np = static_cast<unsigned long long>(n_pieces);
         const unsigned long long R = static_cast<unsigned long long>(rows);
@@ -1177,11 +1289,11 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     };
 #pragma unroll
     for (int m = 0; m < kHeld; ++m)
-        if (m * kTilesBlock + threadIdx.x < n_tile) {
+        if (whole && m * kTilesBlock + threadIdx.x < n_tile) {
             if (!kRowsAhead) fetch(held[m], held_row[kRowsAhead ? m : 0]);
             place(held[m], held_cell[m], held_row[kRowsAhead ? m : 0]);
         }
-    for (unsigned int q = kHeld * kTilesBlock + threadIdx.x; q < n_tile; q += kTilesBlock) {
+    for (unsigned int q = (whole ? kHeld * kTilesBlock : q_from) + threadIdx.x; q < q_to; q += kTilesBlock) {
         unsigned int cell;
         const uint2 x = point(q, cell);
         float row[DP];
@@ -2598,6 +2710,8 @@ __global__ __launch_bounds__(kPlaceBlock) void k_place(long long rows, const Eve
 // cells and ranks lie (next to each other), the tables in the histogram.
 uint2 *bin_ents(const Workspace &ws) { return reinterpret_cast<uint2 *>(ws.pcell); }
 unsigned short *bin_table(const Workspace &ws) { return reinterpret_cast<unsigned short *>(ws.cell_count); }
+unsigned int *crowd_counts(const Workspace &ws) { return ws.kept; }
+unsigned long long *crowd_sums(const Workspace &ws) { return reinterpret_cast<unsigned long long *>(ws.edge_off); }
 
 // Binning through tiles in a one-dimensional grid (event_block): where the largest event
 // has more than kFlatFrom times the mean.  Whole synchronous batches, two and one
@@ -2620,11 +2734,12 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const int gs = static_cast<int>(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
     if (a.bin_span) {
         const int flat = flat_grid(a, rows) ? a.n_events : 0;
-        const dim3 grid = flat ? dim3(static_cast<unsigned int>(blocks_before(rows, a.n_events, a.tile_points / 2, kTilesExtra) + 1))
-                               : dim3(bin_tiles_bound(a.max_n, a.tile_points), a.n_events);
+        const dim3 grid = flat ? dim3(static_cast<unsigned int>(
+                                     blocks_before(rows, a.n_events, tile_block_rows(a.tile_points), kTilesExtra) + 1))
+                               : dim3(bin_tiles_bound(a.max_n, a.tile_points) + a.max_n / crowd_part(a.tile_points), a.n_events);
         hipLaunchKernelGGL(k_tiles<DP>, grid, dim3(kTilesBlock), 0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0,
-                           a.ev_from_arg, flat, a.tile_points / 2, ws.plans,
-                           bin_ents(ws), bin_table(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
+                           a.ev_from_arg, flat, a.tile_points, ws.plans,
+                           bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
                            a.search_blocks * kWaves, ws.rows, ws.claims);
     } else {
         hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
@@ -2698,10 +2813,14 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
     Dims dd;
     for (int p = 0; p < kMaxAxes; ++p) dd.c[p] = p < a.axes ? a.dims[p] : -1;
     mark(0);
-    // The histogram and its tile totals are cleared for the binning by atomics alone.
-    hipLaunchKernelGGL(k_bounds, dim3(a.bounds_blocks, a.n_events), dim3(kBlock), 0, a.stream, a.d, dd, vec4,
-                       ws.ev, a.ev0, a.ev_from_arg, ws.part, ws.cell_count, a.bin_span ? 0ll : ws.cells,
-                       ws.sums_cells, a.bin_span ? 0 : ws.tiles_cells_n, ws.ctr);
+    if (a.bin_span)
+        hipLaunchKernelGGL(k_bounds, dim3(a.bounds_blocks, a.n_events), dim3(kBlock), 0, a.stream, a.d, dd, vec4,
+                           ws.ev, a.ev0, a.ev_from_arg, ws.part, crowd_counts(ws), crowd_at(ws.rows, a.tile_points) + 1,
+                           crowd_sums(ws), a.n_events, ws.ctr);
+    else
+        hipLaunchKernelGGL(k_bounds, dim3(a.bounds_blocks, a.n_events), dim3(kBlock), 0, a.stream, a.d, dd, vec4,
+                           ws.ev, a.ev0, a.ev_from_arg, ws.part, ws.cell_count, ws.cells, ws.sums_cells,
+                           ws.tiles_cells_n, ws.ctr);
     mark(1);
     if (a.bin_span) {
         const int flat = flat_grid(a, ws.rows) ? a.n_events : 0;
@@ -2711,11 +2830,11 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
         if (a.bin_span == kKeysBlock)
             hipLaunchKernelGGL(k_bin<1>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
                                ws.ev, a.ev0, a.ev_from_arg, flat, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
-                               bin_ents(ws), bin_table(ws));
+                               bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws));
         else
             hipLaunchKernelGGL(k_bin<2>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
                                ws.ev, a.ev0, a.ev_from_arg, flat, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
-                               bin_ents(ws), bin_table(ws));
+                               bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws));
         mark(2);
         mark(3);
     } else {
