@@ -49,7 +49,10 @@ constexpr int kKeysBlock = 1024;     // threads per workgroup of the key/histogr
 constexpr int kKeysPer = 2;          // points per thread of the key/histogram pass
 constexpr int kKeysSpan = kKeysBlock * kKeysPer;
 // Binning through tiles (k_bin, k_tiles), for calls whose largest event has at most
-// kBinMaxRows rows: shares of kKeysBlock or twice as many rows, at most kBinMaxShares an
+// kBinMaxRows rows, which is what the tables hold (a share per thread of k_tiles, two rows
+// per thread of k_bin), not where the other binning overtakes it: whole builds of 2^20 rows
+// of 3, 8, 12 and 32 floats 200, 286, 416 and 1,652 us through tiles and 250, 338, 467 and
+// 1,726 by atomics, of one row more 252, 338, 476 and 1,737 (by atomics).  Shares of kKeysBlock or twice as many rows, at most kBinMaxShares an
 // event; tiles of up to 2^kTileShiftMax cells and, on average, at most kTilePointsMin
 // points: fewer leave the shares' segments of a tile too short, more too few tiles for
 // the CUs (120k points: whole build 64.9, 65.3, 66.5 and 70.7 us with 256, 512, 1024 and

@@ -880,14 +880,14 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int d, int vec4, const Event
 // memory per point: k_bin sorts each share of points by tile (a run of cells) in LDS, and
 // k_tiles gathers one tile's points from all shares, counts and orders them by cell in
 // LDS and writes rows, cell starts and search shares.  By atomics (k_keys, k_scan_cells,
-// k_scatter: larger events, whose shares would hold too few points of each of their many
-// tiles) every point takes a returning atomic beyond its XCD's L2 and its row is written
-// to a place that shares its lines with rows of other XCDs.  One 120k-point event: 13.7,
-// 5.1 and 6.9 us by atomics, 8.5 and 10.5 through tiles; 300k 12-D points: 22.0, 5.6 and
-// 14.7 against 10.1 and 19.3; a batch of 64 events (5.6M points): 240, 34 and 217 against
-// 92 and 198, where k_tiles is bound by memory (1.1 GB at 5.4 TB/s: a line of points holds
-// the rows of several tiles and is fetched for each; giving each event's tiles to one XCD
-// took 235 us, the XCDs' shares being uneven).
+// k_scatter: events beyond what the tiles' tables hold, see kBinMaxRows) every point takes
+// a returning atomic beyond its XCD's L2 and its row is written to a place that shares its
+// lines with rows of other XCDs.  One 120k-point event: 13.7, 5.1 and 6.9 us by atomics,
+// 8.5 and 10.5 through tiles; 300k 12-D points: 22.0, 5.6 and 14.7 against 10.1 and 19.3; a
+// batch of 64 events (5.6M points): 240, 34 and 217 against 92 and 198, where k_tiles is
+// bound by memory (1.1 GB at 5.4 TB/s: a line of points holds the rows of several tiles
+// and is fetched for each; giving each event's tiles to one XCD took 235 us, the XCDs'
+// shares being uneven).
 
 // Exclusive prefixes over the block in thread order of two values, and the block's totals
 // of both, for a block of WAVES waves, with one barrier (scratch belongs to this call).
