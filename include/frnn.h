@@ -92,8 +92,8 @@ enum frnn_stage {
     FRNN_STAGE_BOUNDS = 0,   /* bounds of the binned coordinates, non-finite check */
     FRNN_STAGE_KEYS = 1,     /* grid plan, cell keys; points sorted by tile, or the
                                 histogram where the largest event has over 2^20 points */
-    FRNN_STAGE_CELLS = 2,    /* scan of the histogram (no kernel where points were
-                                sorted by tile) */
+    FRNN_STAGE_CELLS = 2,    /* scan of the histogram (no kernel, and 0, where points
+                                were sorted by tile) */
     FRNN_STAGE_SCATTER = 3,  /* rows copied into cell order (tiles: cell starts too) */
     FRNN_STAGE_SEARCH = 4,   /* neighbour-cell search */
     FRNN_STAGE_TOTALS = 5,   /* kept neighbours per tile of 256 queries */

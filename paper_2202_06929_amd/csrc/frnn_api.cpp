@@ -310,7 +310,7 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
     return FRNN_OK;
 }
 
-int report_status(const Report &rep, frnn_stats *stats, bool timing, int64_t edge_capacity);
+int report_status(const Report &rep, frnn_stats *stats, bool timing, bool tiles, int64_t edge_capacity);
 
 // Enqueues, copies the report (and the per-event edge ranges) back and waits.
 int run(const EventDesc *descs, int n_events, long long rows, long long cells, int max_n,
@@ -345,11 +345,12 @@ int run(const EventDesc *descs, int n_events, long long rows, long long cells, i
     if (hipStreamSynchronize(stream) != hipSuccess) return FRNN_ERR_HIP;
     std::atomic_thread_fence(std::memory_order_acquire);
     memcpy(rep_out, t_report, sizeof(Report));
-    return report_status(*rep_out, stats, timing, edge_capacity);
+    return report_status(*rep_out, stats, timing, bin_span_for(max_n) != 0, edge_capacity);
 }
 
-// Status of a finished call from its report; fills the stats.
-int report_status(const Report &rep, frnn_stats *stats, bool timing, int64_t edge_capacity) {
+// Status of a finished call from its report; fills the stats.  A call binned through tiles
+// has no kernel in FRNN_STAGE_CELLS, and no event before FRNN_STAGE_SCATTER.
+int report_status(const Report &rep, frnn_stats *stats, bool timing, bool tiles, int64_t edge_capacity) {
     if (rep.n_edges < 0) return FRNN_ERR_HIP;  // the report never arrived
     if (stats) {
         stats->n_edges = rep.n_edges;
@@ -363,9 +364,12 @@ int report_status(const Report &rep, frnn_stats *stats, bool timing, int64_t edg
         stats->capped_queries = static_cast<int32_t>(rep.capped);
         stats->overflow_queries = static_cast<int32_t>(rep.heavy);
         if (timing)
-            for (int k = 0; k < FRNN_STAGES; ++k)
-                if (hipEventElapsedTime(&stats->stage_ms[k], t_events[k], t_events[k + 1]) != hipSuccess)
+            for (int k = 0; k < FRNN_STAGES; ++k) {
+                if (tiles && k == FRNN_STAGE_CELLS) continue;  // stays 0
+                const int from = tiles && k == FRNN_STAGE_SCATTER ? FRNN_STAGE_CELLS : k;
+                if (hipEventElapsedTime(&stats->stage_ms[k], t_events[from], t_events[k + 1]) != hipSuccess)
                     return FRNN_ERR_HIP;
+            }
     }
     if (rep.abort) return FRNN_ERR_NONFINITE;
     if (rep.n_edges > edge_capacity) return FRNN_ERR_CAPACITY;
@@ -599,7 +603,7 @@ extern "C" int frnn_build_noalloc(const float *points, int64_t n, int32_t d, flo
     if (hipMemcpyAsync(&rep, ws.report, sizeof(Report), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return FRNN_ERR_HIP;
-    const int rs = report_status(rep, stats, false, edge_capacity);
+    const int rs = report_status(rep, stats, false, false, edge_capacity);
     if (rs == FRNN_OK || rs == FRNN_ERR_CAPACITY) *n_edges = rep.n_edges;
     return rs;
 }

@@ -267,7 +267,8 @@ struct LaunchArgs {
     long long *src;
     long long *dst;
     hipStream_t stream;
-    hipEvent_t *events;     // 8 events bracketing the 7 stages, or null
+    hipEvent_t *events;     // 8 events bracketing the 7 stages (without the one before the scatter when
+                            // points are binned through tiles), or null
     int search_blocks;      // resident workgroups of the search kernel
     int search_prio;        // 1: the search grid is one round of resident workgroups
     int bounds_blocks;      // bounds partials per event (<= kBoundsBlocks)

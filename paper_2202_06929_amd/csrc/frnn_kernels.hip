@@ -2835,8 +2835,7 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
             hipLaunchKernelGGL(k_bin<2>, grid, dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes, a.r, a.cell_div, a.tile_points,
                                ws.ev, a.ev0, a.ev_from_arg, flat, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
                                bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws));
-        mark(2);
-        mark(3);
+        mark(2);  // there is no stage 2: stage 3 begins here
     } else {
         hipLaunchKernelGGL(k_keys, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
                            a.r, a.cell_div, a.tile_points, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
