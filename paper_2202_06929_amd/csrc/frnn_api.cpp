@@ -141,8 +141,7 @@ int upload_events(const EventDesc *descs, int n_events, EventDesc *dev, hipStrea
     return FRNN_OK;
 }
 
-thread_local Report *t_report = nullptr;    // pinned host copy of the device report
-thread_local Report *t_report_dev = nullptr;  // its device-visible address (null: copy instead)
+thread_local MappedResult t_report;  // the device report
 thread_local hipEvent_t t_events[FRNN_STAGES + 1] = {};
 thread_local bool t_events_ready = false;
 
@@ -319,24 +318,16 @@ int run(const EventDesc *descs, int n_events, long long rows, long long cells, i
         int64_t *edge_offsets_host) {
     // The last kernel writes the report straight into pinned host memory when the
     // runtime maps it for the device; otherwise it is copied back.
-    if (!t_report) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(Report), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            if (hipHostMalloc(&p, sizeof(Report), hipHostMallocDefault) != hipSuccess) return FRNN_ERR_HIP;
-        } else {
-            void *dp = nullptr;
-            if (hipHostGetDevicePointer(&dp, p, 0) == hipSuccess) t_report_dev = static_cast<Report *>(dp);
-        }
-        t_report = static_cast<Report *>(p);
-    }
+    if (!t_report.ready(sizeof(Report))) return FRNN_ERR_HIP;
+    Report *const report = static_cast<Report *>(t_report.host);
     Workspace ws;
     bool timing = false;
-    t_report->n_edges = -1;
+    report->n_edges = -1;
     const int st = enqueue(descs, n_events, rows, cells, max_n, d, r, K, workspace, src, dst, edge_capacity,
-                           config, stream, true, nullptr, &ws, &timing, t_report_dev);
+                           config, stream, true, nullptr, &ws, &timing, static_cast<Report *>(t_report.dev));
     if (st != FRNN_OK) return st;
-    if (!t_report_dev &&
-        hipMemcpyAsync(t_report, ws.report, sizeof(Report), hipMemcpyDeviceToHost, stream) != hipSuccess)
+    if (!t_report.dev &&
+        hipMemcpyAsync(report, ws.report, sizeof(Report), hipMemcpyDeviceToHost, stream) != hipSuccess)
         return FRNN_ERR_HIP;
     if (edge_offsets_host &&
         hipMemcpyAsync(edge_offsets_host, ws.edge_off, sizeof(long long) * (n_events + 1), hipMemcpyDeviceToHost,
@@ -344,7 +335,7 @@ int run(const EventDesc *descs, int n_events, long long rows, long long cells, i
         return FRNN_ERR_HIP;
     if (hipStreamSynchronize(stream) != hipSuccess) return FRNN_ERR_HIP;
     std::atomic_thread_fence(std::memory_order_acquire);
-    memcpy(rep_out, t_report, sizeof(Report));
+    memcpy(rep_out, report, sizeof(Report));
     return report_status(*rep_out, stats, timing, bin_span_for(max_n) != 0, edge_capacity);
 }
 

@@ -37,6 +37,7 @@
 #include <atomic>
 
 #include "frnn.h"
+#include "frnn_internal.h"
 
 namespace {
 
@@ -363,8 +364,7 @@ int enqueue(const int64_t *src, const int64_t *dst, int64_t n_edges, int64_t n_v
     return hipGetLastError() == hipSuccess ? FRNN_OK : FRNN_ERR_HIP;
 }
 
-thread_local long long *t_result = nullptr;      // pinned host copy of [n_components, status]
-thread_local long long *t_result_dev = nullptr;  // its device-visible address (null: copy instead)
+thread_local frnn::MappedResult t_result;  // [n_components, status]
 
 }  // namespace
 
@@ -393,28 +393,20 @@ extern "C" int frnn_components(const int64_t *src, const int64_t *dst, int64_t n
     // The last kernel writes the result straight into pinned host memory when the runtime
     // maps it for the device (a copy enqueued behind the kernels took several us);
     // otherwise it is copied back.
-    if (!t_result) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, 2 * sizeof(long long), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            if (hipHostMalloc(&p, 2 * sizeof(long long), hipHostMallocDefault) != hipSuccess) return FRNN_ERR_HIP;
-        } else {
-            void *dp = nullptr;
-            if (hipHostGetDevicePointer(&dp, p, 0) == hipSuccess) t_result_dev = static_cast<long long *>(dp);
-        }
-        t_result = static_cast<long long *>(p);
-    }
-    int64_t *result_device =
-        t_result_dev ? reinterpret_cast<int64_t *>(t_result_dev)
-                     : reinterpret_cast<int64_t *>(static_cast<char *>(workspace) + 256 +
-                                                   align256(sizeof(unsigned int) * static_cast<size_t>(n_vertices)));
-    t_result[1] = FRNN_ERR_HIP;  // until the result arrives
+    if (!t_result.ready(2 * sizeof(long long))) return FRNN_ERR_HIP;
+    long long *const result = static_cast<long long *>(t_result.host);
+    int64_t *result_device = t_result.dev ? static_cast<int64_t *>(t_result.dev)
+                                          : reinterpret_cast<int64_t *>(
+                                                static_cast<char *>(workspace) + 256 +
+                                                align256(sizeof(unsigned int) * static_cast<size_t>(n_vertices)));
+    result[1] = FRNN_ERR_HIP;  // until the result arrives
     const int e = enqueue(src, dst, n_edges, n_vertices, scores, threshold, workspace, labels, result_device, s);
     if (e != FRNN_OK) return e;
-    if (!t_result_dev &&
-        hipMemcpyAsync(t_result, result_device, 2 * sizeof(long long), hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (!t_result.dev &&
+        hipMemcpyAsync(result, result_device, 2 * sizeof(long long), hipMemcpyDeviceToHost, s) != hipSuccess)
         return FRNN_ERR_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return FRNN_ERR_HIP;
     std::atomic_thread_fence(std::memory_order_acquire);
-    if (n_components) *n_components = t_result[0];
-    return static_cast<int>(t_result[1]);
+    if (n_components) *n_components = result[0];
+    return static_cast<int>(result[1]);
 }

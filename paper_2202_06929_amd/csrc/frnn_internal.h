@@ -251,6 +251,41 @@ long long describe_events(const int64_t *event_offsets, int n_events, EventDesc 
 // Workspace layout for events of the given sizes (host arithmetic; base may be null).
 Workspace layout(void *base, long long rows, long long cells, int n_events, int d, int64_t edge_capacity);
 
+// Pinned host memory that the kernels of a call write its result into; one per calling
+// thread, so it serves whichever device is current in a call: it is portable, and its
+// address is asked for again when another device is.
+struct MappedResult {
+    void *host = nullptr;
+    void *dev = nullptr;  // the current device's address, or null (the result is copied back)
+    int device = -1;      // the device that dev belongs to
+    bool mapped = false;
+    // For the current device; false if there is no pinned memory.
+    bool ready(size_t bytes) {
+        if (!host) {
+            mapped = hipHostMalloc(&host, bytes, hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable) ==
+                     hipSuccess;
+            if (!mapped) {
+                (void)hipGetLastError();
+                host = nullptr;
+                if (hipHostMalloc(&host, bytes, hipHostMallocPortable) != hipSuccess) {
+                    host = nullptr;
+                    return false;
+                }
+            }
+        }
+        int now = 0;
+        if (hipGetDevice(&now) != hipSuccess) return false;
+        if (mapped && now != device) {
+            if (hipHostGetDevicePointer(&dev, host, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                dev = nullptr;
+            }
+            device = now;
+        }
+        return true;
+    }
+};
+
 struct LaunchArgs {
     int vec4;           // every event's rows are 16-byte aligned float4 groups (d % 4 == 0)
     int n_events;
