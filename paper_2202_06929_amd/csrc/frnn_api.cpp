@@ -81,18 +81,18 @@ bool config_ok(const frnn_config *c, int d) {
     return true;
 }
 
-// Resident search workgroups per (device, padded width), computed once.
+// Resident search workgroups per (device, search kernel), computed once.
 std::mutex g_blocks_mu;
 std::map<std::pair<int, int>, int> g_blocks;
 
-int search_blocks_cached(int dpad, bool sel) {
+int search_blocks_cached(int dpad, bool sel, bool four) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    const int key = dpad * 2 + (sel ? 1 : 0);
+    const int key = dpad * 4 + (sel ? 2 : 0) + (four ? 1 : 0);
     std::lock_guard<std::mutex> lock(g_blocks_mu);
     auto it = g_blocks.find({dev, key});
     if (it != g_blocks.end()) return it->second;
-    int b = search_blocks_for(dpad, sel);
+    int b = search_blocks_for(dpad, sel, four);
     g_blocks[{dev, key}] = b;
     return b;
 }
@@ -266,7 +266,7 @@ int enqueue(const EventDesc *descs, int n_events, long long rows, long long cell
     // hardware hands the remaining shares to whichever workgroups finish first, and the
     // rows that an XCD's resident waves work on at a time fit its L2.
     {
-        const int resident = search_blocks_cached(a.dpad, K < kListCap);
+        const int resident = search_blocks_cached(a.dpad, K < kListCap, axes == 4);
         const long long per_piece = rows / (static_cast<long long>(resident) * kWaves);
         long long m = per_piece / kRowsPerPiece + 1;
         if (config && config->grid_mult > 0) m = config->grid_mult;
@@ -550,10 +550,9 @@ int noalloc_workspace(void **out) {
         void *ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return FRNN_ERR_HIP;
         if (reinterpret_cast<uintptr_t>(ptr) % 256 != 0) return FRNN_ERR_HIP;
-        for (int dp : {4, 8, 12, 16, 24, 32, 48, 64}) {
-            search_blocks_cached(dp, false);
-            search_blocks_cached(dp, true);
-        }
+        for (int dp : {4, 8, 12, 16, 24, 32, 48, 64})
+            for (bool sel : {false, true})
+                for (bool four : {false, true}) search_blocks_cached(dp, sel, four);
         g_noalloc_ptr[dev] = ptr;
     }
     *out = g_noalloc_ptr[dev];

@@ -320,7 +320,7 @@ struct LaunchArgs {
 hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws);
 
 // Resident workgroups of the search kernel for rows padded to dpad (current device);
-// sel: the variant for K below the list size.
-int search_blocks_for(int dpad, bool sel);
+// sel: the variant for K below the list size, four: for four binned axes.
+int search_blocks_for(int dpad, bool sel, bool four);
 
 }  // namespace frnn

@@ -2775,12 +2775,11 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
 }
 
 template <int DP>
-int occupancy_blocks(bool sel) {
+int occupancy_blocks(bool sel, bool four) {
+    const auto kernel = sel ? (four ? k_search<DP, true, true> : k_search<DP, true, false>)
+                            : (four ? k_search<DP, false, true> : k_search<DP, false, false>);
     int per_cu = 0;
-    const hipError_t e = sel ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, true, true>, kBlock, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_search<DP, false, true>, kBlock, 0);
-    if (e != hipSuccess || per_cu < 1)
-        per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -2790,16 +2789,16 @@ int occupancy_blocks(bool sel) {
 
 }  // namespace
 
-int search_blocks_for(int dpad, bool sel) {
+int search_blocks_for(int dpad, bool sel, bool four) {
     switch (dpad) {
-        case 4: return occupancy_blocks<4>(sel);
-        case 8: return occupancy_blocks<8>(sel);
-        case 12: return occupancy_blocks<12>(sel);
-        case 16: return occupancy_blocks<16>(sel);
-        case 24: return occupancy_blocks<24>(sel);
-        case 32: return occupancy_blocks<32>(sel);
-        case 48: return occupancy_blocks<48>(sel);
-        default: return occupancy_blocks<64>(sel);
+        case 4: return occupancy_blocks<4>(sel, four);
+        case 8: return occupancy_blocks<8>(sel, four);
+        case 12: return occupancy_blocks<12>(sel, four);
+        case 16: return occupancy_blocks<16>(sel, four);
+        case 24: return occupancy_blocks<24>(sel, four);
+        case 32: return occupancy_blocks<32>(sel, four);
+        case 48: return occupancy_blocks<48>(sel, four);
+        default: return occupancy_blocks<64>(sel, four);
     }
 }
 

@@ -3,7 +3,7 @@
  * memory.  The kernel whose mangled name contains fake_kernel gets the address that it
  * writes the result to as argument number fake_arg; a synchronisation "runs" it, and the
  * result arrives only if that is the current device's address (or by a copy to the host,
- * where mapping fails). */
+ * where mapping fails).  The names of search kernels are kept for tests of the launch. */
 #include <stddef.h>
 #include <stdlib.h>
 #include <string.h>
@@ -11,6 +11,7 @@
 int fake_device, fake_arg, fake_map_fails, fake_copies;
 unsigned fake_flags;
 char fake_kernel[64], fake_result[128];
+char fake_asked[256], fake_searched[256]; /* search kernels: asked for its occupancy, launched last */
 
 typedef struct {
     unsigned x, y, z;
@@ -20,6 +21,17 @@ static char *host;
 static size_t host_bytes;
 static const void *wanted;
 static void *written;
+
+static struct {
+    const void *f;
+    char name[256];
+} searches[256];
+static int n_searches;
+
+static void name_of(const void *f, char *name) {
+    for (int k = 0; k < n_searches; ++k)
+        if (searches[k].f == f) strcpy(name, searches[k].name);
+}
 
 static char *address(int device) { return host + (size_t)(device + 1) * 4096; }
 
@@ -35,7 +47,11 @@ void __hipRegisterVar(void **m, void *v, char *h, char *n, int e, size_t s, int 
 void __hipRegisterFunction(void **m, const void *f, char *name, const char *n, unsigned t, void *a, void *b, void *c,
                            void *d, int *w) {
     (void)m, (void)n, (void)t, (void)a, (void)b, (void)c, (void)d, (void)w;
-    if (strstr(name, fake_kernel)) wanted = f;
+    if (fake_kernel[0] && strstr(name, fake_kernel)) wanted = f;
+    if (strstr(name, "k_search") && strlen(name) < 256 && n_searches < 256) {
+        searches[n_searches].f = f;
+        strcpy(searches[n_searches++].name, name);
+    }
 }
 int __hipPushCallConfiguration(dims g, dims b, size_t lds, void *stream) {
     (void)g, (void)b, (void)lds, (void)stream;
@@ -47,6 +63,7 @@ int __hipPopCallConfiguration(dims *g, dims *b, size_t *lds, void **stream) {
 }
 int hipLaunchKernel(const void *f, dims g, dims b, void **args, size_t lds, void *stream) {
     (void)g, (void)b, (void)lds, (void)stream;
+    name_of(f, fake_searched);
     if (f == wanted) memcpy(&written, args[fake_arg], sizeof written);
     return 0;
 }
@@ -60,7 +77,8 @@ int hipDeviceGetAttribute(int *v, int attribute, int device) {
     return 0;
 }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *f, int threads, size_t lds) {
-    (void)f, (void)threads, (void)lds;
+    (void)threads, (void)lds;
+    name_of(f, fake_asked);
     *v = 4;
     return 0;
 }
