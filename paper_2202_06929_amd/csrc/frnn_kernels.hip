@@ -655,7 +655,8 @@ __device__ __forceinline__ unsigned int xcd_first_block(unsigned int x, unsigned
 // an event with many long lists waited for its atomics, one per wave that writes lists
 // out: 87 us against 30 for 60,000 points with some 45 neighbours each, 45 against 22
 // for 20,000 in denser ones, 32.4 against 27.5 for a 120k-point event where 2% of the
-// lists are long.
+// lists are long.  The lanes of a wave add one each to the same address; the compiler makes
+// one atomic of theirs, by the first lane, of as many as they are (a test looks for it).
 constexpr int kLongCount = 1, kHugeCount = 2, kExtCount = 3;  // words of an XCD's line of counters
 __device__ __forceinline__ unsigned int *long_counter(unsigned int *claims, unsigned int xcd, int which) {
     return claims + xcd * kClaimStride + which;
