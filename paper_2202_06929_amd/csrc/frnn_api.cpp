@@ -186,8 +186,7 @@ Workspace layout(void *base, long long rows, long long cells, int n_events, int 
     const int64_t groups_kept = (tiles_kept + kKeptGroup - 1) / kKeptGroup;
     ws.sums_kept = cv.take<unsigned long long>(tiles_kept);
     ws.sums_kept2 = cv.take<unsigned long long>(groups_kept);
-    // One padding row after the last: the search requests the row after each query.
-    ws.sorted = cv.take<float>(static_cast<size_t>(rows + 1) * dpad);
+    ws.sorted = cv.take<float>(static_cast<size_t>(rows) * dpad);
     ws.sorted_id = cv.take<unsigned int>(2 * rows);
     ws.kept = cv.take<unsigned int>(rows);
     ws.long_slots = cv.take<unsigned int>(rows);

@@ -70,14 +70,14 @@ constexpr long long kTilePointsFrom = 1 << 19;
 constexpr int bin_span_for(long long max_n) {
     return max_n > kBinMaxRows ? 0 : (max_n > kBinMaxShares * kKeysBlock ? 2 * kKeysBlock : kKeysBlock);
 }
-// Most tiles an event of n rows can have: with the shift at its largest, cells_max /
-// 2^kTileShiftMax + 1; below it n 2^(shift + 1) > n_cells tile_points.
+// Most tiles an event of n rows can have: n_cells / 2^shift rounded up, where with the shift
+// at its largest n_cells <= cells_max, and below it n_cells / 2^shift < 2n / tile_points.
 constexpr int bin_tiles_bound(long long n, int tile_points) {
-    const long long by_points = 2 * n / tile_points + 1;
-    const long long by_cells = ((2 * n > 32768 ? 2 * n : 32768) >> kTileShiftMax) + 1;
+    const long long by_points = (2 * n + tile_points - 1) / tile_points;
+    const long long by_cells = ((2 * n > 32768 ? 2 * n : 32768) + (1 << kTileShiftMax) - 1) >> kTileShiftMax;
     return static_cast<int>(by_points > by_cells ? by_points : by_cells);
 }
-static_assert(bin_tiles_bound(kBinMaxRows, kTilePointsMin) <= kBinMaxTiles + 1, "the tiles of an event fit k_bin's LDS");
+static_assert(bin_tiles_bound(kBinMaxRows, kTilePointsMin) <= kBinMaxTiles, "the tiles of an event fit k_bin's LDS");
 // Tiles of many points are shared among workgroups of k_tiles: cells are of one size, so
 // that points that crowd into few of them (narrow axes beside an outlier) would leave a
 // whole event to one workgroup.  A tile of crowd_part points, eight times what a tile is
@@ -167,7 +167,7 @@ struct Plan {
     int reach;              // neighbour cells searched on each side, per axis
     int abort;              // a coordinate was NaN or infinite
     int axes;               // binned coordinates (3 or 4)
-    int tile_shift;         // log2 of the cells per tile
+    int tile_shift;         // log2 of the cells per tile (set, as the next, where points are binned through tiles)
     int n_tiles;            // tiles of the event
 };
 
@@ -177,10 +177,8 @@ __host__ __device__ constexpr int cell_bits(int axes) { return axes == 4 ? 8 : 1
 // Single-address atomics serialise across the chip (about 11 ns each), so these
 // are touched only by rare events (bad input) or once.
 struct Counters {
-    unsigned int pad0;
     unsigned int abort;            // some event had a non-finite coordinate
     unsigned int capped;           // queries with more than K neighbours (summed after the search)
-    unsigned int pad1;
     unsigned long long tested;     // pairs examined, summed over the search workgroups
     unsigned long long survived;   // pairs that reached the second stage, likewise
 };
@@ -245,11 +243,10 @@ struct Workspace {
 int64_t cells_max_for(int64_t n);
 int dpad_for(int d);
 // Fills descs[e] (if not null) for events given by row offsets; returns the total
-// cell count.
-// (pts stays null; callers set it).
+// cell count (pts stays null; callers set it).
 long long describe_events(const int64_t *event_offsets, int n_events, EventDesc *descs);
 // Workspace layout for events of the given sizes (host arithmetic; base may be null).
-Workspace layout(void *base, long long rows, long long cells, int n_events, int d, int64_t edge_capacity);
+Workspace layout(void *base, long long rows, long long cells, int n_events, int d);
 
 // Pinned host memory that the kernels of a call write its result into; one per calling
 // thread, so it serves whichever device is current in a call: it is portable, and its

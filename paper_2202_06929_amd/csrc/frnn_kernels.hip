@@ -189,17 +189,6 @@ __device__ __forceinline__ T wave_scan_add(T x) {
     return x;
 }
 
-// Inclusive prefix maximum across the 64 lanes (values >= 0).
-__device__ __forceinline__ unsigned int wave_scan_max(unsigned int x) {
-    x = max(x, dpp_move<kRowShr1>(x));
-    x = max(x, dpp_move<kRowShr2>(x));
-    x = max(x, dpp_move<kRowShr4>(x));
-    x = max(x, dpp_move<kRowShr8>(x));
-    x = max(x, dpp_move<kRowBcast15, 0xa>(x));
-    x = max(x, dpp_move<kRowBcast31, 0xc>(x));
-    return x;
-}
-
 // Value of lane 63 in every lane.
 __device__ __forceinline__ unsigned int lane63(unsigned int x) { return __builtin_amdgcn_readlane(x, 63); }
 __device__ __forceinline__ unsigned long long lane63(unsigned long long x) {
@@ -528,6 +517,7 @@ __device__ void derive_plan(const BoundsPartial *__restrict__ part, int nparts, 
     out->reach = cell_div;
     out->abort = bad;
     out->axes = axes;
+    if (tile_points == 0) return;  // not binned through tiles
     // Cells per tile of the tile pass: the power of two that gives a tile at most
     // tile_points points on average.
     int shift = 0;
@@ -574,7 +564,7 @@ constexpr int kMaxCellTiles = ((1 << 24) + kScanTile - 1) / kScanTile + 2;
 // event's rows.  Two points per thread halve the blocks, and with them the
 // blocks' atomic adds to each tile total, which pays for large events.
 __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
-                                                     float r, int cell_div, int tile_points,
+                                                     float r, int cell_div,
                                                      const EventDesc *__restrict__ ev, EventDesc ev0, int ev_from_arg,
                                                      const BoundsPartial *__restrict__ part, int nparts,
                                                      Plan *__restrict__ plans, Counters *__restrict__ ctr,
@@ -605,7 +595,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_keys(int d, Dims dd, int axes,
         }
     }
     if (wave_id() == 0)
-        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points, &P);
+        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, 0, &P);
     const int tile_end = static_cast<int>((E.cell0 + E.cells_max - 1) / kScanTile);
     const int ntiles = tile_end - E.tile0 + 1;
     for (int t = threadIdx.x; t < ntiles; t += kKeysBlock) tile_count[t] = 0ull;
@@ -2347,7 +2337,6 @@ __device__ __forceinline__ void wave_list(const SortedRows<DP> &pts, const unsig
     if (h <= 64u) wave_emit<1>(ids, h, row0, out);
     else if (h <= 128u) wave_emit<2>(ids, h, row0, out);
     else if (h <= 256u) wave_emit<4>(ids, h, row0, out);
-    else if (h <= 512u) wave_emit<8>(ids, h, row0, out);
     else wave_emit<kWaveKeys / 64>(ids, h, row0, out);
     wave_lds_sync();
 }
@@ -2838,7 +2827,7 @@ hipError_t enqueue_build(const LaunchArgs &a, const Workspace &ws) {
         mark(2);  // there is no stage 2: stage 3 begins here
     } else {
         hipLaunchKernelGGL(k_keys, dim3(gkeys, a.n_events), dim3(kKeysBlock), 0, a.stream, a.d, dd, a.axes,
-                           a.r, a.cell_div, a.tile_points, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
+                           a.r, a.cell_div, ws.ev, a.ev0, a.ev_from_arg, ws.part, a.bounds_blocks, ws.plans, ws.ctr,
                            ws.pcell, ws.rank, ws.cell_count, ws.sums_cells);
         mark(2);
         hipLaunchKernelGGL(k_scan_cells, dim3(ws.tiles_cells_n), dim3(kBlock), 0, a.stream, ws.cell_count, ws.cells,
