@@ -52,12 +52,13 @@ constexpr int kKeysSpan = kKeysBlock * kKeysPer;
 // kBinMaxRows rows, which is what the tables hold (a share per thread of k_tiles, two rows
 // per thread of k_bin), not where the other binning overtakes it: whole builds of 2^20 rows
 // of 3, 8, 12 and 32 floats 200, 286, 416 and 1,652 us through tiles and 250, 338, 467 and
-// 1,726 by atomics, of one row more 252, 338, 476 and 1,737 (by atomics).  Shares of kKeysBlock or twice as many rows, at most kBinMaxShares an
-// event; tiles of up to 2^kTileShiftMax cells and, on average, at most kTilePointsMin
-// points: fewer leave the shares' segments of a tile too short, more too few tiles for
-// the CUs (120k points: whole build 64.9, 65.3, 66.5 and 70.7 us with 256, 512, 1024 and
-// 2048; 300k points 138.8, 138.0, 141.8, 141.5).  Calls of more than kTilePointsFrom rows
-// have tiles enough for kTilePointsLarge (a batch of 5.6M rows 1754, 1651, 1639, 1660).
+// 1,726 by atomics, of one row more 252, 338, 476 and 1,737 (by atomics).  Shares of
+// kKeysBlock or twice as many rows, at most kBinMaxShares an event; tiles of up to
+// 2^kTileShiftMax cells and, on average, at most kTilePointsMin points: fewer leave the
+// shares' segments of a tile too short, more too few tiles for the CUs (120k points: whole
+// build 64.9, 65.3, 66.5 and 70.7 us with 256, 512, 1024 and 2048; 300k points 138.8,
+// 138.0, 141.8, 141.5).  Calls of more than kTilePointsFrom rows have tiles enough for
+// kTilePointsLarge (a batch of 5.6M rows 1754, 1651, 1639, 1660).
 constexpr int kTilesBlock = 512;
 constexpr int kBinMaxShares = 512;
 constexpr int kBinMaxRows = kBinMaxShares * kKeysBlock * 2;
@@ -80,28 +81,35 @@ constexpr int bin_tiles_bound(long long n, int tile_points) {
 static_assert(bin_tiles_bound(kBinMaxRows, kTilePointsMin) <= kBinMaxTiles, "the tiles of an event fit k_bin's LDS");
 // Tiles of many points are shared among workgroups of k_tiles: cells are of one size, so
 // that points that crowd into few of them (narrow axes beside an outlier) would leave a
-// whole event to one workgroup.  A tile of crowd_part points, eight times what a tile is
-// aimed at, or more gets a workgroup for each crowd_part of them beside its own.  Its points
-// are counted before by the shares that hold many of them (crowd_reported: three quarters
-// of the tile's mean share, so that a count comes short by less than three quarters of
-// crowd_points); ordinary tiles' shares stay below and add nothing.
-// 120k points in one tile: 581 us for the rows' stage by one workgroup, 64 in parts; the
-// whole build 782 and 257 us, of 400k points 2,490 and 1,355.
+// whole event to one workgroup.  A tile of crowd_least points, eight times what a tile is
+// aimed at, or more gets, beside its own workgroup, one for every half of crowd_least, from
+// the blocks that the event's tiles leave over (for every whole, two, ... of crowd_least
+// where those are too few).  Its points are counted before by the shares that hold many of
+// them (crowd_reported: three quarters of the tile's mean share, so that a count comes short
+// by less than three quarters of crowd_points); ordinary tiles' shares stay below and add
+// nothing.  120k points in one tile: 581 us for the rows' stage by one workgroup, 61 in
+// parts; the whole build 782 and 262 us, of 400k points 2,490 and 1,353.
 // (tile_points is a power of two: quotients are shifts.)
-constexpr int crowd_shift(int tile_points) { return __builtin_ctz(tile_points) + 3; }
-constexpr int crowd_part(int tile_points) { return 1 << crowd_shift(tile_points); }
+constexpr int crowd_least(int tile_points) { return 8 * tile_points; }
 constexpr int crowd_points(int tile_points, int shares) {
-    return 16 * shares > crowd_part(tile_points) ? 16 * shares : crowd_part(tile_points);
+    return 16 * shares > crowd_least(tile_points) ? 16 * shares : crowd_least(tile_points);
 }
 constexpr bool crowd_reported(unsigned int points, int tile_points, int shares) {
     return (points & 0xffffu) * ((4u * shares) & 0xffffu) >= 3u * static_cast<unsigned int>(crowd_points(tile_points, shares));
 }
-// Where the counts of an event's tiles begin: an event of crowd_part rows and more has at
-// most 2n / tile_points + 1 tiles, fewer than lie before the next event's.
+// Where the counts of an event's tiles begin: an event of crowd_least rows and more has
+// fewer than 2n / tile_points + 1 tiles, fewer than lie before the next event's.
 constexpr long long crowd_at(long long row0, int tile_points) { return row0 >> (__builtin_ctz(tile_points) - 2); }
-// Workgroups beside a tile's own, for its count.
-constexpr int crowd_more(int counted, int tile_points, int shares) {
-    return counted >= crowd_points(tile_points, shares) ? counted >> crowd_shift(tile_points) : 0;
+// Blocks of k_tiles for an event: its tiles at most, and some more, so that there are
+// always blocks over.
+constexpr int tile_blocks(int n, int tile_points) {
+    return bin_tiles_bound(n, tile_points) + (n >> (__builtin_ctz(tile_points) + 5)) + 2;
+}
+// Log2 of the points per workgroup beside the tiles' own, for the sum of an event's counts.
+constexpr int crowd_shift(unsigned int crowded, int n, int n_tiles, int tile_points) {
+    int shift = __builtin_ctz(tile_points) + 2;
+    while (crowded >> shift > static_cast<unsigned int>(tile_blocks(n, tile_points) - n_tiles)) ++shift;
+    return shift;
 }
 constexpr int kPlaceBlock = 256;     // threads per workgroup of the placement pass
 constexpr int kPlaceTile = 256;      // queries per workgroup of the placement pass (and kept tile)

@@ -920,14 +920,10 @@ __device__ __forceinline__ int2 event_block(const EventDesc *__restrict__ ev, in
     }
     return make_int2(lo, static_cast<int>(blockIdx.x - blocks_before(ev[lo].row0, lo, rows, extra)));
 }
-// Blocks of k_tiles for an event of n rows: 2n / tile_points tiles and n / crowd_part more
-// parts of crowded ones, that is one block for every tile_block_rows rows, and at most these
-// more.
-constexpr int kTilesExtra = 10;
-__host__ __device__ constexpr int tile_block_rows(int tile_points) {
-    static_assert(crowd_part(512) == 8 * 512, "17 blocks for 8 tile_points rows");
-    return 8 * tile_points / 17;
-}
+// Blocks of k_tiles in a one-dimensional grid: tile_blocks(n) is at most one for every
+// tile_block_rows rows, and these more.
+constexpr int kTilesExtra = 12;
+constexpr int tile_block_rows(int tile_points) { return 32 * tile_points / 65; }
 
 // Grid (shares, n_events): block (b, e) takes rows [b span, (b + 1) span) of event e.  It
 // writes each row's number and packed cell in the order of the rows' tiles to the same
@@ -1080,21 +1076,27 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     if (P.abort || E.n == 0) return;
     const int shares = bin_shares(E.n, span);
     const unsigned int *__restrict__ counts = crowd + crowd_at(E.row0, tile_points);
-    int part = 0;
+    // Workgroups of tile k beside its own.
+    auto more_of = [&](int k, int shift) -> unsigned int {
+        const unsigned int counted = counts[k];
+        return counted >= static_cast<unsigned int>(crowd_points(tile_points, shares)) ? counted >> shift : 0u;
+    };
+    int part = 0, parts = 1;
     if (t >= P.n_tiles) {
         // The x-th of the parts past the first of the event's tiles.
-        const unsigned int x = static_cast<unsigned int>(t - P.n_tiles);
-        if (x >= uniform(crowded_v) >> crowd_shift(tile_points)) return;
+        const unsigned int x = static_cast<unsigned int>(t - P.n_tiles), crowded = uniform(crowded_v);
+        if (x >= crowded >> (__builtin_ctz(tile_points) + 2)) return;
+        const int shift = crowd_shift(crowded, E.n, P.n_tiles, tile_points);
         const int per = (P.n_tiles + kTilesBlock - 1) / kTilesBlock;
         const int t0 = min(static_cast<int>(threadIdx.x) * per, P.n_tiles), t1 = min(t0 + per, P.n_tiles);
         unsigned int more = 0;
-        for (int k = t0; k < t1; ++k) more += crowd_more(static_cast<int>(counts[k]), tile_points, shares);
+        for (int k = t0; k < t1; ++k) more += more_of(k, shift);
         uint2 all;
         unsigned int before = block_prefix2<kTWaves>(make_uint2(more, 0u), scratch[2], all).x;
         if (x >= all.x) return;
         if (before <= x && x < before + more) {
             for (int k = t0; k < t1; ++k) {
-                const unsigned int m = crowd_more(static_cast<int>(counts[k]), tile_points, shares);
+                const unsigned int m = more_of(k, shift);
                 if (before <= x && x < before + m) my_part = make_int2(k, static_cast<int>(x - before) + 1);
                 before += m;
             }
@@ -1114,8 +1116,8 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     const unsigned int key0 = static_cast<unsigned int>(t) << P.tile_shift;  // the tile's first cell
     const int cells = min(1 << P.tile_shift, P.n_cells - static_cast<int>(key0));
     for (int c = threadIdx.x; c < cells; c += kTilesBlock) cursor[c] = 0u;
-    const unsigned int counted = uniform(crowded_v) ? counts[t] : 0u;
-    const int parts = crowd_more(static_cast<int>(counted), tile_points, shares) + 1;
+    if (const unsigned int crowded = uniform(crowded_v))
+        parts += static_cast<int>(more_of(t, crowd_shift(crowded, E.n, P.n_tiles, tile_points)));
     const bool whole = parts == 1;
     if (!whole)
         for (int c = threadIdx.x; c < cells; c += kTilesBlock) weight[c] = 0u;
@@ -2726,7 +2728,7 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
         const int flat = flat_grid(a, rows) ? a.n_events : 0;
         const dim3 grid = flat ? dim3(static_cast<unsigned int>(
                                      blocks_before(rows, a.n_events, tile_block_rows(a.tile_points), kTilesExtra) + 1))
-                               : dim3(bin_tiles_bound(a.max_n, a.tile_points) + a.max_n / crowd_part(a.tile_points), a.n_events);
+                               : dim3(tile_blocks(a.max_n, a.tile_points), a.n_events);
         hipLaunchKernelGGL(k_tiles<DP>, grid, dim3(kTilesBlock), 0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0,
                            a.ev_from_arg, flat, a.tile_points, ws.plans,
                            bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,

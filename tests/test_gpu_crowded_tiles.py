@@ -1,11 +1,11 @@
 """Binning of events whose points crowd into few tiles.
 
-A tile of 4,096 points and more (8,192 in calls beyond 2^19 rows) gets a workgroup for each
-4,096 of them beside its own; its points are counted by the shares of 1,024 rows that hold
-enough of them.  Events with narrow binned axes beside an outlier put all their points into
-one tile, one cell or a few: sizes lie around the first count, at whole and broken parts
-and with shares of 2,048 rows; batches mix them with empty, small and spread events, in
-both grids.  Edges against the CPU oracle, byte for byte (it bins the leading coordinates,
+A tile of 4,096 points and more (8,192 in calls beyond 2^19 rows) gets workgroups beside its
+own, one for every 2,048 of them (or more, where the event's tiles leave few blocks over);
+its points are counted by the shares of 1,024 rows that hold enough of them.  Events with
+narrow binned axes beside an outlier put all their points into one tile, one cell or a few:
+sizes lie around the first count, at whole and broken parts and with shares of 2,048 rows;
+batches mix them with empty, small and spread events, in both grids.  Edges against the CPU oracle, byte for byte (it bins the leading coordinates,
 which are spread).  The rows' stage of a crowded event is timed against a spread one's.
 """
 
