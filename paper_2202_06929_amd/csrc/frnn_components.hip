@@ -160,11 +160,11 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_init(unsigned int *parent, long
 // pass, which then finds equal roots for its edges and swaps nothing.  Lanes of a
 // wave that share a source (edges come grouped by source) take the minimum of their
 // targets, the first one where targets ascend and else by a segmented reduction, and
-// one lane per source does a device-scope atomicMin on the source's parent.  The parent array then still
-// points only to smaller ids and every entry to a neighbour or itself: each
-// vertex is hooked at most under one neighbour, a valid union of two trees, as
-// every vertex is still a root before this pass.  Whatever this pass leaves
-// unjoined, the union-find pass joins.
+// one lane per source does a device-scope atomicMin on the source's parent.  The parent
+// array then still points only to smaller ids and every entry to a neighbour or itself:
+// each vertex is hooked at most under one neighbour, a valid union of two trees, as every
+// vertex is still a root before this pass.  Whatever this pass leaves unjoined, the
+// union-find pass joins.
 __global__ __launch_bounds__(kCcBlock) void k_cc_minhook(const long long *__restrict__ src,
                                                          const long long *__restrict__ dst, long long n_edges,
                                                          long long n, const float *__restrict__ scores,

@@ -95,7 +95,9 @@ constexpr int crowd_points(int tile_points, int shares) {
     return 16 * shares > crowd_least(tile_points) ? 16 * shares : crowd_least(tile_points);
 }
 constexpr bool crowd_reported(unsigned int points, int tile_points, int shares) {
-    return (points & 0xffffu) * ((4u * shares) & 0xffffu) >= 3u * static_cast<unsigned int>(crowd_points(tile_points, shares));
+    // (A product of 24-bit factors: at most 2,048 points and 512 shares.)
+    return (points & 0xffffu) * ((4u * shares) & 0xffffu) >=
+           3u * static_cast<unsigned int>(crowd_points(tile_points, shares));
 }
 // Where the counts of an event's tiles begin: an event of crowd_least rows and more has
 // fewer than 2n / tile_points + 1 tiles, fewer than lie before the next event's.

@@ -3,12 +3,13 @@
 // Pipeline of one call (paper, Section 3.4: bin the points by three projected
 // coordinates into grid cells, then visit only the cells around each query):
 //   k_bounds      min/max of the binned coordinates and a non-finite check over
-//                 all coordinates; clears the histogram, tile totals, counters
+//                 all coordinates; clears what the call counts in
 //   k_bin         grid plan (cell edge, cells per axis), cell of every point, each share
 //                 of points sorted by tile (a run of cells) in LDS
 //   k_tiles       each tile's points gathered from the shares, counted and ordered by
 //                 cell in LDS: first sorted row of each cell, the search's shares of equal
-//                 work (cells' fixed costs plus queries), rows copied into cell order
+//                 work (cells' fixed costs plus queries), rows copied into cell order;
+//                 tiles of many points by several workgroups
 //   or, for calls with an event of more than kBinMaxRows rows, in place of the two:
 //   k_keys        grid plan, cell key of every point, histogram with in-cell arrival
 //                 rank, per-tile histogram totals
@@ -18,9 +19,9 @@
 //   k_search      each wave takes a share of equal work in cell order: a
 //                 cell's queries against the (2R+1)^(axes-1) contiguous runs of
 //                 neighbouring cells along axis 0; each lane holds one candidate (its
-//                 first four coordinates), query rows are wave-uniform; an exact
-//                 early exit after the first two to four terms of the distance
-//                 sum; ballots queue the survivors, whose sums are finished 64 at a
+//                 leading coordinates, two to four), those of the query are
+//                 wave-uniform; an exact early exit after as many terms of the
+//                 distance sum; ballots queue the survivors, whose sums are finished 64 at a
 //                 time; the lists of pending queries are stored as found, in batches
 //   k_kept_sums   kept totals per placement tile and per group of tiles
 //   k_place       output offsets from the totals and a block scan; each short list
@@ -348,8 +349,9 @@ __global__ __launch_bounds__(kBlock) void k_bounds(int d, Dims dd,
     // element: a minimum, a maximum and a comparison each (with the column tracked and
     // compared per element the pass was bound by its instructions: 67 us against 52 on a
     // batch of 5.6M 8-D points, 8.9 against 5.5 on 300k 12-D and 8.2 against 4.3 on 47k
-    // 10-D ones, whose rows are read one float at a time).  Several loads are in flight per thread, issued together also for the
-    // last, partial round (the grid gives most threads exactly four).
+    // 10-D ones, whose rows are read one float at a time).  Several loads are in flight
+    // per thread, issued together also for the last, partial round (the grid gives most
+    // threads exactly four).
     if (vec4) {
         const float4 *X4 = reinterpret_cast<const float4 *>(Xe);
         const long long nv = total / 4;
@@ -963,7 +965,8 @@ __global__ __launch_bounds__(kKeysBlock) void k_bin(int d, Dims dd, int axes, fl
         }
     }
     if (wave_id() == 0)
-        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points, &P);
+        derive_plan(part + static_cast<size_t>(e) * nparts, nparts, r, cell_div, axes, E.cells_max, E.n, tile_points,
+                    &P);
     for (int t = threadIdx.x; t < kBinMaxTiles; t += kKeysBlock) start[t] = 0u;
     __syncthreads();
     if (share == 0 && threadIdx.x == 0) {
@@ -1431,7 +1434,7 @@ struct RunMap {
 };
 
 // Waves per SIMD the search asks the register allocator for: a lane holds only a
-// candidate's first four coordinates, so rows of up to 16 floats fit in 64
+// candidate's leading coordinates, so rows of up to 16 floats fit in 64
 // registers (8 waves, some scalar registers spilled to vector lanes); wider rows,
 // whose second stage holds the rest of a row, keep the compiler's choice (48 floats:
 // held just below the 128 registers of 4 waves).
@@ -1567,7 +1570,7 @@ __global__ __launch_bounds__(kBlock, kSearchWaves<DP>) void k_search(const float
     // Second stage for ring entries [h, h + nb): lane l takes entry h + l and
     // adds terms kLead.. of the definition to the first stage's partial sum, in
     // the same order.  An entry names its query and the candidate's sorted row; the
-    // remaining coordinates are loaded here (the chunk holds only the first four), so
+    // remaining coordinates are loaded here (the chunk holds only the leading ones), so
     // entries outlive their chunk and cell.
     auto finish_rows = [&](unsigned int h, unsigned int nb) {
         survived += nb;

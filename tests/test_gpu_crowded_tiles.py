@@ -5,8 +5,9 @@ own, one for every 2,048 of them (or more, where the event's tiles leave few blo
 its points are counted by the shares of 1,024 rows that hold enough of them.  Events with
 narrow binned axes beside an outlier put all their points into one tile, one cell or a few:
 sizes lie around the first count, at whole and broken parts and with shares of 2,048 rows;
-batches mix them with empty, small and spread events, in both grids.  Edges against the CPU oracle, byte for byte (it bins the leading coordinates,
-which are spread).  The rows' stage of a crowded event is timed against a spread one's.
+batches mix them with empty, small and spread events, in both grids.  Edges against the CPU
+oracle, byte for byte (it bins the leading coordinates, which are spread).  The rows' stage
+of a crowded event is timed against a spread one's.
 """
 
 import numpy as np
@@ -57,6 +58,24 @@ def test_other_grids(config):
     X = crowded(30_000, 8, 3, 4.0, 7)
     X[:, 0] *= 0.01
     check(X, 0.2, 12, **config)
+
+
+@pytest.mark.parametrize("n", [20_000, 60_000])
+def test_few_blocks_over(n):
+    # Cells that divide into nearly as many tiles as there are blocks, all points in one row of them.
+    r = np.float32(0.01)
+    c = r * np.float32(1.0009765625)
+    rng = np.random.Generator(np.random.PCG64(n))
+    X = rng.uniform(0, 1e-5, size=(n, 3))
+    wide = 100 if n == 20_000 else 170  # 100 x 98 and 170 x 172 cells: 77 of 78 and 229 of 234 tiles
+    high = {100: 98, 170: 172}[wide]
+    X[:, 0] = rng.uniform(0, (wide - 0.5) * c, size=n)
+    X[:2, 0] = 0, (wide - 0.5) * c
+    X[5, 1] = (high - 0.5) * c
+    X = X.astype(np.float32)
+    _, stats = frnn.build(torch.from_numpy(X).to(DEV), float(r), 64, return_stats=True)
+    assert stats["grid"][:3] == [wide, high, 1], stats["grid"]
+    check(X, float(r), 64)
 
 
 def test_shares_of_2048_rows():
