@@ -95,6 +95,20 @@ def test_batches(others):
         assert np.array_equal(edges[:, eo[e]:eo[e + 1]], oracle.frnn_grid(X, 0.1, 64)), e
 
 
+def test_one_workspace_for_events_in_turn():
+    n, d, r, K = 30_000, 8, 0.25, 64
+    rng = np.random.Generator(np.random.PCG64(4))
+    evs = [crowded(n, d, 4, 5.0, 1), rng.uniform(-1, 1, size=(n, d)).astype(np.float32), crowded(n, d, 3, 5.0, 2),
+           crowded(n - 9_000, d, 4, 5.0, 3), crowded(n, d, 4, 5.0, 1)]
+    ws = torch.full((frnn.workspace_bytes(n, d),), 0xA5, dtype=torch.uint8, device=DEV)
+    out = torch.empty((2, K * n), dtype=torch.int64, device=DEV)
+    for k, X in enumerate(evs):
+        print(f"event {k}: n={len(X)}", flush=True)
+        st, E = frnn.build_into(torch.from_numpy(X).to(DEV), r, K, ws, out[0], out[1])
+        assert st == frnn.FRNN_OK
+        assert np.array_equal(out[:, :E].cpu().numpy(), oracle.frnn_grid(X, r, K)), k
+
+
 def stage_us(X, r, stage):
     pts = torch.from_numpy(X).to(DEV)
     n, d = X.shape
