@@ -102,10 +102,11 @@ constexpr bool crowd_reported(unsigned int points, int tile_points, int shares) 
 // Where the counts of an event's tiles begin: an event of crowd_least rows and more has
 // fewer than 2n / tile_points + 1 tiles, fewer than lie before the next event's.
 constexpr long long crowd_at(long long row0, int tile_points) { return row0 >> (__builtin_ctz(tile_points) - 2); }
-// Blocks of k_tiles for an event: its tiles at most, and some more, so that there are
-// always blocks over.
+// Blocks of k_tiles for an event: its tiles at most, and some more where a tile may be
+// crowded, so that there are always blocks over.
 constexpr int tile_blocks(int n, int tile_points) {
-    return bin_tiles_bound(n, tile_points) + (n >> (__builtin_ctz(tile_points) + 5)) + 2;
+    const int more = n < crowd_least(tile_points) ? 0 : (n >> (__builtin_ctz(tile_points) + 5)) + 2;
+    return bin_tiles_bound(n, tile_points) + more;
 }
 // Log2 of the points per workgroup beside the tiles' own, for the sum of an event's counts.
 constexpr int crowd_shift(unsigned int crowded, int n, int n_tiles, int tile_points) {

@@ -923,8 +923,8 @@ __device__ __forceinline__ int2 event_block(const EventDesc *__restrict__ ev, in
     return make_int2(lo, static_cast<int>(blockIdx.x - blocks_before(ev[lo].row0, lo, rows, extra)));
 }
 // Blocks of k_tiles in a one-dimensional grid: tile_blocks(n) is at most one for every
-// tile_block_rows rows, and these more.
-constexpr int kTilesExtra = 12;
+// tile_block_rows rows, and these more (an odd number, as below).
+constexpr int kTilesExtra = 11;
 constexpr int tile_block_rows(int tile_points) { return 32 * tile_points / 65; }
 
 // Grid (shares, n_events): block (b, e) takes rows [b span, (b + 1) span) of event e.  It
@@ -1073,9 +1073,12 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     int t = which.y;
     const EventDesc E = ev_from_arg ? ev0 : ev[which.x];
     const Plan P = plans[which.x];
-    // Points of crowded tiles: a vector load, so that only the blocks that use it at once wait.
-    const unsigned int crowded_v = static_cast<unsigned int>(
-        __hip_atomic_load(crowd_sum + which.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
+    // Points of crowded tiles (no tile is where crowd_sum is null): a vector load, so that only
+    // the blocks that use it at once wait.
+    unsigned int crowded_v = 0u;
+    if (crowd_sum)
+        crowded_v = static_cast<unsigned int>(
+            __hip_atomic_load(crowd_sum + which.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
     if (P.abort || E.n == 0) return;
     const int shares = bin_shares(E.n, span);
     const unsigned int *__restrict__ counts = crowd + crowd_at(E.row0, tile_points);
@@ -1087,6 +1090,7 @@ __global__ __launch_bounds__(kTilesBlock) void k_tiles(int d, int vec4, int span
     int part = 0, parts = 1;
     if (t >= P.n_tiles) {
         // The x-th of the parts past the first of the event's tiles.
+        if (!crowd_sum || E.n < crowd_least(tile_points)) return;
         const unsigned int x = static_cast<unsigned int>(t - P.n_tiles), crowded = uniform(crowded_v);
         if (x >= crowded >> (__builtin_ctz(tile_points) + 2)) return;
         const int shift = crowd_shift(crowded, E.n, P.n_tiles, tile_points);
@@ -2728,13 +2732,19 @@ void launch_rows(const LaunchArgs &a, const Workspace &ws, int vec4) {
     const long long nb = (static_cast<long long>(a.max_n) + kBlock - 1) / kBlock;
     const int gs = static_cast<int>(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
     if (a.bin_span) {
+        // An odd number of blocks an event: they are dealt to the XCDs in turn, so that with a
+        // multiple of 8 the events' first tiles, in small events the only ones with points,
+        // would all go to one XCD (2,000 events of one point: 31 us with 9 blocks each, 43
+        // with 10, 87 with 8).
         const int flat = flat_grid(a, rows) ? a.n_events : 0;
         const dim3 grid = flat ? dim3(static_cast<unsigned int>(
                                      blocks_before(rows, a.n_events, tile_block_rows(a.tile_points), kTilesExtra) + 1))
-                               : dim3(tile_blocks(a.max_n, a.tile_points), a.n_events);
+                               : dim3(tile_blocks(a.max_n, a.tile_points) | 1, a.n_events);
         hipLaunchKernelGGL(k_tiles<DP>, grid, dim3(kTilesBlock), 0, a.stream, a.d, vec4, a.bin_span, ws.ev, a.ev0,
                            a.ev_from_arg, flat, a.tile_points, ws.plans,
-                           bin_ents(ws), bin_table(ws), crowd_counts(ws), crowd_sums(ws), ws.cell_start, ws.sorted, ws.sorted_id, ws.wave_start,
+                           bin_ents(ws), bin_table(ws), crowd_counts(ws),
+                           a.max_n < crowd_least(a.tile_points) ? nullptr : crowd_sums(ws), ws.cell_start, ws.sorted,
+                           ws.sorted_id, ws.wave_start,
                            a.search_blocks * kWaves, ws.rows, ws.claims);
     } else {
         hipLaunchKernelGGL(k_scatter<DP>, dim3(gs, a.n_events), dim3(kBlock), 0, a.stream, a.d, vec4, ws.ev, a.ev0,
